@@ -46,7 +46,7 @@ struct PInt {
   static constexpr int value = V;
 };
 
-// NBD: column blocks (of 16) holding dense columns, 0 when all columns are probes.
+// NBD: NB when the columns are dense, 0 when they are probes.
 template <int RB, int NB, int NBD, bool FAST>
 __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int by) {
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
@@ -159,23 +159,20 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         uint4 bh = uint4{0, 0, 0, 0}, bl = uint4{0, 0, 0, 0};
-        if (a.nz > 0) {
+        if constexpr (DENSE) {
+          const bool isd = 16 * nb + l16 < a.nd;
+          bh = select4(isd, dh[4 * nb + kb], bh);
+          bl = select4(isd, dl[4 * nb + kb], bl);
+        } else {
           const uint32_t word = zw[zrow[nb] + w];
           bh = expand_signs(__builtin_amdgcn_perm(word, word, psel), zmask[nb], zone[nb]);
-        }
-        if constexpr (DENSE) {
-          if (nb < NBD) {                          // static: column blocks that hold dense columns
-            const bool isd = 16 * nb + l16 < a.nd;
-            bh = select4(isd, dh[4 * nb + kb], bh);
-            bl = select4(isd, dl[4 * nb + kb], bl);
-          }
         }
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
           const int r = 16 * rb + l16;
           const uint4 av = *reinterpret_cast<const uint4*>(&xt[r * kProjSlice + 8 * ((4 * kb + g) ^ l16)]);
           acc[rb][nb] = mfma16x16x32(av, bh, acc[rb][nb]);
-          if (DENSE && nb < NBD) acc[rb][nb] = mfma16x16x32(av, bl, acc[rb][nb]);
+          if constexpr (DENSE) acc[rb][nb] = mfma16x16x32(av, bl, acc[rb][nb]);
         }
       }
     }
@@ -593,6 +590,14 @@ static bool plan_rblocks(ProjectArgs* jobs, int n) {
   return true;
 }
 
+// The instantiations that rows_per_wg's row counts reach: sign columns in 16-row blocks or,
+// up to 64 columns, 32-row ones (48 stay in 16); dense columns (at most 32, never mixed
+// with signs) in 16-, 32- or 64-row blocks.
+template <int RB, int NB>
+constexpr bool kProjSigns = RB == 1 || (RB == 2 && NB <= 4 && NB != 3);
+template <int RB, int NB>
+constexpr bool kProjDense = NB <= 2;
+
 template <int RB, int NB>
 static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
   const bool fast = plan_rblocks<RB, NB>(bt.job, bt.njobs);
@@ -603,17 +608,18 @@ static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
     bt.blk0[j] = bt.blocks;
     bt.blocks += (bt.job[j].T_pad / (16 * RB * bt.job[j].rblocks)) * bt.job[j].B;
   }
-  const int nbd = (bt.job[0].nd + 15) / 16;
-#define DPRC_PROJECT_BATCH_CASE(NBDV)                                                                    \
-  if (nbd == NBDV) {                                                                                      \
-    if (fast) DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, true>), dim3(bt.blocks), dim3(kBlock), lds, st, bt); \
-    else DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, false>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);     \
-  }
-  DPRC_PROJECT_BATCH_CASE(0)
-  if constexpr (NB >= 1) { DPRC_PROJECT_BATCH_CASE(1) }
-  if constexpr (NB >= 2) { DPRC_PROJECT_BATCH_CASE(2) }
-#undef DPRC_PROJECT_BATCH_CASE
+  const bool dense = bt.job[0].nd > 0;
+#define DPRC_PROJECT_BATCH_CASE(NBDV)                                                                             \
+  if (fast) DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, true>), dim3(bt.blocks), dim3(kBlock), lds, st, bt); \
+  else DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, false>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);     \
   return hipGetLastError();
+  if (!dense) {
+    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_BATCH_CASE(0) }
+  } else {
+    if constexpr (kProjDense<RB, NB>) { DPRC_PROJECT_BATCH_CASE(NB) }
+  }
+#undef DPRC_PROJECT_BATCH_CASE
+  return hipErrorInvalidValue;
 }
 
 template <int RB>
@@ -630,12 +636,11 @@ static hipError_t launch_batch_rb(const ProjectBatch& bt, hipStream_t st) {
 hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st) {
   if (bt.njobs < 1 || bt.njobs > kProjMaxJobs) return hipErrorInvalidValue;
   const int rb = rows_per_wg / 16;
-  const int nbd = (bt.job[0].nd + 15) / 16;
   for (int j = 0; j < bt.njobs; ++j) {
     const ProjectArgs& a = bt.job[j];
     // one instantiation serves every job
-    if (a.ncols_pad != bt.job[0].ncols_pad || (a.nd + 15) / 16 != nbd || a.words_per_chunk % 16 != 0 ||
-        a.nd > 32 || a.nd > a.ncols_pad || a.T_pad % rows_per_wg != 0)
+    if (a.ncols_pad != bt.job[0].ncols_pad || (a.nd > 0) != (bt.job[0].nd > 0) || (a.nd > 0 && a.nz > 0) ||
+        a.words_per_chunk % 16 != 0 || a.nd > a.ncols_pad || a.T_pad % rows_per_wg != 0)
       return hipErrorInvalidValue;
   }
   switch (rb) {
@@ -648,21 +653,21 @@ hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st
 
 template <int RB, int NB>
 static hipError_t launch_rb_nb(ProjectArgs a, hipStream_t st) {
-  if (a.words_per_chunk % 16 != 0 || a.nd > 32 || a.nd > 16 * NB) return hipErrorInvalidValue;
+  if (a.words_per_chunk % 16 != 0 || a.nd > 16 * NB || (a.nd > 0 && a.nz > 0)) return hipErrorInvalidValue;
   const bool fast = plan_rblocks<RB, NB>(&a, 1);
   const size_t lds = project_lds<RB, NB>(a);
   dim3 grid((unsigned)(a.T_pad / (16 * RB * a.rblocks)), (unsigned)a.B);
-  const int nbd = (a.nd + 15) / 16;
-#define DPRC_PROJECT_CASE(NBD)                                                           \
-  if (nbd == NBD) {                                                                      \
-    if (fast) DPRC_LAUNCH((project_kernel<RB, NB, NBD, true>), grid, dim3(kBlock), lds, st, a);  \
-    else DPRC_LAUNCH((project_kernel<RB, NB, NBD, false>), grid, dim3(kBlock), lds, st, a);      \
-  }
-  DPRC_PROJECT_CASE(0)
-  if constexpr (NB >= 1) { DPRC_PROJECT_CASE(1) }
-  if constexpr (NB >= 2) { DPRC_PROJECT_CASE(2) }
-#undef DPRC_PROJECT_CASE
+#define DPRC_PROJECT_CASE(NBDV)                                                                   \
+  if (fast) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, true>), grid, dim3(kBlock), lds, st, a);   \
+  else DPRC_LAUNCH((project_kernel<RB, NB, NBDV, false>), grid, dim3(kBlock), lds, st, a);       \
   return hipGetLastError();
+  if (a.nd == 0) {
+    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_CASE(0) }
+  } else {
+    if constexpr (kProjDense<RB, NB>) { DPRC_PROJECT_CASE(NB) }
+  }
+#undef DPRC_PROJECT_CASE
+  return hipErrorInvalidValue;
 }
 
 template <int RB>
