@@ -672,12 +672,13 @@ dprc_status hpp_pass(int which, const View& v, int32_t s, int32_t r, uint32_t k0
 
 // Pass `which` of a group of layers: one projection launch and one token-reduction launch
 // for all of them (each layer has its own Y and partials), the split sums deferred to the
-// caller.  Passes wider than 64 columns take a launch pair per layer.
+// caller.  Projections over more than 64 columns take a launch per layer, and so do token
+// reductions over more than kTokBatchCols columns.
 dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int32_t s, int32_t r, uint32_t k0,
                            uint32_t k1, hipStream_t st, TokredArgs* def) {
   const PassSpec p0 = hpp_spec(which, vs[0], s, r, bufs[0]);
   const int ncols_pad = pad_cols(p0.nd + p0.nz);
-  if (ncols_pad > 64 || ng > kProjMaxJobs || !bufs[0].Y) {
+  if (ncols_pad > kTokBatchCols || ng > kProjMaxJobs || !bufs[0].Y) {
     for (int q = 0; q < ng; ++q) {
       const dprc_status stt = hpp_pass(which, vs[q], s, r, k0, k1, bufs[q], st, &def[q]);
       if (stt != DPRC_SUCCESS) return stt;
@@ -705,10 +706,15 @@ dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int3
     tb.job[tb.njobs++] = def[ot[q]];
   }
   const int rpw = rows_per_wg(rows, ncols_pad, p0.nd > 0);
-  if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project_batch(pb, rpw, st); }) != hipSuccess ||
-      traced(DPRC_KERNEL_TOKEN_REDUCE, st, [&] { return launch_tokred_batch(tb, st); }) != hipSuccess)
-    return DPRC_ERROR_HIP;
-  return DPRC_SUCCESS;
+  if (ncols_pad <= 64) {
+    if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project_batch(pb, rpw, st); }) != hipSuccess)
+      return DPRC_ERROR_HIP;
+  } else {
+    for (int q = 0; q < ng; ++q)
+      if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project(pb.job[q], rpw, st); }) != hipSuccess)
+        return DPRC_ERROR_HIP;
+  }
+  return hip_status(traced(DPRC_KERNEL_TOKEN_REDUCE, st, [&] { return launch_tokred_batch(tb, st); }));
 }
 
 // The fp32 Hutch++ path (the tiny workload): SIMT passes, the same QR and finalize.
@@ -872,9 +878,9 @@ bool hutch_batched(const dprc_layer* layers, int32_t n) {
   return true;
 }
 
-// The collected projections (widest first, up to kProjMaxJobs per launch) and token
-// reductions (one launch per column count) of a batch of activation groups; work over
-// more than 64 columns takes one launch per layer or group.
+// The collected projections (widest first, up to kProjMaxJobs per launch; one launch per
+// layer above 64 columns) and token reductions (one launch per column count; one per group
+// above kTokBatchCols columns) of a batch of activation groups.
 dprc_status hutch_launch_batched(ProjectArgs* pj, int npj, const TokredBatch& groups, hipStream_t st) {
   std::stable_sort(pj, pj + npj, [](const ProjectArgs& a, const ProjectArgs& b) { return a.m > b.m; });
   for (int c = 0; c < npj && pj[c].ncols_pad > 64; ++c)    // batched launches take up to 64 columns
@@ -894,7 +900,7 @@ dprc_status hutch_launch_batched(ProjectArgs* pj, int npj, const TokredBatch& gr
   std::stable_sort(tj, tj + groups.njobs, [](const TokredArgs& a, const TokredArgs& b) {
     return a.ncols_pad != b.ncols_pad ? a.ncols_pad < b.ncols_pad : a.n > b.n; });
   for (int q = 0; q < groups.njobs;) {
-    if (tj[q].ncols_pad > 64) {
+    if (tj[q].ncols_pad > kTokBatchCols) {
       if (traced(DPRC_KERNEL_TOKEN_REDUCE, st, [&] { return launch_tokred(tj[q], st); }) != hipSuccess)
         return DPRC_ERROR_HIP;
       ++q;

@@ -3,7 +3,7 @@
 // Hutch++), followed by either the squared-norm estimate or a store of M_i.
 //
 // A workgroup owns one sample, a 128-column tile of X (two adjacent tiles, eight waves,
-// in unsplit squared-norm launches) and a contiguous range of tokens.  X tiles (64 tokens x 128 columns, 256 bytes per token row) are
+// in unsplit squared-norm launches and wide ones) and a contiguous range of tokens.  X tiles (64 tokens x 128 columns, 256 bytes per token row) are
 // loaded with coalesced 16-byte reads, double-buffered through LDS and read
 // back token-contiguous with the gfx950 LDS transpose read, which is the
 // operand layout of the MFMA (the contraction runs over tokens, X is stored
@@ -99,24 +99,29 @@ struct Int {
   static constexpr int value = V;
 };
 
-// TT = 2 (unsplit squared-norm launches with an even number of 16-column blocks): a
-// workgroup of eight waves reduces two adjacent 128-column tiles, so each Y stage read
-// from L2 serves twice the columns.  Waves 4h .. 4h + 3 work on tile h exactly as the
-// four waves of a one-tile workgroup do.
+// TT = 2: a workgroup of eight waves reduces two adjacent 128-column tiles, so each Y stage
+// read from L2 serves twice the columns.  Waves 4h .. 4h + 3 work on tile h exactly as the
+// four waves of a one-tile workgroup do.  q, k and v of 16 layers of the stack (96 columns of
+// Y over 134 MB of activations each) took 228 us per group in launches of their own with
+// Y read from global memory at use (128 workgroups, 0.6 TB/s); two launches of eight groups
+// of pairs with Y staged in LDS take 36 us per group (3.8 TB/s).  What bounds them now is
+// the LDS: 28 KB of fragment reads per wave and 64-token stage.
 template <int NB, bool FAST, int TT = 1>
 __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by) {
-  static_assert(TT == 1 || (NB % 2 == 0 && NB <= 4), "two-tile workgroups stage Y through LDS, two halves");
-  // Y stages go through LDS with X (one 16-byte load per thread per 16 columns)
-  // when they are small; wider Y is read straight from global memory at use.
-  constexpr bool YLDS = NB <= 4;
+  // Y stages go through LDS with X (16 bytes per thread and 16 columns) up to 128 columns
+  // (143 KB of LDS with two tiles); wider Y is read straight from global memory at use.
+  constexpr bool YLDS = NB <= 8;
+  static_assert(TT == 1 || YLDS, "two-tile workgroups stage Y through LDS");
   constexpr int YLd = kStage + 8;                       // padded LDS row of one Y column (144 bytes)
   constexpr int XLd = TT * kTile + 16;                  // padded LDS row of the X stage
-  constexpr int YN = YLDS ? NB / TT : 1;                // Y loads per thread per stage
+  constexpr int YN = YLDS ? (NB + TT - 1) / TT : 1;     // Y loads per thread per stage
   __shared__ __attribute__((aligned(16))) uint16_t lds[2][kStage * XLd];
   __shared__ __attribute__((aligned(16))) uint16_t ylds[YLDS ? 2 : 1][YLDS ? 2 * 16 * NB * YLd : 8];
   __shared__ double dred[4 * TT];
-  constexpr int P = 4;                                  // stages in flight in registers, one more in LDS
-  static_assert(P == 4, "the stage loop below is written out for four ring slots");
+  // stages in flight in registers, one more in LDS; eight waves of more than 64 columns
+  // have room for two next to their accumulators (256 registers per lane; three at 96
+  // columns spill and measured the same)
+  constexpr int P = TT == 1 || NB <= 4 ? 4 : 2;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int g = lane >> 4, l16 = lane & 15, r4 = l16 >> 2, c4 = lane & 3;
   const int i = by;
@@ -134,7 +139,13 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
   const uint32_t lane_off = j0 + lc < a.n ? (uint32_t)lr0 * row_bytes + 2u * lc : kOobOffset;
   const uint16_t* ys = a.Yt + (int64_t)i * a.T_pad;
   // Y stage loads: column-half ch = tid / 8 + 32 TT r (h = ch / ncols16, c = ch % ncols16), tokens 8 (tid % 8) ..
+  // (an odd number of column blocks leaves half the threads of a two-tile workgroup without
+  // a last piece: they load the first column's and store nothing)
   const int ych = tid >> 3, ytk = (tid & 7) * 8;
+  auto y_ch = [&](int r) __attribute__((always_inline)) {
+    const int ch = ych + 32 * TT * r;
+    return NB % TT == 0 || ch < 32 * NB ? ch : 0;
+  };
 
   struct Stage {
     uint4 x[4];
@@ -163,7 +174,7 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
       const int ytok = tb + min(st, nst - 1) * kStage + ytk;
 #pragma unroll
       for (int r = 0; r < YN; ++r) {
-        const int ch = ych + 32 * TT * r, h = ch / (16 * NB), c = ch - h * 16 * NB;
+        const int ch = y_ch(r), h = ch / (16 * NB), c = ch - h * 16 * NB;
         dst.y[r] = *reinterpret_cast<const uint4*>(ys + ((int64_t)h * a.ncols_pad + c) * a.yt_ld + ytok);
       }
     }
@@ -175,7 +186,8 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     if constexpr (YLDS) {
 #pragma unroll
       for (int r = 0; r < YN; ++r)
-        *reinterpret_cast<uint4*>(&ylds[buf][(ych + 32 * TT * r) * YLd + ytk]) = src.y[r];
+        if (NB % TT == 0 || ych + 32 * TT * r < 32 * NB)
+          *reinterpret_cast<uint4*>(&ylds[buf][y_ch(r) * YLd + ytk]) = src.y[r];
     }
   };
 
@@ -190,28 +202,45 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
   auto mult = [&](int buf, int st) __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      uint4 bop[2][NB];
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          if constexpr (YLDS)
-            bop[h][nb] = *reinterpret_cast<const uint4*>(
-                &ylds[buf][(h * 16 * NB + 16 * nb + l16) * YLd + 32 * ks + 8 * g]);
-          else
-            bop[h][nb] = *reinterpret_cast<const uint4*>(
-                ys + ((int64_t)h * a.ncols_pad + 16 * nb + l16) * a.yt_ld + tb + st * kStage + 32 * ks + 8 * g);
-        }
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
+      auto bload = [&](int h, int nb) __attribute__((always_inline)) {
+        if constexpr (YLDS)
+          return *reinterpret_cast<const uint4*>(&ylds[buf][(h * 16 * NB + 16 * nb + l16) * YLd + 32 * ks + 8 * g]);
+        else
+          return *reinterpret_cast<const uint4*>(ys + ((int64_t)h * a.ncols_pad + 16 * nb + l16) * a.yt_ld + tb +
+                                                 st * kStage + 32 * ks + 8 * g);
+      };
+      auto aload = [&](int x) __attribute__((always_inline)) {
         const int mb = 2 * wv + x;
         // rows 32ks + 8g + r4 (+4) all have bit 3 equal to g & 1
         const uint16_t* p = &lds[buf][(32 * ks + 8 * g + r4) * XLd + ((16 * mb + 4 * c4) ^ ((g & 1) << 6))];
-        const uint4 av = make_u4(lds_read_tr16(p), lds_read_tr16(p + 4 * XLd));
+        return make_u4(lds_read_tr16(p), lds_read_tr16(p + 4 * XLd));
+      };
+      if constexpr (NB <= 4) {
+        uint4 bop[2][NB];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) acc[x][h][nb] = mfma16x16x32(av, bop[h][nb], acc[x][h][nb]);
+          for (int nb = 0; nb < NB; ++nb) bop[h][nb] = bload(h, nb);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const uint4 av = aload(x);
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[x][h][nb] = mfma16x16x32(av, bop[h][nb], acc[x][h][nb]);
+        }
+      } else {                                     // half of Y's fragments in registers at a time
+        const uint4 av[2] = {aload(0), aload(1)};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          uint4 bop[NB];
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) bop[nb] = bload(h, nb);
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[x][h][nb] = mfma16x16x32(av[x], bop[nb], acc[x][h][nb]);
+        }
       }
     }
   };
@@ -223,10 +252,11 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     swrite(ring[0], 0);
     __syncthreads();
     auto step = [&](int st, auto ph) __attribute__((always_inline)) {
-      gload(ring[ph.value], st + P);               // ring[ph] held stage st, already in LDS
-      mult(ph.value & 1, st);
+      constexpr int u = decltype(ph)::value;
+      gload(ring[u % P], st + P);                  // ring[u % P] held stage st, already in LDS
+      mult(u & 1, st);
       // unconditional: after the last stage it stores an unused (empty-range) stage
-      swrite(ring[(ph.value + 1) % P], (ph.value + 1) & 1);
+      swrite(ring[(u + 1) % P], (u + 1) & 1);
       __syncthreads();
     };
     // whole groups of P stages in the loop (no early exit reaches its back edge, so
@@ -235,12 +265,16 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     for (; st0 + P <= nst; st0 += P) {
       step(st0 + 0, Int<0>{});
       step(st0 + 1, Int<1>{});
-      step(st0 + 2, Int<2>{});
-      step(st0 + 3, Int<3>{});
+      if constexpr (P > 2) {
+        step(st0 + 2, Int<2>{});
+        step(st0 + 3, Int<3>{});
+      }
     }
     if (st0 + 0 < nst) step(st0 + 0, Int<0>{});
-    if (st0 + 1 < nst) step(st0 + 1, Int<1>{});
-    if (st0 + 2 < nst) step(st0 + 2, Int<2>{});
+    if constexpr (P > 2) {
+      if (st0 + 1 < nst) step(st0 + 1, Int<1>{});
+      if (st0 + 2 < nst) step(st0 + 2, Int<2>{});
+    }
   }
 
   // W = hi part + lo part; lane holds rows j0 + 16*mb + 4*g + (0..3) of column 16*nb + l16
@@ -252,8 +286,10 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
 #pragma unroll
       for (int q = 0; q < 4; ++q) w[x][nb][q] = acc[x][0][nb][q] + acc[x][1][nb][q];
 
-  const int64_t tslot = (int64_t)i * a.ntiles + tile;
-  if constexpr (TT > 1) {                              // unsplit squared norms only
+  // the tile and the position in it of this wave (a pair's second tile may not exist)
+  const int mytile = TT * tile + (wv >> 2), mw = wv & 3;
+  const int64_t tslot = (int64_t)i * a.ntiles + mytile;
+  if (a.S == 1 && a.mode == 0) {
     double sq[kMaxGroup] = {};
 #pragma unroll
     for (int x = 0; x < 2; ++x)
@@ -266,24 +302,13 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     seg_publish<TT>(a, (int64_t)i * a.ntiles + TT * tile, TT * tile, sq, dred);
     return;
   }
+  if (mytile >= a.ntiles) return;
   if (a.S == 1) {
-    if (a.mode == 0) {
-      double sq[kMaxGroup] = {};
 #pragma unroll
-      for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const int c = 16 * nb + l16;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) seg_add(a, c, (double)(w[x][nb][q] * w[x][nb][q]), sq);
-        }
-      seg_publish<1>(a, tslot, tile, sq, dred);
-    } else {
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) store4(a, i, 16 * nb + l16, j0 + 16 * (2 * wv + x) + 4 * g, w[x][nb]);
-    }
+      for (int nb = 0; nb < NB; ++nb)
+        store4(a, i, 16 * nb + l16, mytile * kTile + 16 * (2 * mw + x) + 4 * g, w[x][nb]);
     return;
   }
   // token splits: publish the partial tile; the finish kernel sums the splits in order
@@ -292,7 +317,7 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
   for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      float* dst = mypart + (int64_t)(16 * nb + l16) * kTile + 16 * (2 * wv + x) + 4 * g;
+      float* dst = mypart + (int64_t)(16 * nb + l16) * kTile + 16 * (2 * mw + x) + 4 * g;
       *reinterpret_cast<float4*>(dst) = float4{w[x][nb][0], w[x][nb][1], w[x][nb][2], w[x][nb][3]};
     }
 }
@@ -536,14 +561,21 @@ hipError_t launch_tokred_sample(const TokredArgs& a, hipStream_t st) {
 
 hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
   if (bt.njobs < 1 || bt.njobs > kTokMaxJobs) return hipErrorInvalidValue;
-  bool fast = true, pairs = bt.job[0].ncols_pad % 32 == 0;
+  const int nb = bt.job[0].ncols_pad / 16;
+  bool fast = true, pairs = nb % 2 == 0;
+  int64_t pair_blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {
     const TokredArgs& a = bt.job[j];
     if (a.ncols_pad != bt.job[0].ncols_pad) return hipErrorInvalidValue;   // one instantiation
     // buffer offsets within one 64-row stage stay below 2^31
     fast = fast && a.vec && a.n % 8 == 0 && (int64_t)kStage * a.ldx * 2 < ((int64_t)1 << 31);
-    pairs = pairs && a.S == 1 && a.mode == 0;       // unsplit squared norms: two tiles per workgroup
+    pairs = pairs && a.S == 1 && a.mode == 0;
+    pair_blocks += (int64_t)(a.ntiles + 1) / 2 * a.S * a.B;
   }
+  // Two tiles per workgroup: up to 64 columns in unsplit squared-norm launches; above 64
+  // columns, where one workgroup's LDS leaves room for no second one in a CU (92 KB of it
+  // at 96 columns), as soon as the pairs alone give every CU a workgroup.
+  if (nb > 4) pairs = pair_blocks >= 256;
   const int tt = pairs ? 2 : 1;
   bt.blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {
@@ -555,24 +587,33 @@ hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
 #define DPRC_TOKRED_BATCH_LAUNCH(NB, TT)                                                                  \
   if (fast) DPRC_LAUNCH((tokred_batch_kernel<NB, true, TT>), grid, dim3(kBlock * TT), 0, st, bt);        \
   else DPRC_LAUNCH((tokred_batch_kernel<NB, false, TT>), grid, dim3(kBlock * TT), 0, st, bt);
-  switch (bt.job[0].ncols_pad / 16) {
+#define DPRC_TOKRED_BATCH_CASE(NB)                         \
+  case NB:                                                  \
+    if (tt == 2) { DPRC_TOKRED_BATCH_LAUNCH(NB, 2) }       \
+    else { DPRC_TOKRED_BATCH_LAUNCH(NB, 1) }               \
+    break;
+  switch (nb) {
     case 1: DPRC_TOKRED_BATCH_LAUNCH(1, 1) break;
-    case 2:
-      if (tt == 2) { DPRC_TOKRED_BATCH_LAUNCH(2, 2) }
-      else { DPRC_TOKRED_BATCH_LAUNCH(2, 1) }
-      break;
+    DPRC_TOKRED_BATCH_CASE(2)
     case 3: DPRC_TOKRED_BATCH_LAUNCH(3, 1) break;
-    case 4:
-      if (tt == 2) { DPRC_TOKRED_BATCH_LAUNCH(4, 2) }
-      else { DPRC_TOKRED_BATCH_LAUNCH(4, 1) }
-      break;
+    DPRC_TOKRED_BATCH_CASE(4)
+    DPRC_TOKRED_BATCH_CASE(5)
+    DPRC_TOKRED_BATCH_CASE(6)
+    DPRC_TOKRED_BATCH_CASE(8)
     default: return hipErrorInvalidValue;
   }
+#undef DPRC_TOKRED_BATCH_CASE
 #undef DPRC_TOKRED_BATCH_LAUNCH
   return hipGetLastError();
 }
 
 hipError_t launch_tokred(const TokredArgs& a, hipStream_t st) {
+  if (a.ncols_pad > 64 && a.ncols_pad <= kTokBatchCols) {   // one job of the wide batched kernel
+    TokredBatch bt{};
+    bt.njobs = 1;
+    bt.job[0] = a;
+    return launch_tokred_batch(bt, st);
+  }
   dim3 grid((unsigned)(a.ntiles * a.S), (unsigned)a.B);
   // buffer offsets within one 64-row stage stay below 2^31
   const bool fast = a.vec && a.n % 8 == 0 && (int64_t)kStage * a.ldx * 2 < ((int64_t)1 << 31);
@@ -586,9 +627,6 @@ hipError_t launch_tokred(const TokredArgs& a, hipStream_t st) {
     DPRC_TOKRED_CASE(2)
     DPRC_TOKRED_CASE(3)
     DPRC_TOKRED_CASE(4)
-    DPRC_TOKRED_CASE(5)
-    DPRC_TOKRED_CASE(6)
-    DPRC_TOKRED_CASE(8)
     DPRC_TOKRED_CASE(12)
     DPRC_TOKRED_CASE(16)
     default: return hipErrorInvalidValue;

@@ -111,6 +111,7 @@ struct TokredArgs {
 
 // Token-split sums of several layers' passes in one launch.
 constexpr int kTokMaxJobs = 32;       // 7.3 KB of kernel arguments
+constexpr int kTokBatchCols = 128;    // most columns of a batched token reduction
 struct TokredBatch {
   int32_t njobs, blocks;
   int32_t blk0[kTokMaxJobs];     // first block of each job (ntiles * B blocks each)
@@ -327,7 +328,7 @@ hipError_t launch_gauss_probe(uint32_t key0, uint32_t key1, uint32_t layer, int6
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_project(const ProjectArgs& a, int rows_per_wg, hipStream_t st);
 hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st);   // <= 64 columns
-hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st);                      // <= 64 columns
+hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st);                      // <= kTokBatchCols columns
 hipError_t launch_tokred(const TokredArgs& a, hipStream_t st);
 hipError_t launch_tokred_splits(const TokredArgs& a, hipStream_t st);   // S > 1
 hipError_t launch_tokred_splits_batch(const TokredBatch& bt, hipStream_t st);

@@ -184,7 +184,7 @@ def test_hutch_many_groups_batched(D, k, probe):
     # 15 bf16 layers in 11 activation groups (one batch of up to 32): shared groups of
     # three and two layers between single layers, so one batch holds more than eight
     # projections and token reductions of several column counts (k = 40: groups over 64
-    # columns; k = 100: projections over 64 columns, one launch each)
+    # columns, still batched; k = 100: projections over 64 columns, one launch each)
     B, T = 2, 150
     groups = [(96, (130, 72, 72)), (64, (300,)), (136, (520, 260)), (48, (90,)), (80, (200,)),
               (72, (64,)), (40, (150,)), (88, (110, 96)), (56, (70,)), (64, (260,)), (120, (100,))]
@@ -207,6 +207,39 @@ def test_hutch_many_groups_batched(D, k, probe):
     assert np.all(_rel(got, solo.cpu().numpy()) < 1e-6)
     if k % 16 == 0:
         assert torch.equal(n2l, solo)
+
+
+@pytest.mark.parametrize("T,ngroups,k,G", [
+    (200, 8, 32, 3),      # 1056 (sample, tile) pairs: unsplit, 96 columns
+    (520, 2, 25, 3),      # two token splits, 75 columns in 80 (an odd number of column blocks)
+    (520, 2, 32, 4),      # 128 columns
+])
+def test_hutch_wide_groups_two_tiles(D, T, ngroups, k, G):
+    # activation groups of more than 64 columns with enough tile pairs for two-tile workgroups;
+    # 4104-wide activations have an odd number of tiles, the last one 8 columns wide
+    B, d = 4, 4104
+    pairs = []
+    for g in range(ngroups):
+        A, Es = _shared_a(B, T, d, (40, 72, 24, 56)[:G], layer0=400 + 10 * g)
+        pairs += [(A, E, 10 * g + j) for j, E in enumerate(Es)]
+    n2l = torch.zeros(len(pairs), B, device="cuda")
+    D.dprc_norm_hutch(pairs, k, 4, n2_layers=n2l)
+    solo = torch.stack([D.dprc_norm_hutch([(A.clone(), E, j)], k, 4) for (A, E, j) in pairs])
+    assert np.all(_rel(n2l.cpu().numpy(), solo.cpu().numpy()) < 1e-5)
+    for q in (0, G - 1, len(pairs) - 1):
+        A, E, j = pairs[q]
+        assert np.all(_rel(n2l[q].cpu().numpy(), est.hutch_layer(_np(A), _np(E), k, 4, j)) < NORM_RTOL), q
+
+
+def test_hutchpp_wide_store_two_tiles(D):
+    # s + r = 80 columns stored (not squared) by two-tile workgroups over four token splits,
+    # 2056-wide activations (17 tiles)
+    B, T, s, r = 4, 1030, 16, 64
+    pairs = [_draw(B, T, 2056, p, law="student_t", layer=450 + j) + (j,) for j, p in enumerate((100, 72))]
+    n2l = torch.zeros(len(pairs), B, device="cuda")
+    D.dprc_norm_hutchpp(pairs, s, r, 9, n2_layers=n2l)
+    for q, (A, E, j) in enumerate(pairs):
+        assert np.all(_rel(n2l[q].cpu().numpy(), est.hutchpp_layer(_np(A), _np(E), s, r, 9, j)) < NORM_RTOL), q
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
@@ -438,8 +471,8 @@ def test_hutchpp_many_layers_grouped(D):
 
 
 def test_hutchpp_grouped_wide_passes(D):
-    # three bf16 layers with s + r = 80 > 64 columns: the grouped passes take one launch pair
-    # per layer (wider than the batched kernels), all sharing the group's pass scratch
+    # three bf16 layers with s + r = 80 > 64 columns: the grouped passes take one projection
+    # launch per layer (wider than the batched kernel) and one token reduction
     B, T, s, r = 2, 300, 16, 64
     shapes = [(120, 260), (72, 500), (200, 136)]
     pairs = []
