@@ -353,40 +353,48 @@ size_t hutch_group_ws(const View* v, int G, int32_t k, int probe) {
     pass_ws(ar, v[0].B, v[0].T, v[0].n, pad_cols(G * k), nullptr, nullptr, nullptr, G);
     return ar.off;
   }
-  if (probe != DPRC_PROBE_GAUSSIAN) ar.take<uint32_t>((size_t)k * ceil_div(v[0].m, 32));
   ar.take<float>((size_t)v[0].B * v[0].T * k);
-  ar.take<float>((size_t)v[0].B * k * v[0].n);
+  ar.take<double>((size_t)v[0].B * tokred_f32_tiles(v[0].n, k));
   return ar.off;
 }
 
+// Tile sums of an fp32 layer's token reduction (rows x cols results), squared and added per
+// sample in tile order.
+dprc_status f32_squares(const float* Xo, int64_t ldo, const View& v, const float* Y, int32_t k, double* tilesq,
+                        float* n2, float* n2_layer, int accumulate, float clipC, float* clip_c, hipStream_t st) {
+  const TokredF32Args ta{Xo, ldo, v.T * ldo, (int32_t)v.B, (int32_t)v.T, (int32_t)v.n, Y, k, nullptr, 0, 0, tilesq};
+  if (traced(DPRC_KERNEL_TOKEN_REDUCE_F32, st, [&] { return launch_tokred_f32(ta, st); }) != hipSuccess)
+    return DPRC_ERROR_HIP;
+  TokredArgs sa{};
+  sa.B = (int32_t)v.B; sa.ntiles = tokred_f32_tiles(v.n, k); sa.nseg = 1; sa.tilesq = tilesq;
+  sa.scale = 1.0f / (float)k; sa.n2 = n2; sa.n2_layer = n2_layer; sa.accumulate = accumulate;
+  sa.clip_C = clipC; sa.clip_c = clip_c;
+  return hip_status(traced(DPRC_KERNEL_SAMPLE_SQ, st, [&] { return launch_tokred_sample(sa, st); }));
+}
+
 dprc_status hutch_f32(const View& v, int32_t k, int probe, uint32_t k0, uint32_t k1, float* n2,
-                      float* n2_layer, int accumulate, void* ws, hipStream_t st) {
+                      float* n2_layer, int accumulate, float clipC, float* clip_c, void* ws, hipStream_t st) {
   const bool gauss = probe == DPRC_PROBE_GAUSSIAN;
   Arena ar(ws);
   GaussBufs g{};
-  hipError_t e = hipSuccess;
   if (gauss) {
     g = take_gauss(ar, v, k);
-    if ((e = traced(DPRC_KERNEL_PROBE_GAUSS, st, [&] {
-           return launch_gauss_probe(k0, k1, v.layer_id, v.m, k, g.ld, nullptr, nullptr, g.f32, st); })) != hipSuccess)
+    if (traced(DPRC_KERNEL_PROBE_GAUSS, st, [&] {
+          return launch_gauss_probe(k0, k1, v.layer_id, v.m, k, g.ld, nullptr, nullptr, g.f32, st); }) != hipSuccess)
       return DPRC_ERROR_HIP;
   }
-  uint32_t* zb = gauss ? nullptr : ar.take<uint32_t>((size_t)k * ceil_div(v.m, 32));
   float* Y = ar.take<float>((size_t)v.B * v.T * k);
-  float* M = ar.take<float>((size_t)v.B * k * v.n);
-  if (!gauss && (e = traced(DPRC_KERNEL_PROBE_BITS, st, [&] { return launch_probe_bits(probe, k0, k1, v.layer_id, 0, v.m, k, zb, st); })) != hipSuccess)
+  double* tilesq = ar.take<double>((size_t)v.B * tokred_f32_tiles(v.n, k));
+  ProjectF32Args pa{};
+  pa.X = (const float*)v.X; pa.ldx = v.ldx; pa.x_ss = v.T * v.ldx;
+  pa.B = (int32_t)v.B; pa.T = (int32_t)v.T; pa.m = (int32_t)v.m;
+  pa.nd = gauss ? k : 0; pa.nz = gauss ? 0 : k; pa.ncols = k;
+  pa.Rd = g.f32; pa.ld_r = g.ld; pa.r_ss = 0;
+  pa.probe_kind = probe; pa.key0 = k0; pa.key1 = k1; pa.layer_id = v.layer_id; pa.stream_id = 0;
+  pa.Y = Y;
+  if (traced(DPRC_KERNEL_PROJECT_F32, st, [&] { return launch_project_f32(pa, st); }) != hipSuccess)
     return DPRC_ERROR_HIP;
-  ProjectF32Args pa = gauss
-      ? ProjectF32Args{(const float*)v.X, v.ldx, v.T * v.ldx, (int32_t)v.B, (int32_t)v.T, (int32_t)v.m,
-                       k, 0, k, g.f32, g.ld, 0, nullptr, Y}
-      : ProjectF32Args{(const float*)v.X, v.ldx, v.T * v.ldx, (int32_t)v.B, (int32_t)v.T, (int32_t)v.m,
-                       0, k, k, nullptr, 0, 0, zb, Y};
-  if ((e = traced(DPRC_KERNEL_PROJECT_F32, st, [&] { return launch_project_f32(pa, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-  TokredF32Args ta{(const float*)v.Xo, v.ldo, v.T * v.ldo, (int32_t)v.B, (int32_t)v.T, (int32_t)v.n, Y, k,
-                   M, v.n, (int64_t)k * v.n};
-  if ((e = traced(DPRC_KERNEL_TOKEN_REDUCE_F32, st, [&] { return launch_tokred_f32(ta, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-  return hip_status(traced(DPRC_KERNEL_SAMPLE_SQ, st, [&] { return launch_sample_sq(M, v.n, (int64_t)k * v.n, (int32_t)v.B, k, (int32_t)v.n,
-                                     1.0f / (float)k, n2, n2_layer, accumulate, st); }));
+  return f32_squares((const float*)v.Xo, v.ldo, v, Y, k, tilesq, n2, n2_layer, accumulate, clipC, clip_c, st);
 }
 
 // G layers (G = 1, or a shared-activation group of bf16 OUT layers): one projection
@@ -398,11 +406,8 @@ dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0,
                         float* n2_layers, int accumulate, void* ws, hipStream_t st, float clipC = 0.f,
                         float* clip_c = nullptr, TokredArgs* defer = nullptr, const TokBufs* own = nullptr,
                         ProjectArgs* pjobs = nullptr, int* npj = nullptr) {
-  if (v[0].dtype != DPRC_BF16) {
-    dprc_status s = hutch_f32(v[0], k, probe, k0, k1, n2, n2_layers, accumulate, ws, st);
-    if (s != DPRC_SUCCESS || !clip_c) return s;
-    return hip_status(traced(DPRC_KERNEL_CLIP_SCALE, st, [&] { return launch_clip_scale(n2, v[0].B, clipC, clip_c, st); }));
-  }
+  if (v[0].dtype != DPRC_BF16)
+    return hutch_f32(v[0], k, probe, k0, k1, n2, n2_layers, accumulate, clipC, clip_c, ws, st);
   const bool gauss = probe == DPRC_PROBE_GAUSSIAN;
   const int64_t B = v[0].B, T = v[0].T;
   Arena ar(ws);
@@ -481,8 +486,8 @@ struct PPBufs {
   float* Q;                                // [B][s][m]
   uint16_t *Qhi, *Qlo; int64_t ld_q;       // bf16 path
   float* UW;                               // [B][s+r][n]
-  uint32_t* zb;                            // fp32 path: probe bits (s or r columns)
   float* Y32;                              // fp32 path
+  double* tilesq;                          // fp32 path without a sketch
   void* pass_ws;                           // bf16 path: scratch of one pass
   float* part;                             // grouped layers: the layer's own token-split partials
   uint16_t* Y;                             // grouped layers: the layer's own Y (batched passes)
@@ -538,9 +543,8 @@ size_t hutchpp_layout(const View& v, int32_t s, int32_t r, void* ws, PPBufs* out
       ar.off += hpp_pass_bytes(v, s, r);
     }
   } else {
-    b.zb = ar.take<uint32_t>((size_t)std::max(s, r) * ceil_div(std::max(v.m, v.n), 32));
     b.Y32 = ar.take<float>((size_t)B * v.T * (s + r));
-    if (s == 0) b.UW = ar.take<float>((size_t)B * r * v.n);
+    if (s == 0) b.tilesq = ar.take<double>((size_t)B * tokred_f32_tiles(v.n, r));
   }
   if (out) *out = b;
   return ar.off;
@@ -717,40 +721,35 @@ dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int3
   return hip_status(traced(DPRC_KERNEL_TOKEN_REDUCE, st, [&] { return launch_tokred_batch(tb, st); }));
 }
 
-// The fp32 Hutch++ path (the tiny workload): SIMT passes, the same QR and finalize.
+// The fp32 Hutch++ path: fp32 matrix-core passes, the same QR and finalize.
 dprc_status hutchpp_f32(const View& v, int32_t s, int32_t r, uint32_t k0, uint32_t k1, PPBufs& b, float* n2,
                         float* n2_layer, int accumulate, hipStream_t st) {
   const int64_t B = v.B, T = v.T;
-  hipError_t e;
-  {
-    const float* X = (const float*)v.X;
-    const float* Xo = (const float*)v.Xo;
-    if (s > 0) {
-      if ((e = traced(DPRC_KERNEL_PROBE_BITS, st, [&] { return launch_probe_bits(0, k0, k1, v.layer_id, 1, v.m, s, b.zb, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-      ProjectF32Args a1{X, v.ldx, T * v.ldx, (int32_t)B, (int32_t)T, (int32_t)v.m, 0, s, s, nullptr, 0, 0, b.zb, b.Y32};
-      if ((e = traced(DPRC_KERNEL_PROJECT_F32, st, [&] { return launch_project_f32(a1, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-      TokredF32Args t1{Xo, v.ldo, T * v.ldo, (int32_t)B, (int32_t)T, (int32_t)v.n, b.Y32, s, b.WS32, v.n, (int64_t)s * v.n};
-      if ((e = traced(DPRC_KERNEL_TOKEN_REDUCE_F32, st, [&] { return launch_tokred_f32(t1, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-      ProjectF32Args a2{Xo, v.ldo, T * v.ldo, (int32_t)B, (int32_t)T, (int32_t)v.n, s, 0, s, b.WS32, v.n,
-                        (int64_t)s * v.n, nullptr, b.Y32};
-      if ((e = traced(DPRC_KERNEL_PROJECT_F32, st, [&] { return launch_project_f32(a2, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-      TokredF32Args t2{X, v.ldx, T * v.ldx, (int32_t)B, (int32_t)T, (int32_t)v.m, b.Y32, s, b.OS, v.m, (int64_t)s * v.m};
-      if ((e = traced(DPRC_KERNEL_TOKEN_REDUCE_F32, st, [&] { return launch_tokred_f32(t2, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-      PPBufs* bp = &b;
-      const dprc_status sq = run_qr(&bp, &v, 1, k0, k1, false, st);
-      if (sq != DPRC_SUCCESS) return sq;
-    }
-    if ((e = traced(DPRC_KERNEL_PROBE_BITS, st, [&] { return launch_probe_bits(0, k0, k1, v.layer_id, 0, v.m, r, b.zb, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-    ProjectF32Args a3{X, v.ldx, T * v.ldx, (int32_t)B, (int32_t)T, (int32_t)v.m, s, r, s + r, b.Q, v.m,
-                      (int64_t)s * v.m, b.zb, b.Y32};
-    if ((e = traced(DPRC_KERNEL_PROJECT_F32, st, [&] { return launch_project_f32(a3, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-    TokredF32Args t3{Xo, v.ldo, T * v.ldo, (int32_t)B, (int32_t)T, (int32_t)v.n, b.Y32, s + r, b.UW, v.n,
-                     (int64_t)(s + r) * v.n};
-    if ((e = traced(DPRC_KERNEL_TOKEN_REDUCE_F32, st, [&] { return launch_tokred_f32(t3, st); })) != hipSuccess) return DPRC_ERROR_HIP;
-    if (s == 0)
-      return hip_status(traced(DPRC_KERNEL_SAMPLE_SQ, st, [&] { return launch_sample_sq(b.UW, v.n, (int64_t)r * v.n, (int32_t)B, r, (int32_t)v.n,
-                                         1.0f / (float)r, n2, n2_layer, accumulate, st); }));
+  const float* X = (const float*)v.X;
+  const float* Xo = (const float*)v.Xo;
+  auto project = [&](const float* x, int64_t ld, int64_t m, int32_t nd, const float* Rd, int32_t nz, uint32_t stream) {
+    ProjectF32Args a{};
+    a.X = x; a.ldx = ld; a.x_ss = T * ld; a.B = (int32_t)B; a.T = (int32_t)T; a.m = (int32_t)m;
+    a.nd = nd; a.nz = nz; a.ncols = nd + nz; a.Rd = Rd; a.ld_r = m; a.r_ss = (int64_t)nd * m;
+    a.probe_kind = DPRC_PROBE_RADEMACHER; a.key0 = k0; a.key1 = k1; a.layer_id = v.layer_id; a.stream_id = stream;
+    a.Y = b.Y32;
+    return traced(DPRC_KERNEL_PROJECT_F32, st, [&] { return launch_project_f32(a, st); }) == hipSuccess;
+  };
+  auto reduce = [&](const float* x, int64_t ld, int64_t n, int32_t ncols, float* M) {
+    const TokredF32Args a{x, ld, T * ld, (int32_t)B, (int32_t)T, (int32_t)n, b.Y32, ncols, M, n, (int64_t)ncols * n, nullptr};
+    return traced(DPRC_KERNEL_TOKEN_REDUCE_F32, st, [&] { return launch_tokred_f32(a, st); }) == hipSuccess;
+  };
+  if (s == 0) {                                      // Hutchinson with the r residual probes
+    if (!project(X, v.ldx, v.m, 0, nullptr, r, 0)) return DPRC_ERROR_HIP;
+    return f32_squares(Xo, v.ldo, v, b.Y32, r, b.tilesq, n2, n2_layer, accumulate, 0.f, nullptr, st);
   }
+  if (!project(X, v.ldx, v.m, 0, nullptr, s, 1) || !reduce(Xo, v.ldo, v.n, s, b.WS32) ||
+      !project(Xo, v.ldo, v.n, s, b.WS32, 0, 0) || !reduce(X, v.ldx, v.m, s, b.OS))
+    return DPRC_ERROR_HIP;
+  PPBufs* bp = &b;
+  const dprc_status sq = run_qr(&bp, &v, 1, k0, k1, false, st);
+  if (sq != DPRC_SUCCESS) return sq;
+  if (!project(X, v.ldx, v.m, s, b.Q, r, 0) || !reduce(Xo, v.ldo, v.n, s + r, b.UW)) return DPRC_ERROR_HIP;
   return hpp_final(v, s, r, b, n2, n2_layer, accumulate, st);
 }
 
@@ -1273,10 +1272,11 @@ dprc_status dprc_clip_accumulate(const dprc_layer* L, const float* c, float* gra
   const size_t need = dprc_clip_accumulate_workspace(L);
   if (ws_bytes < need) return DPRC_ERROR_WORKSPACE_TOO_SMALL;
   if (need && (!ws || !aligned(ws, kAlign))) return DPRC_ERROR_INVALID_VALUE;
-  if (L->dtype == DPRC_F32)
-    return hip_status(traced(DPRC_KERNEL_ACCUMULATE_F32, stream, [&] { return launch_gemm_f32((const float*)L->A, L->lda, L->T * L->lda, (const float*)L->E, L->lde,
-                                      L->T * L->lde, (int32_t)L->B, (int32_t)L->T, (int32_t)L->d, (int32_t)L->p, c,
-                                      grad, ldg, accumulate, stream); }));
+  if (L->dtype == DPRC_F32) {
+    const GemmF32Args f{(const float*)L->A, L->lda, L->T * L->lda, (const float*)L->E, L->lde, L->T * L->lde,
+                        (int32_t)L->B, (int32_t)L->T, (int32_t)L->d, (int32_t)L->p, c, grad, ldg, accumulate};
+    return hip_status(traced(DPRC_KERNEL_ACCUMULATE_F32, stream, [&] { return launch_gemm_f32(f, stream); }));
+  }
   const GemmPlan g = gemm_plan(*L);
   GemmArgs a;
   a.A = (const uint16_t*)L->A; a.lda = L->lda; a.a_ss = L->T * L->lda;

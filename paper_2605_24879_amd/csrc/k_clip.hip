@@ -39,36 +39,6 @@ hipError_t launch_splitk_reduce(const float* part, int32_t S, int32_t d, int32_t
   return hipGetLastError();
 }
 
-// ---- fp32 inputs (SIMT): one thread per gradient entry --------------------------------------
-__global__ void gemm_f32_kernel(const float* A, int64_t lda, int64_t a_ss, const float* E, int64_t lde,
-                                int64_t e_ss, int32_t B, int32_t T, int32_t d, int32_t p,
-                                const float* c, float* out, int64_t ldo, int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)d * p) return;
-  const int j = (int)(idx / p), u = (int)(idx - (int64_t)j * p);
-  float total = 0.f;
-  for (int i = 0; i < B; ++i) {
-    const float ci = c[i];
-    if (ci == 0.f) continue;
-    float s = 0.f;
-    for (int t = 0; t < T; ++t)
-      s = fmaf(A[(int64_t)i * a_ss + (int64_t)t * lda + j], E[(int64_t)i * e_ss + (int64_t)t * lde + u], s);
-    total = fmaf(ci, s, total);
-  }
-  float* o = out + (int64_t)j * ldo + u;
-  *o = accumulate ? *o + total : total;
-}
-
-hipError_t launch_gemm_f32(const float* A, int64_t lda, int64_t a_ss, const float* E, int64_t lde,
-                           int64_t e_ss, int32_t B, int32_t T, int32_t d, int32_t p,
-                           const float* c, float* out, int64_t ldo, int accumulate,
-                           hipStream_t st) {
-  const int64_t total = (int64_t)d * p;
-  DPRC_LAUNCH(gemm_f32_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, st, A, lda,
-                     a_ss, E, lde, e_ss, B, T, d, p, c, out, ldo, accumulate);
-  return hipGetLastError();
-}
-
 // ---- Gaussian noise ----------------------------------------------------------------------------
 // Element e: Philox block e/4 of stream 2 keyed by (seed, tensor), through box_muller.
 __global__ void noise_kernel(float* g, int64_t numel, float scale, uint32_t key0, uint32_t key1,

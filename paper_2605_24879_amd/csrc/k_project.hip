@@ -744,35 +744,4 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ---- fp32 inputs (SIMT) -------------------------------------------------------------
-// One thread per (token row, column); plain fp32 sums.  Used for fp32 layers.
-__global__ void project_f32_kernel(ProjectF32Args a) {
-  const int64_t total = (int64_t)a.B * a.T * a.ncols;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int c = (int)(idx % a.ncols);
-  const int64_t row = idx / a.ncols;
-  const int i = (int)(row / a.T), t = (int)(row - (int64_t)i * a.T);
-  const float* x = a.X + (int64_t)i * a.x_ss + (int64_t)t * a.ldx;
-  float s = 0.f;
-  if (c < a.nd) {
-    const float* r = a.Rd + (int64_t)i * a.r_ss + (int64_t)c * a.ld_r;
-    for (int u = 0; u < a.m; ++u) s = fmaf(x[u], r[u], s);
-  } else {
-    const int64_t nw = (a.m + 31) / 32;
-    const uint32_t* zb = a.zbits + (int64_t)(c - a.nd) * nw;
-    for (int u = 0; u < a.m; ++u) {
-      const uint32_t bit = (zb[u >> 5] >> (u & 31)) & 1u;
-      s += bit ? -x[u] : x[u];
-    }
-  }
-  a.Y[row * a.ncols + c] = s;
-}
-
-hipError_t launch_project_f32(const ProjectF32Args& a, hipStream_t st) {
-  const int64_t total = (int64_t)a.B * a.T * a.ncols;
-  DPRC_LAUNCH(project_f32_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
 }  // namespace dprc

@@ -635,52 +635,4 @@ hipError_t launch_tokred(const TokredArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ---- fp32 inputs (SIMT) ---------------------------------------------------------------
-__global__ void tokred_f32_kernel(TokredF32Args a) {
-  const int64_t total = (int64_t)a.B * a.n * a.ncols;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int j = (int)(idx % a.n);
-  const int64_t r = idx / a.n;
-  const int c = (int)(r % a.ncols), i = (int)(r / a.ncols);
-  const float* x = a.X + (int64_t)i * a.x_ss + j;
-  const float* y = a.Y + (int64_t)i * a.T * a.ncols + c;
-  float s = 0.f;
-  for (int t = 0; t < a.T; ++t) s = fmaf(x[(int64_t)t * a.ldx], y[(int64_t)t * a.ncols], s);
-  a.M[(int64_t)i * a.m_ss + (int64_t)c * a.m_ld + j] = s;
-}
-
-hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st) {
-  const int64_t total = (int64_t)a.B * a.n * a.ncols;
-  DPRC_LAUNCH(tokred_f32_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(kBlock) void sample_sq_kernel(const float* M, int64_t m_ld, int64_t m_ss,
-                                                         int32_t ncols, int32_t n, float scale,
-                                                         float* n2, float* n2_layer, int accumulate) {
-  __shared__ double dred[4];
-  const int i = blockIdx.x;
-  double s = 0.0;
-  for (int64_t e = threadIdx.x; e < (int64_t)ncols * n; e += kBlock) {
-    const int c = (int)(e / n), j = (int)(e - (int64_t)c * n);
-    const double v = M[(int64_t)i * m_ss + (int64_t)c * m_ld + j];
-    s += v * v;
-  }
-  s = block_sum_d(s, dred);
-  if (threadIdx.x == 0) {
-    const float est = (float)(s * (double)scale);
-    n2[i] = (accumulate ? n2[i] : 0.f) + est;
-    if (n2_layer) n2_layer[i] = est;
-  }
-}
-
-hipError_t launch_sample_sq(const float* M, int64_t m_ld, int64_t m_ss, int32_t B, int32_t ncols,
-                            int32_t n, float scale, float* n2, float* n2_layer, int accumulate,
-                            hipStream_t st) {
-  DPRC_LAUNCH(sample_sq_kernel, dim3(B), dim3(kBlock), 0, st, M, m_ld, m_ss, ncols, n, scale,
-                     n2, n2_layer, accumulate);
-  return hipGetLastError();
-}
-
 }  // namespace dprc

@@ -164,16 +164,19 @@ struct GemmPlan {
 };
 GemmPlan gemm_plan_v2(int64_t B, int64_t T, int64_t d, int64_t p);
 
-// fp32 (SIMT) variants, used for fp32 inputs.
+// fp32 layers (k_f32.hip).  Projection: columns 0 .. nd - 1 dense, then nz generated +-1
+// columns (column c - nd of the probe stream).
 struct ProjectF32Args {
   const float* X;
   int64_t ldx, x_ss;
   int32_t B, T, m;
-  int32_t nd, nz, ncols;
+  int32_t nd, nz, ncols;  // nd + nz = ncols
   const float* Rd;        // dense columns [i][c][ld_r]
   int64_t ld_r, r_ss;
-  const uint32_t* zbits;  // generated columns, packed [c][ceil(m/32)]
+  int32_t probe_kind;
+  uint32_t key0, key1, layer_id, stream_id;
   float* Y;               // [B][T][ncols]
+  int32_t words_per_chunk;   // set by the launcher
 };
 
 struct TokredF32Args {
@@ -182,8 +185,22 @@ struct TokredF32Args {
   int32_t B, T, n;
   const float* Y;         // [B][T][ncols]
   int32_t ncols;
-  float* M;               // M[i*m_ss + c*m_ld + j]
+  float* M;               // M[i*m_ss + c*m_ld + j], or null: the tiles' squared sums
   int64_t m_ld, m_ss;
+  double* tilesq;         // [B][tokred_f32_tiles(n, ncols)]
+};
+int32_t tokred_f32_tiles(int64_t n, int32_t ncols);
+
+struct GemmF32Args {
+  const float* A;
+  int64_t lda, a_ss;
+  const float* E;
+  int64_t lde, e_ss;
+  int32_t B, T, d, p;
+  const float* c;
+  float* out;
+  int64_t ldo;
+  int32_t accumulate;
 };
 
 // Tall-skinny QR of O S (m x s per sample, s <= 32) and C = Q^T P (Hutch++), as a
@@ -335,12 +352,8 @@ hipError_t launch_tokred_splits_batch(const TokredBatch& bt, hipStream_t st);
 // mode 0: the estimates of the jobs' layers added to n2 in order, then the clip factor (clip_c may be null)
 hipError_t launch_sample_sums(const SampleSumArgs& a, hipStream_t st);
 hipError_t launch_tokred_sample(const TokredArgs& a, hipStream_t st);   // mode 0
-hipError_t launch_project_f32(const ProjectF32Args& a, hipStream_t st);
+hipError_t launch_project_f32(ProjectF32Args a, hipStream_t st);
 hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st);
-// n2 (=|+=) scale * sum_{c<ncols, j<n} M[i][c][j]^2 (+ optional per-layer copy)
-hipError_t launch_sample_sq(const float* M, int64_t m_ld, int64_t m_ss, int32_t B, int32_t ncols,
-                            int32_t n, float scale, float* n2, float* n2_layer, int accumulate,
-                            hipStream_t st);
 hipError_t launch_qr_factor(const QrBatch& bt, hipStream_t st);   // a level-0 job reads O S
 hipError_t launch_qr_expand(const QrBatch& bt, hipStream_t st);   // a level-0 job writes Q and C
 hipError_t launch_hpp_csum(const FinalArgs& a, hipStream_t st);
@@ -353,10 +366,7 @@ hipError_t launch_hpp_sum_batch(const FinalBatch& bt, hipStream_t st);
 hipError_t launch_clip_scale(const float* n2, int64_t B, float C, float* c, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st);
 hipError_t launch_gemm_batch(GemmBatch bt, hipStream_t st);
-hipError_t launch_gemm_f32(const float* A, int64_t lda, int64_t a_ss, const float* E, int64_t lde,
-                           int64_t e_ss, int32_t B, int32_t T, int32_t d, int32_t p,
-                           const float* c, float* out, int64_t ldo, int accumulate,
-                           hipStream_t st);
+hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t st);
 hipError_t launch_splitk_reduce(const float* part, int32_t S, int32_t d, int32_t p, float* out,
                                 int64_t ldo, int accumulate, hipStream_t st);
 hipError_t launch_noise(float* g, int64_t numel, float scale, uint32_t key0, uint32_t key1,

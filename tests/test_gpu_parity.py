@@ -129,6 +129,57 @@ def test_hutch_gaussian_multilayer_accumulate(D):
     assert np.all(_rel(n2.cpu().numpy(), np.array([0.5, 1.0]) + r1 + r2) < NORM_RTOL)
 
 
+# fp32 sums of n terms in any order: relative error at most n 2^-24 of the sum of magnitudes;
+# with random signs that is about sqrt(n) 2^-24 of the result, and 3e-6 covers n = 1000 tenfold
+F32_RTOL = 3e-6
+
+
+@pytest.mark.parametrize("B,T,d,p,k,probe,pad", [
+    (1, 1, 1, 1, 1, "rademacher", 0),           # one entry
+    (2, 17, 3, 2, 5, "hadamard", 0),            # rows of less than one 16-byte piece
+    (2, 33, 65, 513, 17, "rademacher", 3),      # one past the tiles of 64, 512 and 16; odd strides
+    (1, 70, 130, 20000, 64, "rademacher", 0),   # two chunks of probe words, 64 columns
+    (3, 40, 70, 131, 130, "rademacher", 1),     # more than 64 columns: three column groups
+    (2, 36, 66, 258, 9, "gaussian", 0),
+])
+def test_f32_norm_edges(D, B, T, d, p, k, probe, pad):
+    A, E = _draw(B, T, d, p, dtype="f32", layer=500, row_pad_a=pad, row_pad_e=pad)
+    pid = {"rademacher": 0, "hadamard": 1, "gaussian": 2}[probe]
+    n2, c = D.dprc_norm_hutch_clip([(A, E, 3)], k, 6, 0.5, probe=pid)
+    ref = est.hutch_layer(_np(A), _np(E), k, 6, 3, probe=probe)
+    assert np.all(_rel(n2.cpu().numpy(), ref) < 2 * F32_RTOL)
+    assert torch.equal(c, D.dprc_clip_scale(n2, 0.5))
+
+
+@pytest.mark.parametrize("B,T,d,p,pad,accumulate", [
+    (1, 1, 1, 1, 0, False),
+    (2, 33, 3, 70, 2, True),                    # narrow operand (element loads)
+    (3, 31, 33, 34, 1, False),                  # one past a 32-wide tile, tokens short of a slab
+    (2, 65, 1025, 1030, 3, True),               # 64-wide tiles, ragged, odd strides
+    (2, 40, 2049, 2050, 0, False),              # 128-wide tiles, last ones 1 and 2 wide
+    (5, 32, 130, 4, 0, False),
+])
+def test_f32_accumulate_edges(D, B, T, d, p, pad, accumulate):
+    A, E = _draw(B, T, d, p, dtype="f32", layer=510, row_pad_a=pad, row_pad_e=pad)
+    c = torch.linspace(0.0, 1.0, B + 1, device="cuda")[1:].contiguous()
+    if B > 2:
+        c[1] = 0.0
+        E.select(0, 1).fill_(float("nan"))      # a dropped sample is not read into the sum
+    grad = torch.full((d, p + 3), 0.5, device="cuda")[:, :p]
+    D.dprc_clip_accumulate(A, E, c, grad=grad, accumulate=accumulate)
+    ref = est.clip_accumulate(_np(A), _np(E), c.cpu().numpy().astype(np.float64)) + (0.5 if accumulate else 0.0)
+    err = np.linalg.norm(grad.cpu().numpy() - ref) / np.linalg.norm(ref)
+    assert err < F32_RTOL
+
+
+@pytest.mark.parametrize("s,r", [(16, 7), (20, 40)])
+def test_f32_hutchpp_mixed_column_blocks(D, s, r):
+    # pass 3 projects dense and sign columns that share a block of 16
+    A, E = _draw(2, 50, 90, 210, dtype="f32", law="student_t", layer=520)
+    n2 = D.dprc_norm_hutchpp([(A, E, 1)], s, r, 2)
+    assert np.all(_rel(n2.cpu().numpy(), est.hutchpp_layer(_np(A), _np(E), s, r, 2, 1)) < 1e-4)
+
+
 # ---- layers sharing their activations (one token reduction over A) -------------------------
 
 def _shared_a(B, T, d, ps, layer0=0):
