@@ -323,12 +323,15 @@ GaussBufs take_gauss(Arena& ar, const View& v, int32_t k) {
 // Consecutive bf16 layers that read the same activations (same A, shape and row
 // stride) and sketch the output side share one token reduction over A: each
 // layer's Y = E Z fills k columns of one Y, and the reduction squares each
-// layer's columns separately (q, k, v of an attention block; gate and up).
+// layer's columns separately (q, k, v of an attention block; gate and up).  A group has
+// at most kTokBatchCols columns, what the batched token reduction stages in LDS: three
+// layers of 64 probes took 127 us per 35 MB of activations in one reduction of 192 columns,
+// 40 us as 128 and 64 columns that read the activations once each.
 int32_t group_end(const dprc_layer* layers, int32_t l0, int32_t num_layers, int32_t k, dprc_side side) {
   const dprc_layer& L = layers[l0];
   if (L.dtype != DPRC_BF16 || resolve(L, side) != DPRC_SIDE_OUT) return l0 + 1;
   int32_t l = l0 + 1;
-  while (l < num_layers && l - l0 < kMaxGroup && (int64_t)(l - l0 + 1) * k <= 256) {
+  while (l < num_layers && l - l0 < kMaxGroup && (int64_t)(l - l0 + 1) * k <= kTokBatchCols) {
     const dprc_layer& M = layers[l];
     if (M.A != L.A || M.lda != L.lda || M.d != L.d || M.B != L.B || M.T != L.T || M.dtype != L.dtype ||
         resolve(M, side) != DPRC_SIDE_OUT)
