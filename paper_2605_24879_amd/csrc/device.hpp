@@ -97,15 +97,48 @@ __device__ __forceinline__ uint4 signs_to_bf16x8(uint32_t byte) {
   return r;
 }
 
-// Loads of 8 consecutive bf16 of a token row.  The fast form is one 16-byte
-// load with no branch: callers pass a pointer that is valid and 16-byte aligned
-// even when the lane is masked (a clamped address) and the value is zeroed by a
-// select, so all loads of a stage stay in flight together.  The element form
-// serves rows that are not 16-byte aligned or widths that are not a multiple
-// of 8 (the host picks the form per launch).
-__device__ __forceinline__ uint4 load8_sel(const uint16_t* p, bool ok) {
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  return ok ? v : uint4{0, 0, 0, 0};
+// Loads of 8 consecutive bf16 of a token row, in one of three modes that the host picks per
+// launch (every operand of the launch has to allow it):
+//   kLoadVec   rows on 16-byte boundaries and widths that are multiples of 8: raw buffer
+//              loads, masked lanes read zero through an out-of-range offset;
+//   kLoadAny   any 2-byte aligned rows: 16-byte global loads at the element's own address
+//              (gfx950 takes global loads at any alignment).  A piece may reach past the
+//              end of its row, but never past the operand's last element: it starts at
+//              most 8 elements before the end (the operand has at least 8), and
+//              the caller shifts such a piece down (shr_elems) and drops what is not its
+//              own.  Odd widths are as fast as even ones this way: a vocabulary of 50257
+//              columns projected in 587 us and accumulated in 2706 us with element loads;
+//   kLoadElem  one element at a time, for operands of fewer than 8 elements or with rows
+//              too long for 32-bit offsets.
+enum : int { kLoadElem = 0, kLoadAny = 1, kLoadVec = 2 };
+
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 load16_any(const uint16_t* base, int32_t elem) {
+  const u32x4_any v = *reinterpret_cast<const u32x4_any*>(base + elem);
+  return uint4{v[0], v[1], v[2], v[3]};
+}
+
+// The last element, counted from `from`, at which a 16-byte piece of an operand of B * T
+// rows (width elements, stride ld, samples T * ld apart) may start.
+__device__ __forceinline__ int operand_room(const uint16_t* X, int B, int T, int64_t ld, int64_t width,
+                                            const uint16_t* from) {
+  const int64_t r = (X - from) + ((int64_t)B * T - 1) * ld + width - 8;
+  return (int)(r < 0x3FFFFFFF ? r : 0x3FFFFFFF);
+}
+
+// v with its first s 16-bit elements dropped (s >= 8: nothing of use is left)
+__device__ __forceinline__ uint4 shr_elems(uint4 v, int s) {
+  if (s & 4) v = uint4{v.z, v.w, 0u, 0u};
+  if (s & 2) v = uint4{v.y, v.z, v.w, 0u};
+  if (s & 1)
+    v = uint4{(v.x >> 16) | (v.y << 16), (v.y >> 16) | (v.z << 16), (v.z >> 16) | (v.w << 16), v.w >> 16};
+  return v;
+}
+
+// the first n 16-bit elements of v (n <= 0: none), zeros after them
+__device__ __forceinline__ uint4 first_elems(uint4 v, int n) {
+  auto keep = [&](uint32_t d, int k) { return n >= k + 2 ? d : (n == k + 1 ? d & 0xFFFFu : 0u); };
+  return uint4{keep(v.x, 0), keep(v.y, 2), keep(v.z, 4), keep(v.w, 6)};
 }
 
 __device__ __forceinline__ uint4 load8_elem(const uint16_t* row, int64_t u, int64_t lim, bool ok) {
@@ -150,17 +183,6 @@ __device__ __forceinline__ uint32_t shl16x2(uint32_t v, unsigned short lo, unsig
 __device__ __forceinline__ uint4 expand_signs(uint32_t P, uint32_t mask, uint32_t one) {
   return uint4{(shl16x2(P, 15, 14) & mask) | one, (shl16x2(P, 13, 12) & mask) | one,
                (shl16x2(P, 11, 10) & mask) | one, (shl16x2(P, 9, 8) & mask) | one};
-}
-
-template <bool FAST>
-__device__ __forceinline__ uint4 load_bf16x8(const uint16_t* row, int64_t u, int64_t lim, bool row_ok,
-                                             const uint16_t* safe) {
-  if constexpr (FAST) {
-    const bool ok = row_ok && u < lim;          // lim % 8 == 0: u < lim implies u + 8 <= lim
-    return load8_sel(ok ? row + u : safe, ok);
-  } else {
-    return load8_elem(row, u, lim, row_ok);
-  }
 }
 
 // ---- matrix cores and LDS ------------------------------------------------------------

@@ -42,7 +42,7 @@ struct GInt {
 };
 
 // wg: the tile (before the XCD reordering), split: the token split.
-template <int NW, int NS, bool FAST>
+template <int NW, int NS, int LD>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) {
   constexpr int kThreads = 64 * NW;
   constexpr int WN = NW == 8 ? 64 : 128;             // wave tile columns
@@ -71,10 +71,11 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
   const int64_t ja = (int64_t)d0 + lc, je = (int64_t)p0 + lc;
 
   uint4 ga[NS][RQ], ge[NS][RQ];                   // slabs in flight
-  // FAST: per slab one buffer resource per operand over its (up to) 32 token rows,
+  // kLoadVec: per slab one buffer resource per operand over its (up to) 32 token rows,
   // starting at the tile's first column; rows past T and columns past d / p read
   // as zero through out-of-range offsets, and a slab past the sample's last one has
-  // an empty range.  Element loads otherwise.
+  // an empty range.  kLoadAny: see device.hpp; columns past d / p only reach entries that
+  // are not stored, and rows past T are replaced by zeros on the way to LDS.
   const uint32_t arow = (uint32_t)a.lda * 2u, erow = (uint32_t)a.lde * 2u;
   const uint32_t aoff = d0 + lc < a.d ? (uint32_t)lr * arow + 2u * lc : kOobOffset;
   const uint32_t eoff = p0 + lc < a.p ? (uint32_t)lr * erow + 2u * lc : kOobOffset;
@@ -82,7 +83,18 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     const int tok0 = st * kGK;
     const uint16_t* as = a.A + (int64_t)i * a.a_ss;
     const uint16_t* es = a.E + (int64_t)i * a.e_ss;
-    if constexpr (FAST) {
+    if constexpr (LD == kLoadAny) {                // rows past the slab's last read its first
+      const int rows = st < st_end ? min(kGK, a.T - tok0) : 0;
+      const uint16_t* ab = as + (int64_t)(rows > 0 ? tok0 : 0) * a.lda + d0;
+      const uint16_t* eb = es + (int64_t)(rows > 0 ? tok0 : 0) * a.lde + p0;
+      const int aroom = operand_room(a.A, a.B, a.T, a.lda, a.d, ab), eroom = operand_room(a.E, a.B, a.T, a.lde, a.p, eb);
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const int row = lr + RP * r < rows ? lr + RP * r : 0;
+        ga[sl][r] = load16_any(ab, min(aroom, row * (int)a.lda + lc));
+        ge[sl][r] = load16_any(eb, min(eroom, row * (int)a.lde + lc));
+      }
+    } else if constexpr (LD == kLoadVec) {
       const int rows = st < st_end ? min(kGK, a.T - tok0) : 0;
       const int64_t t0 = rows > 0 ? tok0 : 0;
       const __amdgpu_buffer_rsrc_t ar = buffer_rsrc(as + t0 * a.lda + d0, (uint32_t)rows * arow);
@@ -102,7 +114,25 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
       }
     }
   };
-  auto swrite = [&](int sl, int buf) __attribute__((always_inline)) {
+  // slab st of sample i into LDS buffer buf
+  auto swrite = [&](int sl, int buf, int i, int st, int st_end) __attribute__((always_inline)) {
+    const int tok0 = st * kGK;
+    const int rows = st < st_end ? min(kGK, a.T - tok0) : 0;
+    if (LD == kLoadAny && (rows < kGK || d0 + kGM > a.d || p0 + kGM > a.p)) {
+      const int64_t t0 = rows > 0 ? tok0 : 0;
+      const int aroom = operand_room(a.A, a.B, a.T, a.lda, a.d, a.A + (int64_t)i * a.a_ss + t0 * a.lda + d0);
+      const int eroom = operand_room(a.E, a.B, a.T, a.lde, a.p, a.E + (int64_t)i * a.e_ss + t0 * a.lde + p0);
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const bool ok = lr + RP * r < rows;
+        const int row = ok ? lr + RP * r : 0;
+        const int aat = row * (int)a.lda + lc, eat = row * (int)a.lde + lc;
+        const uint4 va = shr_elems(ga[sl][r], aat - min(aat, aroom)), ve = shr_elems(ge[sl][r], eat - min(eat, eroom));
+        *reinterpret_cast<uint4*>(&la[buf][(lr + RP * r) * kGLd + lc]) = ok ? va : uint4{0, 0, 0, 0};
+        *reinterpret_cast<uint4*>(&le[buf][(lr + RP * r) * kGLd + lc]) = ok ? ve : uint4{0, 0, 0, 0};
+      }
+      return;
+    }
 #pragma unroll
     for (int r = 0; r < RQ; ++r) {
       *reinterpret_cast<uint4*>(&la[buf][(lr + RP * r) * kGLd + lc]) = ga[sl][r];
@@ -170,7 +200,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     // Slabs past the sample's last load empty ranges (zeros).
 #pragma unroll
     for (int q = 0; q < NS; ++q) gload(q, i, st_lo + q, st_hi);
-    swrite(0, 0);
+    swrite(0, 0, i, st_lo, st_hi);
     __syncthreads();
     frag(f0a, f0b, 0, 0);
     constexpr int NQ = kGK / 16;                 // 16-token quarters of a slab (even)
@@ -191,7 +221,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
           mm(f1a, f1b);
         }
       }
-      swrite((k + 1) % NS, (k + 1) % 2);
+      swrite((k + 1) % NS, (k + 1) % 2, i, st + 1, st_hi);
       __syncthreads();
       frag(f0a, f0b, (k + 1) % 2, 0);
       mm(f1a, f1b);
@@ -252,16 +282,16 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     }
 }
 
-template <int NW, int NS, bool FAST>
+template <int NW, int NS, int LD>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_kernel(GemmArgs a) {
-  gemm_body<NW, NS, FAST>(a, blockIdx.x, blockIdx.y);
+  gemm_body<NW, NS, LD>(a, blockIdx.x, blockIdx.y);
 }
 
 // Several layers in one launch, each unsplit (S = 1): job j owns blocks blk0[j] ..
 // blk0[j] + ntiles_j - 1, and blk0[j] is a multiple of 8, so that a job's blocks are
 // dealt to the XCDs as those of a launch of its own; blocks up to the next multiple of
 // 8 are idle.
-template <int NW, int NS, bool FAST>
+template <int NW, int NS, int LD>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_batch_kernel(GemmBatch bt) {
   int jb = 0;
 #pragma unroll 8
@@ -269,7 +299,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_batch_kernel(GemmBatch bt) {
   const GemmArgs& a = bt.job[jb];
   const int wg = (int)blockIdx.x - bt.blk0[jb];
   if (wg >= (int)(((int64_t)a.d + kGM - 1) / kGM * (((int64_t)a.p + kGM - 1) / kGM))) return;
-  gemm_body<NW, NS, FAST>(a, wg, 0);
+  gemm_body<NW, NS, LD>(a, wg, 0);
 }
 
 GemmPlan gemm_plan_v2(int64_t B, int64_t T, int64_t d, int64_t p) {
@@ -285,36 +315,38 @@ GemmPlan gemm_plan_v2(int64_t B, int64_t T, int64_t d, int64_t p) {
   return g;
 }
 
+static int gemm_load(const GemmArgs& a) {        // offsets within one slab stay below 2^31
+  return std::min(load_mode(a.vec_a, a.B, a.T, a.d, a.lda, kGK), load_mode(a.vec_e, a.B, a.T, a.p, a.lde, kGK));
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
   const int tiles = (int)(ceil_div(a.d, kGM) * ceil_div(a.p, kGM));
   dim3 grid((unsigned)tiles, (unsigned)a.S);
   constexpr int NW = 8, NS = 2;
-  // buffer offsets within one 32-row slab stay below 2^31
-  if (a.vec_a && a.vec_e && a.d % 8 == 0 && a.p % 8 == 0 &&
-      (int64_t)kGK * std::max(a.lda, a.lde) * 2 < ((int64_t)1 << 31))
-    DPRC_LAUNCH((gemm_kernel<NW, NS, true>), grid, dim3(64 * NW), 0, st, a);
-  else
-    DPRC_LAUNCH((gemm_kernel<NW, NS, false>), grid, dim3(64 * NW), 0, st, a);
+  const int load = gemm_load(a);
+  if (load == kLoadVec) DPRC_LAUNCH((gemm_kernel<NW, NS, kLoadVec>), grid, dim3(64 * NW), 0, st, a);
+  else if (load == kLoadAny) DPRC_LAUNCH((gemm_kernel<NW, NS, kLoadAny>), grid, dim3(64 * NW), 0, st, a);
+  else DPRC_LAUNCH((gemm_kernel<NW, NS, kLoadElem>), grid, dim3(64 * NW), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_batch(GemmBatch bt, hipStream_t st) {
   if (bt.njobs < 1 || bt.njobs > kGemmMaxJobs) return hipErrorInvalidValue;
   constexpr int NW = 8, NS = 2;
-  bool fast = true;
+  int load = kLoadVec;
   int64_t blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {
     const GemmArgs& a = bt.job[j];
     if (a.S != 1) return hipErrorInvalidValue;
-    fast = fast && a.vec_a && a.vec_e && a.d % 8 == 0 && a.p % 8 == 0 &&
-           (int64_t)kGK * std::max(a.lda, a.lde) * 2 < ((int64_t)1 << 31);
+    load = std::min(load, gemm_load(a));
     bt.blk0[j] = (int32_t)blocks;
     blocks += round_up(ceil_div(a.d, kGM) * ceil_div(a.p, kGM), 8);
   }
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);
-  if (fast) DPRC_LAUNCH((gemm_batch_kernel<NW, NS, true>), grid, dim3(64 * NW), 0, st, bt);
-  else DPRC_LAUNCH((gemm_batch_kernel<NW, NS, false>), grid, dim3(64 * NW), 0, st, bt);
+  if (load == kLoadVec) DPRC_LAUNCH((gemm_batch_kernel<NW, NS, kLoadVec>), grid, dim3(64 * NW), 0, st, bt);
+  else if (load == kLoadAny) DPRC_LAUNCH((gemm_batch_kernel<NW, NS, kLoadAny>), grid, dim3(64 * NW), 0, st, bt);
+  else DPRC_LAUNCH((gemm_batch_kernel<NW, NS, kLoadElem>), grid, dim3(64 * NW), 0, st, bt);
   return hipGetLastError();
 }
 

@@ -47,7 +47,7 @@ struct PInt {
 };
 
 // NBD: NB when the columns are dense, 0 when they are probes.
-template <int RB, int NB, int NBD, bool FAST>
+template <int RB, int NB, int NBD, int LD>
 __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int by) {
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   constexpr bool DENSE = NBD > 0;
@@ -82,10 +82,15 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
   for (int j = 0; j < NL; ++j) {
     const int rr = 4 * j + lrow;
     lpiece[j] = lslot ^ (rr & 15);
-    roff[j] = (uint32_t)(rr * a.ldx) * 2u;
     const int t = t0 + rr;
+    if constexpr (LD == kLoadAny) roff[j] = (uint32_t)((t < a.T ? rr : 0) * a.ldx);   // elements; rows past T read row 0
+    else roff[j] = (uint32_t)(rr * a.ldx) * 2u;
     rowp[j] = xs + (int64_t)(t < a.T ? t : 0) * a.ldx;
   }
+  // kLoadAny: the block's first row, and the last element from it at which a piece may start
+  // (blocks past T read nothing that is used: they start at the sample)
+  const uint16_t* xb = xs + (int64_t)(t0 < a.T ? t0 : 0) * a.ldx;
+  const int room = LD == kLoadAny ? operand_room(a.X, a.B, a.T, a.ldx, a.m, xb) : 0;
 
   f32x4_t acc[RB][NB];
 #pragma unroll
@@ -122,9 +127,11 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       const int col = c0 + 8 * lpiece[j];
-      if constexpr (FAST) {
+      if constexpr (LD == kLoadVec) {
         const bool ok = col < col_end;
         dst[j] = buffer_load16_nt(xr, ok ? roff[j] + 2u * (uint32_t)col : kOobOffset);
+      } else if constexpr (LD == kLoadAny) {       // lanes past the width all read the block's first piece
+        dst[j] = load16_any(xb, min(room, col < col_end ? (int)roff[j] + col : 0));
       } else {
         dst[j] = load8_elem(rowp[j], col, col_end, t0 + 4 * j + lrow < a.T);
       }
@@ -143,11 +150,21 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
       }
     }
   };
-  auto to_lds = [&](const uint4 (&src)[NL]) __attribute__((always_inline)) {
+  auto to_lds = [&](const uint4 (&src)[NL], int st) __attribute__((always_inline)) {
     wave_lds_fence();                              // the previous stage's reads are done
+    const int c0 = st * kProjStage + kProjSlice * wv;
+    if (LD == kLoadAny && c0 + kProjSlice > a.m) { // the slice with the rows' ends (wave-uniform)
 #pragma unroll
-    for (int j = 0; j < NL; ++j)
-      *reinterpret_cast<uint4*>(&xt[(4 * j + lrow) * kProjSlice + 8 * lslot]) = src[j];
+      for (int j = 0; j < NL; ++j) {
+        const int col = c0 + 8 * lpiece[j], at = (int)roff[j] + col;
+        *reinterpret_cast<uint4*>(&xt[(4 * j + lrow) * kProjSlice + 8 * lslot]) =
+            first_elems(shr_elems(src[j], at - min(at, room)), a.m - col);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NL; ++j)
+        *reinterpret_cast<uint4*>(&xt[(4 * j + lrow) * kProjSlice + 8 * lslot]) = src[j];
+    }
     wave_lds_fence();
   };
   auto mult = [&](int st, int uc, const uint4 (&dh)[ND], const uint4 (&dl)[ND]) __attribute__((always_inline)) {
@@ -214,7 +231,7 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
         dh[e] = rdh[q][e];
         dl[e] = rdl[q][e];
       }
-      to_lds(ring[q]);
+      to_lds(ring[q], st);
       gload(ring[q], rdh[q], rdl[q], st + P, k + P < nst ? col_end : 0);
       mult(st, uc, dh, dl);
     };
@@ -260,6 +277,7 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
     float y = 0.f;
 #pragma unroll
     for (int s = 0; s < 4; ++s) y += red[s * rows * RS + r * RS + c];
+    if (LD == kLoadAny && t0 + r >= a.T) y = 0.f;  // (the other modes read zeros there)
     uint32_t h, l;
     split_bf16(y, h, l);
     yhi[(int64_t)c * a.yt_ld + r] = (uint16_t)h;
@@ -502,25 +520,25 @@ __device__ __forceinline__ void project_rows_body(const ProjectArgs& a, int bx, 
 // The row-block body serves the sign-probe instantiations that fit three workgroups of
 // 32 rows in a CU at k = 32 (LDS, and a third of the register file without spills); the
 // general body serves the rest, one row block per workgroup.
-template <int RB, int NB, int NBD, bool FAST>
-constexpr bool kProjRows = NBD == 0 && FAST && RB <= 2 && RB * NB <= 4;
+template <int RB, int NB, int NBD, int LD>
+constexpr bool kProjRows = NBD == 0 && LD == kLoadVec && RB <= 2 && RB * NB <= 4;
 
-template <int RB, int NB, int NBD, bool FAST>
+template <int RB, int NB, int NBD, int LD>
 __device__ __forceinline__ void project_dispatch(const ProjectArgs& a, int bx, int by) {
-  if constexpr (kProjRows<RB, NB, NBD, FAST>) project_rows_body<RB, NB>(a, bx, by);
-  else project_body<RB, NB, NBD, FAST>(a, bx, by);
+  if constexpr (kProjRows<RB, NB, NBD, LD>) project_rows_body<RB, NB>(a, bx, by);
+  else project_body<RB, NB, NBD, LD>(a, bx, by);
 }
 
-template <int RB, int NB, int NBD, bool FAST>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, FAST> ? 3 : 1)))
+template <int RB, int NB, int NBD, int LD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_kernel(ProjectArgs a) {
-  project_dispatch<RB, NB, NBD, FAST>(a, blockIdx.x, blockIdx.y);
+  project_dispatch<RB, NB, NBD, LD>(a, blockIdx.x, blockIdx.y);
 }
 
 // Projections of several layers in one launch (same instantiation): block (x, sample) of
 // job j at blk0[j] + sample * (T_pad / (16 RB rblocks)) + x.
-template <int RB, int NB, int NBD, bool FAST>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, FAST> ? 3 : 1)))
+template <int RB, int NB, int NBD, int LD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_batch_kernel(ProjectBatch bt) {
   int jb = 0;
 #pragma unroll
@@ -528,7 +546,7 @@ void project_batch_kernel(ProjectBatch bt) {
   const ProjectArgs& a = bt.job[jb];
   const int gx = a.T_pad / (16 * RB * a.rblocks);
   const int rel = (int)blockIdx.x - bt.blk0[jb];
-  project_dispatch<RB, NB, NBD, FAST>(a, rel % gx, rel / gx);
+  project_dispatch<RB, NB, NBD, LD>(a, rel % gx, rel / gx);
 }
 
 template <int RB, int NB>
@@ -539,30 +557,30 @@ static size_t project_lds(const ProjectArgs& a) {
 }
 
 template <int RB>
-static bool project_fast(const ProjectArgs& a) {
-  // buffer offsets of one workgroup's rows stay below 2^31
-  return a.vec && a.m % 8 == 0 && (int64_t)16 * RB * a.rblocks * a.ldx * 2 < ((int64_t)1 << 31);
+static int project_load(const ProjectArgs& a) {
+  // offsets of one workgroup's rows stay below 2^31
+  return load_mode(a.vec, a.B, a.T, a.m, a.ldx, (int64_t)16 * RB * a.rblocks);
 }
 
 // Row blocks per workgroup, for the row-block body (the sign-probe instantiations of
 // kProjRows with 16-byte loads; every other launch keeps one block per workgroup).  A
 // workgroup of a narrow layer streams consecutive row blocks, doubling while it reads at
 // most kProjWgBytes of X, and the launch keeps at least kProjMinWgs workgroups (the jobs
-// with the most row blocks per workgroup give way first).  Returns whether the launch
-// takes 16-byte loads.
+// with the most row blocks per workgroup give way first).  Returns the launch's load mode.
 constexpr int64_t kProjWgBytes = 2 << 20;
 constexpr int kProjMaxRowBlocks = 16;
 constexpr int64_t kProjMinWgs = 2048;
 template <int RB, int NB>
-static bool plan_rblocks(ProjectArgs* jobs, int n) {
+static int plan_rblocks(ProjectArgs* jobs, int n) {
   constexpr int rows = 16 * RB;
-  bool fast = true, dense = false;
+  int load = kLoadVec;
+  bool dense = false;
   for (int j = 0; j < n; ++j) {
     jobs[j].rblocks = 1;
-    fast = fast && project_fast<RB>(jobs[j]);
+    load = std::min(load, project_load<RB>(jobs[j]));
     dense = dense || jobs[j].nd > 0;
   }
-  if (!kProjRows<RB, NB, 0, true> || !fast || dense) return fast;
+  if (!kProjRows<RB, NB, 0, kLoadVec> || load != kLoadVec || dense) return load;
   int64_t wgs = 0;
   for (int j = 0; j < n; ++j) {
     ProjectArgs& a = jobs[j];
@@ -587,7 +605,7 @@ static bool plan_rblocks(ProjectArgs* jobs, int n) {
       a.rblocks = top / 2;
     }
   }
-  return true;
+  return load;
 }
 
 // The instantiations that rows_per_wg's row counts reach: sign columns in 16-row blocks or,
@@ -600,7 +618,7 @@ constexpr bool kProjDense = NB <= 2;
 
 template <int RB, int NB>
 static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
-  const bool fast = plan_rblocks<RB, NB>(bt.job, bt.njobs);
+  const int load = plan_rblocks<RB, NB>(bt.job, bt.njobs);
   size_t lds = 0;
   bt.blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {
@@ -610,8 +628,10 @@ static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
   }
   const bool dense = bt.job[0].nd > 0;
 #define DPRC_PROJECT_BATCH_CASE(NBDV)                                                                             \
-  if (fast) DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, true>), dim3(bt.blocks), dim3(kBlock), lds, st, bt); \
-  else DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, false>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);     \
+  if (load == kLoadVec)                                                                                            \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);       \
+  else                                                                                                             \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);       \
   return hipGetLastError();
   if (!dense) {
     if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_BATCH_CASE(0) }
@@ -643,6 +663,16 @@ hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st
         a.words_per_chunk % 16 != 0 || a.nd > a.ncols_pad || a.T_pad % rows_per_wg != 0)
       return hipErrorInvalidValue;
   }
+  // a job that needs element loads sends every job to a launch of its own
+  for (int j = 0; j < bt.njobs; ++j) {
+    const ProjectArgs& a = bt.job[j];
+    if (load_mode(a.vec, a.B, a.T, a.m, a.ldx, rows_per_wg) != kLoadElem) continue;
+    for (int q = 0; q < bt.njobs; ++q) {
+      const hipError_t e = launch_project(bt.job[q], rows_per_wg, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   switch (rb) {
     case 1: return launch_batch_rb<1>(bt, st);
     case 2: return launch_batch_rb<2>(bt, st);
@@ -654,12 +684,17 @@ hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st
 template <int RB, int NB>
 static hipError_t launch_rb_nb(ProjectArgs a, hipStream_t st) {
   if (a.words_per_chunk % 16 != 0 || a.nd > 16 * NB || (a.nd > 0 && a.nz > 0)) return hipErrorInvalidValue;
-  const bool fast = plan_rblocks<RB, NB>(&a, 1);
+  const int load = plan_rblocks<RB, NB>(&a, 1);
   const size_t lds = project_lds<RB, NB>(a);
   dim3 grid((unsigned)(a.T_pad / (16 * RB * a.rblocks)), (unsigned)a.B);
 #define DPRC_PROJECT_CASE(NBDV)                                                                   \
-  if (fast) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, true>), grid, dim3(kBlock), lds, st, a);   \
-  else DPRC_LAUNCH((project_kernel<RB, NB, NBDV, false>), grid, dim3(kBlock), lds, st, a);       \
+  if (load == kLoadVec)                                                                              \
+    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadVec>), grid, dim3(kBlock), lds, st, a);          \
+  else if (load == kLoadAny)                                                                        \
+    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadAny>), grid, dim3(kBlock), lds, st, a);          \
+  else                                                                                              \
+    if constexpr (RB == 1) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadElem>), grid, dim3(kBlock), lds, st, a); \
+    else return hipErrorInvalidValue;                                                               \
   return hipGetLastError();
   if (a.nd == 0) {
     if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_CASE(0) }
@@ -689,6 +724,8 @@ static hipError_t launch_rb(const ProjectArgs& a, hipStream_t st) {
 hipError_t launch_project(const ProjectArgs& args, int rows_per_wg, hipStream_t st) {
   if (rows_per_wg != 16 && rows_per_wg != 32 && rows_per_wg != 64) return hipErrorInvalidValue;
   if (args.T_pad % rows_per_wg != 0) return hipErrorInvalidValue;
+  // element loads are built for 16-row workgroups only
+  if (load_mode(args.vec, args.B, args.T, args.m, args.ldx, rows_per_wg) == kLoadElem) rows_per_wg = 16;
   switch (rows_per_wg) {
     case 16: return launch_rb<1>(args, st);
     case 32: return launch_rb<2>(args, st);

@@ -106,7 +106,7 @@ struct Int {
 // Y read from global memory at use (128 workgroups, 0.6 TB/s); two launches of eight groups
 // of pairs with Y staged in LDS take 36 us per group (3.8 TB/s).  What bounds them now is
 // the LDS: 28 KB of fragment reads per wave and 64-token stage.
-template <int NB, bool FAST, int TT = 1>
+template <int NB, int LD, int TT = 1>
 __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by) {
   // Y stages go through LDS with X (16 bytes per thread and 16 columns) up to 128 columns
   // (143 KB of LDS with two tiles); wider Y is read straight from global memory at use.
@@ -133,7 +133,7 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
 
   const int lr0 = tid >> (3 + TT), lc = (tid & (16 * TT - 1)) * 8;
   const uint16_t* xs = a.X + (int64_t)i * a.x_ss;
-  // FAST: one buffer resource per stage (64 token rows from column j0); rows past
+  // kLoadVec: one buffer resource per stage (64 token rows from column j0); rows past
   // the split and columns past n read as zero through out-of-range offsets
   const uint32_t row_bytes = (uint32_t)a.ldx * 2u;
   const uint32_t lane_off = j0 + lc < a.n ? (uint32_t)lr0 * row_bytes + 2u * lc : kOobOffset;
@@ -147,6 +147,12 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     return NB % TT == 0 || ch < 32 * NB ? ch : 0;
   };
 
+  // kLoadAny: element offset of piece q from the stage's first row and column
+  auto any_off = [&](int q, int rows) __attribute__((always_inline)) {
+    const int r = lr0 + 16 * q;
+    return (r < rows ? r * (int)a.ldx : 0) + lc;
+  };
+
   struct Stage {
     uint4 x[4];
     uint4 y[YN];
@@ -155,19 +161,24 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
   // clamped to the last stage (Y): the load sequence is the same in every stage,
   // so the waits on the in-order load counter count exactly.
   auto gload = [&](Stage& dst, int st) __attribute__((always_inline)) {
-    if constexpr (FAST) {
-      const int t0 = tb + st * kStage;
-      const int rows = max(0, min(kStage, te - t0));
+    const int t0 = tb + st * kStage;
+    const int rows = max(0, min(kStage, te - t0));
+    if constexpr (LD == kLoadVec) {
       const __amdgpu_buffer_rsrc_t xr =
           buffer_rsrc(xs + (int64_t)(rows > 0 ? t0 : 0) * a.ldx + j0, (uint32_t)rows * row_bytes);
 #pragma unroll
       for (int q = 0; q < 4; ++q) dst.x[q] = buffer_load16_nt(xr, lane_off + (uint32_t)(16 * q) * row_bytes);
+    } else if constexpr (LD == kLoadAny) {         // rows past the stage's last read its first
+      const uint16_t* xb = xs + (int64_t)(rows > 0 ? t0 : 0) * a.ldx + j0;
+      const int room = operand_room(a.X, a.B, a.T, a.ldx, a.n, xb);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dst.x[q] = load16_any(xb, min(room, any_off(q, rows)));
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int t = tb + st * kStage + lr0 + 16 * q;
         const bool ok = st < nst && t < te;
-        dst.x[q] = load_bf16x8<false>(xs + (int64_t)(ok ? t : 0) * a.ldx, (int64_t)j0 + lc, a.n, ok, xs);
+        dst.x[q] = load8_elem(xs + (int64_t)(ok ? t : 0) * a.ldx, (int64_t)j0 + lc, a.n, ok);
       }
     }
     if constexpr (YLDS) {
@@ -179,10 +190,26 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
       }
     }
   };
-  auto swrite = [&](const Stage& src, int buf) __attribute__((always_inline)) {
+  // stage st into buffer buf.  kLoadAny: tokens past the last become zeros and pieces that
+  // were moved back from the operand's end move down again (columns past n hold anything:
+  // they only reach results past n).
+  auto swrite = [&](const Stage& src, int buf, int st) __attribute__((always_inline)) {
+    if (LD == kLoadAny && (te - tb < (st + 1) * kStage || j0 + TT * kTile > a.n)) {
+      const int t0 = tb + st * kStage;
+      const int rows = max(0, min(kStage, te - t0));
+      const int room = operand_room(a.X, a.B, a.T, a.ldx, a.n, xs + (int64_t)(rows > 0 ? t0 : 0) * a.ldx + j0);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<uint4*>(&lds[buf][(lr0 + 16 * q) * XLd + lds_swz(lr0 + 16 * q, lc)]) = src.x[q];
+      for (int q = 0; q < 4; ++q) {
+        const int at = any_off(q, rows);
+        const uint4 v = shr_elems(src.x[q], at - min(at, room));
+        *reinterpret_cast<uint4*>(&lds[buf][(lr0 + 16 * q) * XLd + lds_swz(lr0 + 16 * q, lc)]) =
+            lr0 + 16 * q < rows ? v : uint4{0, 0, 0, 0};
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<uint4*>(&lds[buf][(lr0 + 16 * q) * XLd + lds_swz(lr0 + 16 * q, lc)]) = src.x[q];
+    }
     if constexpr (YLDS) {
 #pragma unroll
       for (int r = 0; r < YN; ++r)
@@ -215,7 +242,7 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
         const uint16_t* p = &lds[buf][(32 * ks + 8 * g + r4) * XLd + ((16 * mb + 4 * c4) ^ ((g & 1) << 6))];
         return make_u4(lds_read_tr16(p), lds_read_tr16(p + 4 * XLd));
       };
-      if constexpr (NB <= 4) {
+      if constexpr (NB <= 4 || !YLDS) {
         uint4 bop[2][NB];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -249,14 +276,14 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     Stage ring[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) gload(ring[q], q);
-    swrite(ring[0], 0);
+    swrite(ring[0], 0, 0);
     __syncthreads();
     auto step = [&](int st, auto ph) __attribute__((always_inline)) {
       constexpr int u = decltype(ph)::value;
       gload(ring[u % P], st + P);                  // ring[u % P] held stage st, already in LDS
       mult(u & 1, st);
       // unconditional: after the last stage it stores an unused (empty-range) stage
-      swrite(ring[(u + 1) % P], (u + 1) & 1);
+      swrite(ring[(u + 1) % P], (u + 1) & 1, st + 1);
       __syncthreads();
     };
     // whole groups of P stages in the loop (no early exit reaches its back edge, so
@@ -288,6 +315,16 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
 
   // the tile and the position in it of this wave (a pair's second tile may not exist)
   const int mytile = TT * tile + (wv >> 2), mw = wv & 3;
+  if constexpr (LD == kLoadAny) {                      // results past n (the other modes give zeros)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (mytile * kTile + 16 * (2 * mw + x) + 4 * g + q < a.n) continue;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) w[x][nb][q] = 0.f;
+      }
+  }
   const int64_t tslot = (int64_t)i * a.ntiles + mytile;
   if (a.S == 1 && a.mode == 0) {
     double sq[kMaxGroup] = {};
@@ -322,9 +359,9 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     }
 }
 
-template <int NB, bool FAST>
+template <int NB, int LD>
 __global__ __launch_bounds__(kBlock) void tokred_kernel(TokredArgs a) {
-  tokred_body<NB, FAST>(a, blockIdx.x, blockIdx.y);
+  tokred_body<NB, LD>(a, blockIdx.x, blockIdx.y);
 }
 
 // Token reductions of several layers in one launch (same instantiation).  Within job j
@@ -338,7 +375,7 @@ __global__ __launch_bounds__(kBlock) void tokred_kernel(TokredArgs a) {
 // splits the runs were slower (mlp layers, 5%) and ids map to blocks directly.  The grid
 // is padded to whole windows.
 constexpr int kXcdRun = 16;
-template <int NB, bool FAST, int TT>
+template <int NB, int LD, int TT>
 __global__ __launch_bounds__(kBlock * TT) void tokred_batch_kernel(TokredBatch bt) {
   constexpr int W = 8 * kXcdRun;
   const int id = (int)blockIdx.x;
@@ -352,7 +389,7 @@ __global__ __launch_bounds__(kBlock * TT) void tokred_batch_kernel(TokredBatch b
   const int gx = nt * a.S;
   const int rel = b - bt.blk0[jb], idx = rel % gx;
   const int split = idx / nt, tile = idx - split * nt;
-  tokred_body<NB, FAST, TT>(a, tile * a.S + split, rel / gx);
+  tokred_body<NB, LD, TT>(a, tile * a.S + split, rel / gx);
 }
 
 // Sum of the token splits of one tile, in split order: its squared norm (mode 0)
@@ -562,13 +599,13 @@ hipError_t launch_tokred_sample(const TokredArgs& a, hipStream_t st) {
 hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
   if (bt.njobs < 1 || bt.njobs > kTokMaxJobs) return hipErrorInvalidValue;
   const int nb = bt.job[0].ncols_pad / 16;
-  bool fast = true, pairs = nb % 2 == 0;
+  int load = kLoadVec;
+  bool pairs = nb % 2 == 0;
   int64_t pair_blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {
     const TokredArgs& a = bt.job[j];
     if (a.ncols_pad != bt.job[0].ncols_pad) return hipErrorInvalidValue;   // one instantiation
-    // buffer offsets within one 64-row stage stay below 2^31
-    fast = fast && a.vec && a.n % 8 == 0 && (int64_t)kStage * a.ldx * 2 < ((int64_t)1 << 31);
+    load = std::min(load, load_mode(a.vec, a.B, a.T, a.n, a.ldx, kStage));
     pairs = pairs && a.S == 1 && a.mode == 0;
     pair_blocks += (int64_t)(a.ntiles + 1) / 2 * a.S * a.B;
   }
@@ -576,7 +613,7 @@ hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
   // columns, where one workgroup's LDS leaves room for no second one in a CU (92 KB of it
   // at 96 columns), as soon as the pairs alone give every CU a workgroup.
   if (nb > 4) pairs = pair_blocks >= 256;
-  const int tt = pairs ? 2 : 1;
+  const int tt = pairs && load != kLoadElem ? 2 : 1;  // (element loads: one tile only)
   bt.blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {
     const TokredArgs& a = bt.job[j];
@@ -585,8 +622,10 @@ hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
   }
   const dim3 grid((unsigned)round_up(bt.blocks, 8 * kXcdRun));   // whole windows (see the kernel)
 #define DPRC_TOKRED_BATCH_LAUNCH(NB, TT)                                                                  \
-  if (fast) DPRC_LAUNCH((tokred_batch_kernel<NB, true, TT>), grid, dim3(kBlock * TT), 0, st, bt);        \
-  else DPRC_LAUNCH((tokred_batch_kernel<NB, false, TT>), grid, dim3(kBlock * TT), 0, st, bt);
+  if (load == kLoadVec) DPRC_LAUNCH((tokred_batch_kernel<NB, kLoadVec, TT>), grid, dim3(kBlock * TT), 0, st, bt); \
+  else if (load == kLoadAny)                                                                                        \
+    DPRC_LAUNCH((tokred_batch_kernel<NB, kLoadAny, TT>), grid, dim3(kBlock * TT), 0, st, bt);                       \
+  else DPRC_LAUNCH((tokred_batch_kernel<NB, kLoadElem, 1>), grid, dim3(kBlock), 0, st, bt);
 #define DPRC_TOKRED_BATCH_CASE(NB)                         \
   case NB:                                                  \
     if (tt == 2) { DPRC_TOKRED_BATCH_LAUNCH(NB, 2) }       \
@@ -615,12 +654,12 @@ hipError_t launch_tokred(const TokredArgs& a, hipStream_t st) {
     return launch_tokred_batch(bt, st);
   }
   dim3 grid((unsigned)(a.ntiles * a.S), (unsigned)a.B);
-  // buffer offsets within one 64-row stage stay below 2^31
-  const bool fast = a.vec && a.n % 8 == 0 && (int64_t)kStage * a.ldx * 2 < ((int64_t)1 << 31);
+  const int load = load_mode(a.vec, a.B, a.T, a.n, a.ldx, kStage);
 #define DPRC_TOKRED_CASE(NB)                                                                   \
   case NB:                                                                                     \
-    if (fast) DPRC_LAUNCH((tokred_kernel<NB, true>), grid, dim3(kBlock), 0, st, a);     \
-    else DPRC_LAUNCH((tokred_kernel<NB, false>), grid, dim3(kBlock), 0, st, a);         \
+    if (load == kLoadVec) DPRC_LAUNCH((tokred_kernel<NB, kLoadVec>), grid, dim3(kBlock), 0, st, a);      \
+    else if (load == kLoadAny) DPRC_LAUNCH((tokred_kernel<NB, kLoadAny>), grid, dim3(kBlock), 0, st, a); \
+    else DPRC_LAUNCH((tokred_kernel<NB, kLoadElem>), grid, dim3(kBlock), 0, st, a);                      \
     break;
   switch (a.ncols_pad / 16) {
     DPRC_TOKRED_CASE(1)

@@ -41,6 +41,14 @@ __host__ __device__ constexpr int lds_swz(int row, int col) { return col ^ (((ro
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
+// The load mode (device.hpp) of an operand of B * T token rows of `width` bf16, stride ld,
+// when a workgroup's offsets span `rows` rows.
+inline int load_mode(int vec, int64_t B, int64_t T, int64_t width, int64_t ld, int64_t rows) {
+  if (rows * ld * 2 >= ((int64_t)1 << 31)) return 0;        // kLoadElem
+  if (vec && width % 8 == 0) return 2;                      // kLoadVec
+  return (B * T - 1) * ld + width >= 8 ? 1 : 0;             // kLoadAny
+}
+
 // Y = X R on matrix cores.  X: bf16 token rows [B][T][ldx] (width m).  R has
 // `nd` dense columns per sample (bf16 hi/lo pairs, Rhi/Rlo[i][c][ld_r]) followed
 // by `nz` generated +-1 columns.  Output Yt: bf16 hi/lo, column-major per

@@ -129,6 +129,62 @@ def test_hutch_gaussian_multilayer_accumulate(D):
     assert np.all(_rel(n2.cpu().numpy(), np.array([0.5, 1.0]) + r1 + r2) < NORM_RTOL)
 
 
+# ---- rows at any 2-byte alignment -----------------------------------------------------------
+
+def _in_nans(X, pad, lead):
+    """The same values as a view into storage whose other elements are all NaN: rows `pad`
+    elements apart beyond their width, the first one `lead` elements in, the last one ending
+    with the storage."""
+    B, T, n = X.shape
+    ld = n + pad
+    store = torch.full((lead + B * T * ld - pad,), float("nan"), dtype=X.dtype, device=X.device)
+    view = store.as_strided((B, T, n), (T * ld, ld, 1), lead)
+    view.copy_(X)
+    return view
+
+
+@pytest.mark.parametrize("B,T,d,p,k,pads,lead", [
+    (1, 1, 1, 1, 2, (0, 0), 0),           # fewer than 8 elements: element loads
+    (2, 3, 3, 5, 4, (1, 2), 1),           # rows shorter than one 16-byte piece
+    (3, 17, 8, 9, 16, (1, 0), 1),         # 16-byte widths on odd rows, one more than a piece
+    (2, 65, 129, 513, 16, (0, 4), 3),     # one past the tiles of 128 and 512, T one past a stage
+    (2, 100, 255, 1031, 33, (7, 1), 5),   # general projection body, 33 columns
+    (1, 130, 777, 4099, 80, (0, 0), 1),   # 96 columns, several probe chunks
+    (2, 4200, 24, 31, 20, (3, 8), 2),     # 32-row workgroups
+])
+@pytest.mark.parametrize("side", [0, 1])
+def test_any_alignment_hutch_and_accumulate(D, B, T, d, p, k, pads, lead, side):
+    A, E = _draw(B, T, d, p, layer=530)
+    Av, Ev = _in_nans(A, pads[0], lead), _in_nans(E, pads[1], lead)
+    n2 = D.dprc_norm_hutch([(Av, Ev, 3)], k, 6, side=side)
+    ref = est.hutch_layer(_np(A), _np(E), k, 6, 3, side=side)
+    assert np.all(_rel(n2.cpu().numpy(), ref) < NORM_RTOL)
+    c = torch.linspace(0.5, 1.0, B, device="cuda")
+    g = D.dprc_clip_accumulate(Av, Ev, c)
+    refg = est.clip_accumulate(_np(A), _np(E), c.cpu().numpy().astype(np.float64))
+    assert np.linalg.norm(g.cpu().numpy() - refg) < 1e-5 * np.linalg.norm(refg)
+    # two layers: the batched kernels; the gradients in one launch
+    n2l = torch.zeros(2, B, device="cuda")
+    D.dprc_norm_hutch([(Av, Ev, 3), (A, E, 3)], k, 6, side=side, n2_layers=n2l)
+    assert np.all(_rel(n2l.cpu().numpy(), np.stack([ref, ref])) < NORM_RTOL)
+    for q in D.dprc_clip_accumulate_layers([(Av, Ev), (A, E)], c):
+        assert np.linalg.norm(q.cpu().numpy() - refg) < 1e-5 * np.linalg.norm(refg)
+
+
+@pytest.mark.parametrize("B,T,d,p,s,r", [(2, 40, 33, 61, 8, 9), (1, 8200, 35, 131, 20, 12)])
+def test_any_alignment_hutchpp_and_gaussian(D, B, T, d, p, s, r):
+    # dense projections of unaligned rows (16- and 64-row workgroups), stored reductions
+    A, E = _draw(B, T, d, p, law="student_t", layer=540)
+    Av, Ev = _in_nans(A, 3, 1), _in_nans(E, 0, 1)
+    for pairs in ([(Av, Ev, 2)], [(Av, Ev, 2), (A, E, 5)]):
+        n2l = torch.zeros(len(pairs), B, device="cuda")
+        D.dprc_norm_hutchpp(pairs, s, r, 7, n2_layers=n2l)
+        for q, (_, _, j) in enumerate(pairs):
+            assert np.all(_rel(n2l[q].cpu().numpy(), est.hutchpp_layer(_np(A), _np(E), s, r, 7, j)) < NORM_RTOL)
+    n2 = D.dprc_norm_hutch([(Av, Ev, 2)], 11, 7, probe=D.PROBE_GAUSSIAN)
+    assert np.all(_rel(n2.cpu().numpy(), est.hutch_layer(_np(A), _np(E), 11, 7, 2, probe="gaussian")) < NORM_RTOL)
+
+
 # fp32 sums of n terms in any order: relative error at most n 2^-24 of the sum of magnitudes;
 # with random signs that is about sqrt(n) 2^-24 of the result, and 3e-6 covers n = 1000 tenfold
 F32_RTOL = 3e-6
