@@ -242,8 +242,8 @@ dprc_status dprc_private_adamw(float* theta, float* m, float* v, int64_t ldt, co
  * (lam = 0 only when n_lambda = 1), in fp64.  arg (may be NULL) receives
  * (i, j, l) of the maximiser, the first in (i, j, l) order among equal values.
  * Each form's CDF is a convolution integral evaluated by composite
- * Gauss-Legendre quadrature (16 panels of 16 nodes) with regularised incomplete
- * gamma functions; about 1e-12 absolute.  x, best, arg: device.  Limits:
+ * Gauss-Legendre quadrature (at least 16 panels of 16 nodes) over a chi density and the
+ * integral of a gamma density; about 1e-12 absolute.  x, best, arg: device.  Limits:
  * 1 <= nx <= 65535, k >= 1, 2 <= d, k * d < 2^31, 1 <= n_lambda <= 4096.
  * Workspace: dprc_envelope_middle_workspace() bytes. */
 size_t dprc_envelope_middle_workspace(int32_t nx, int32_t d, int32_t n_lambda);

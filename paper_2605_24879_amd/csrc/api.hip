@@ -804,6 +804,24 @@ void gauss_legendre(int n, double* x, double* w) {
   }
 }
 
+// gi[q][e] = integral from -1 to x_q of the polynomial of degree < n that is 1 at node e and 0
+// at the others: sum over m < n of w_e P_m(x_e) / 2 times (2m + 1) int_{-1}^{x_q} P_m, which
+// is x_q + 1 for m = 0 and P_{m+1}(x_q) - P_{m-1}(x_q) after it.
+void integration_matrix(int n, const double* x, const double* w, double* gi) {
+  for (int q = 0; q < n; ++q)
+    for (int e = 0; e < n; ++e) {
+      double sum = 0.5 * (x[q] + 1.0);
+      double a0 = 1.0, a1 = x[q], b0 = 1.0, b1 = x[e];        // P_{m-1}, P_m at x_q and x_e
+      for (int m = 1; m < n; ++m) {
+        const double a2 = ((2.0 * m + 1.0) * x[q] * a1 - m * a0) / (m + 1.0);
+        const double b2 = ((2.0 * m + 1.0) * x[e] * b1 - m * b0) / (m + 1.0);
+        sum += 0.5 * b1 * (a2 - a0);
+        a0 = a1; a1 = a2; b0 = b1; b1 = b2;
+      }
+      gi[q * n + e] = w[e] * sum;
+    }
+}
+
 // Scratch of dprc_norm_hutch_clip_static: one array on every device the library runs
 // on, held until the process ends.  In host code the name `scratch` is a host-side
 // stand-in, not a device address: the address comes from hipGetSymbolAddress, taken
@@ -1425,8 +1443,8 @@ dprc_status dprc_envelope_middle(const double* x, int32_t nx, int32_t k, int32_t
   EnvArgs a;
   a.x = x; a.nx = nx; a.k = k; a.d = d; a.n_lambda = n_lambda;
   a.ncand = (int64_t)d * (d - 1) / 2 * n_lambda;
-  a.panels = 16;
   gauss_legendre(kEnvNodes, a.gx, a.gw);
+  integration_matrix(kEnvNodes, a.gx, a.gw, &a.gi[0][0]);
   Arena ar(ws);
   const int nblk = env_blocks(a.ncand);
   a.part_v = ar.take<double>((size_t)nx * nblk);

@@ -292,8 +292,8 @@ struct EnvArgs {
   const double* x;
   int32_t nx, k, d, n_lambda;
   int64_t ncand;          // d (d - 1) / 2 * n_lambda
-  int32_t panels;
   double gx[kEnvNodes], gw[kEnvNodes];   // Gauss-Legendre nodes and weights on [-1, 1]
+  double gi[kEnvNodes][kEnvNodes];       // gi[q][e]: integral from -1 to node q of the polynomial that is 1 at node e, 0 at the others
   double* part_v;         // [nx][blocks]
   int64_t* part_c;
   double* best;           // [nx]

@@ -158,3 +158,63 @@ def test_pld_fold_and_delta_kernels_match_oracle(mods):
     got = D.dprc_pld_delta(q2, h, qi2, _t(eps)).cpu().numpy()
     ref = np.array([ac.delta_of_eps(grid, r2, ri2, e) for e in eps])
     assert np.max(np.abs(got - ref)) < 1e-12
+
+
+@pytest.mark.parametrize("k,d,i,j,lam", [
+    (1, 3, 1, 2, 0.5), (1, 64, 63, 1, 0.01), (2, 5, 2, 1, 0.35), (32, 64, 1, 63, 0.5), (32, 64, 40, 3, 0.02),
+    (64, 200, 1, 199, 0.5),                  # the second term is narrow: more than 16 panels
+])
+def test_middle_region_single_forms(mods, k, d, i, j, lam):
+    # MiddleRegionCDF is the largest form; each form's own CDF is checked through d = i + j with
+    # the grid holding lam, against fine quadrature (400 panels of 32 nodes, scipy's gammainc)
+    D, _ = mods
+    from scipy import special
+    nodes, w = np.polynomial.legendre.leggauss(32)
+
+    def form(x, i, j, lam):
+        n1, n2 = i * k, j * k
+        a, b = lam / n1, (1 - lam) / n2
+        smax, c = math.sqrt(x / a), math.sqrt(n1)
+        lo, hi = max(0.0, c - 10), min(smax, c + 10)
+        if hi <= lo:
+            return 0.0
+        edge = hi >= smax
+        t = np.linspace(0 if edge else lo, math.sqrt(smax - lo) if edge else hi, 401)
+        h = (t[1:] - t[:-1]) / 2
+        tt = (t[:-1] + h)[:, None] + h[:, None] * nodes
+        s = smax - tt * tt if edge else tt
+        rest = a * tt * tt * (2 * smax - tt * tt) if edge else x - a * s * s
+        ok = (s > 0) & (rest > 0)
+        f = np.exp((1 - n1 / 2) * math.log(2) - special.gammaln(n1 / 2) + (n1 - 1) * np.log(np.where(ok, s, 1)) - s * s / 2)
+        f = np.where(ok, f * (2 * tt if edge else 1), 0) * special.gammainc(n2 / 2, np.where(ok, rest, 0) / (2 * b))
+        return float((h * (f @ w)).sum())
+
+    for x in (0.8, 1.001, 1.3):
+        best, arg = D.dprc_envelope_middle(_t([x]), k, d, 51)
+        bi, bj, bl = arg[0].tolist()
+        blam = bl / 100.0
+        ref = form(x, bi, bj, blam) if bl else special.gammainc(bj * k / 2, x * bj * k / 2)
+        assert abs(best.item() - ref) < 1e-11            # the maximiser's value
+        assert best.item() > form(x, i, j, lam) - 1e-11  # and no other form exceeds it
+
+
+@pytest.mark.parametrize("n_half,n_bins", [(1, 0), (33, 1), (100, 65), (700, 513)])
+def test_pld_small_grids(mods, n_half, n_bins):
+    # grids shorter than a workgroup, bins that do not fill a wave's table
+    D, A = mods
+    h, sigma, p = 0.05, 0.9, 0.3
+    y = w = None
+    if n_bins:
+        y = np.linspace(0.3, 2.0, n_bins)
+        w = np.full(n_bins, 1.0 / n_bins)
+        w[n_bins // 2] = 0.0
+        w /= max(w.sum(), 1e-300) if w.sum() > 0 else 1.0
+        if w.sum() == 0:
+            w[:] = 1.0
+    q, qi = D.dprc_pld_step(sigma, p, h, n_half, _t(y) if n_bins else None, _t(w) if n_bins else None)
+    grid, qr, qir = ac.single_step_pld(sigma, p, h, n_half * h, y, w)
+    assert np.max(np.abs(q.cpu().numpy() - qr)) < 1e-13 and abs(qi.item() - qir) < 1e-13
+    r = _t(np.convolve(qr, qr))
+    q2, qi2 = D.dprc_pld_fold(r, len(qr), qi, qi)
+    r2, ri2 = ac._conv_truncated(qr, qir, qr, qir)
+    assert np.max(np.abs(q2.cpu().numpy() - r2)) < 1e-13 and abs(qi2.item() - ri2) < 1e-13
