@@ -97,7 +97,8 @@ def _compose2(a, ainf, b, binf):
     dprc_pld_fold truncates it back to the grid and updates the atom."""
     L = a.numel()
     size = 1 << (2 * L - 2).bit_length()
-    r = torch.fft.irfft(torch.fft.rfft(a, size) * torch.fft.rfft(b, size), size)
+    fa = torch.fft.rfft(a, size)
+    r = torch.fft.irfft(fa * (fa if b is a else torch.fft.rfft(b, size)), size)
     return D.dprc_pld_fold(r, L, ainf, binf)
 
 
