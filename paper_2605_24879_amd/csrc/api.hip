@@ -595,8 +595,10 @@ dprc_status run_qr(PPBufs* const* bs, const View* vs, int n, uint32_t k0, uint32
       };
       for (int l = 0; l < n; ++l) {
         const int nlev = bs[l]->qr.nlev;
-        if (e >= nlev) continue;
-        const int level = pass == 0 ? e : nlev - 1 - e;
+        // both ways the trees are aligned at their leaves, so that the expensive level 0 of
+        // every layer shares a launch
+        const int level = pass == 0 ? e : maxlev - 1 - e;
+        if (level >= nlev) continue;
         QrJob j = qr_job(*bs[l], vs[l], level, k0, k1, bf16_out);
         j.blk0 = bt.blocks;
         bt.job[bt.njobs++] = j;

@@ -117,13 +117,28 @@ __device__ __forceinline__ int qr_job_index(const QrBatch& bt) {
   return jb;
 }
 
+// f(QInt<I>{}) for I = B, B + 1, ..., E - 1.
+template <int V>
+struct QInt {
+  static constexpr int value = V;
+};
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(QInt<B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
 // ---- factor one 128-row block of a level ----------------------------------------------------------
-// Lane l holds rows l and l + 64 of the block.  Step k works on column k, held in
-// register column 0: the columns not yet factored shift down one place after each
-// step, so every register index is a constant.  v_k = x_k - alpha_k e_k over rows
-// >= k, tau_k = 2 / |v_k|^2 (0: identity reflector for a zero column), alpha_k =
-// R_kk; the dot products v_k . A_c come from one pass with the norm: x_k . A_c -
-// alpha_k A_kc.  v_k, tau_k and row k of R are written out as each step ends.
+// Lane l holds rows l and l + 64 of the block.  Step k works on column k: v_k = x_k -
+// alpha_k e_k over rows >= k, tau_k = 2 / |v_k|^2 (0: identity reflector for a zero column),
+// alpha_k = R_kk; the dot products v_k . A_c come from one pass with the norm: x_k . A_c -
+// alpha_k A_kc.  v_k stays in column k (rows >= k) and row k of R in lane k's row (columns
+// > k, with alpha_k kept apart) until the block is done.  The steps are unrolled: each works
+// on the columns it still has, with constant register indices (a loop that moved the
+// remaining columns down one register per step, and kept them all, took 17 to 20 us per level
+// at 16 columns, this takes 12 to 15).
 template <int SP>
 __global__ __launch_bounds__(64) void qr_factor_kernel(QrBatch bt) {
   __shared__ double red[SP * kRedLd];
@@ -166,231 +181,183 @@ __global__ __launch_bounds__(64) void qr_factor_kernel(QrBatch bt) {
   double* tb = L.tau + ((int64_t)i * L.nblk + b) * s;
   const bool has_next = level + 1 < a.nlev;
   const QrLevel N = has_next ? a.X : a.L;
-  // outputs stay in registers until the loop ends (a store costs the wave tens of
-  // cycles even with one lane active): v_k and tau_k enter register column SP - 1
-  // and move down one place per step, so after s steps column k sits at SP - s + k;
-  // lane k keeps row k of R (offset e from the diagonal in register column e)
-  double Vs[2][SP], Ts[SP], Rr[SP];
+  double diag = 0.0, tau = 0.0;                     // lane k: alpha_k, tau_k
+  static_for<0, SP>([&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
+    if (k < s) {                                    // uniform
+      const double x0k = lane >= k ? A[0][k] : 0.0;
+      double pv[SP];
 #pragma unroll
-  for (int e = 0; e < SP; ++e) {
-    Vs[0][e] = Vs[1][e] = 0.0;
-    Ts[e] = 0.0;
-    Rr[e] = 0.0;
-  }
-  for (int k = 0; k < s; ++k) {
-    double pv[SP];
+      for (int c = k; c < SP; ++c) pv[c] = x0k * A[0][c] + A[1][k] * A[1][c];
+      wave_vec_sum<SP>(pv, k, red, tot);
+      const double nrm2 = pv[k];
+      if (nrm2 > 0.0) {                             // uniform; a zero column keeps the identity reflector
+        const double x0 = readlane_f64(A[0][k], k);
+        const double al = -copysign(sqrt(nrm2), x0);
+        const double v0 = x0 - al;
+        const double vn2 = nrm2 - x0 * x0 + v0 * v0;
+        const double t = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
+        const double tv0 = lane >= k ? t * (lane == k ? v0 : A[0][k]) : 0.0, tv1 = t * A[1][k];
 #pragma unroll
-    for (int c = 0; c < SP; ++c) pv[c] = 0.0;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const double xk = lane + 64 * u >= k ? A[u][0] : 0.0;
-#pragma unroll
-      for (int c = 0; c < SP; ++c) pv[c] += xk * A[u][c];
-    }
-    wave_vec_sum<SP>(pv, 0, red, tot);
-    const double nrm2 = pv[0];
-    double t = 0.0, al = 0.0;
-    if (nrm2 > 0.0) {                               // uniform; a zero column keeps the identity reflector
-      const double x0 = readlane_f64(A[0][0], k);  // row k < 32 sits in lane k
-      al = -copysign(sqrt(nrm2), x0);
-      const double v0 = x0 - al;
-      const double vn2 = nrm2 - x0 * x0 + v0 * v0;
-      t = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
-      double d[SP];
-#pragma unroll
-      for (int c = 1; c < SP; ++c) d[c] = pv[c] - al * readlane_f64(A[0][c], k);
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int j = lane + 64 * u;
-        if (j >= k) {
-          const double vj = j == k ? v0 : A[u][0];
-#pragma unroll
-          for (int c = 1; c < SP; ++c) A[u][c] -= t * vj * d[c];
-          A[u][0] = vj;
+        for (int c = k + 1; c < SP; ++c) {
+          const double d = pv[c] - al * readlane_f64(A[0][c], k);
+          A[0][c] -= tv0 * d;
+          A[1][c] -= tv1 * d;
+        }
+        if (lane == k) {
+          A[0][k] = v0;
+          diag = al;
+          tau = t;
         }
       }
     }
-    // v_k (zero above the diagonal; for a zero column the column itself, which is zero),
-    // tau_k, and row k of R (R_kk = alpha_k, R_k,k+e = A[0][e]) in lane k
+  });
+  // V (zero above the diagonal), tau, and the rows of R into rows b*s + q of the next level's
+  // input (zero left of the diagonal)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int j = lane + 64 * u;
-#pragma unroll
-      for (int e = 0; e + 1 < SP; ++e) Vs[u][e] = Vs[u][e + 1];
-      Vs[u][SP - 1] = j >= k ? A[u][0] : 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e + 1 < SP; ++e) Ts[e] = Ts[e + 1];
-    Ts[SP - 1] = t;
-    if (lane == k) {
-      Rr[0] = al;
-#pragma unroll
-      for (int e = 1; e < SP; ++e) Rr[e] = A[0][e];
-    }
-    // the remaining columns move down one register column
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-      for (int c = 0; c + 1 < SP; ++c) A[u][c] = A[u][c + 1];
-      A[u][SP - 1] = 0.0;
+  for (int k = 0; k < SP; ++k) {
+    if (k < s) {
+      V[(int64_t)k * kQrRows + lane] = lane >= k ? A[0][k] : 0.0;
+      V[(int64_t)k * kQrRows + lane + 64] = A[1][k];
     }
   }
-  // V (column k of the block at register column SP - s + k), tau, and the rows of R
-  // into rows b*s + q of the next level's input (zero left of the diagonal)
-#pragma unroll
-  for (int e = 0; e < SP; ++e) {
-    const int k = e - (SP - s);
-    if (k >= 0) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) V[(int64_t)k * kQrRows + lane + 64 * u] = Vs[u][e];
-      if (lane == 0) tb[k] = Ts[e];
-    }
-  }
+  if (lane < s) tb[lane] = tau;
   if (has_next && lane < s) {
     double* nm = N.M + (int64_t)i * s * N.rows + (int64_t)b * s + lane;
 #pragma unroll
-    for (int e = 0; e < SP; ++e) {
-      if (lane + e < s) nm[(int64_t)(lane + e) * N.rows] = Rr[e];
-      if (e >= 1 && e <= lane) nm[(int64_t)(lane - e) * N.rows] = 0.0;
-    }
+    for (int c = 0; c < SP; ++c)
+      if (c < s) nm[(int64_t)c * N.rows] = c > lane ? A[0][c] : (c == lane ? diag : 0.0);
   }
 }
 
 // ---- expand one block: W = H_0 ... H_{s-1} [Q_up rows; 0]; level 0 writes Q and C_b = Q_b^T P_b ----
+// Wave 0 applies the reflectors (unrolled, as in the factorization).  At level 0 the other
+// waves draw the residual probes meanwhile, and all four then form C_b on the fp64 matrix
+// cores (16x16x4 MFMA: A[c][j] from the block's Q in LDS, B[j][q] = +-1 from the probe bits;
+// D register e of lane l is row 4 e + l / 16, column l % 16).  One wave adding 128 signed rows
+// per entry took 37 of the 49 us of a level-0 launch.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 template <int SP>
-__global__ __launch_bounds__(64) void qr_expand_kernel(QrBatch bt) {
+__global__ __launch_bounds__(256) void qr_expand_kernel(QrBatch bt) {
   __shared__ double red[SP * kRedLd];
   __shared__ double tot[SP];
-  __shared__ double qs[SP * (kQrRows + 1)];
+  constexpr int SR = SP < 16 ? 16 : SP;           // rows of Q in LDS, whole blocks of 16
+  constexpr int QLd = kQrRows + 1;
+  __shared__ double qs[SR * QLd];
   __shared__ uint32_t zw[256 * 4];
   const QrJob& a = bt.job[qr_job_index(bt)];
   const int level = a.level;
   const int rel = (int)blockIdx.x - a.blk0;
-  const int b = rel % a.L.nblk, i = rel / a.L.nblk, lane = threadIdx.x;
+  const int b = rel % a.L.nblk, i = rel / a.L.nblk, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int s = a.s;
   const QrLevel L = a.L;
-  const bool top = level + 1 == a.nlev;
-  const QrLevel U = top ? a.L : a.X;
-  // all loads are issued before the first use (masked entries read a valid address)
-  double W[2][SP];
-  const double* uq = U.Q + (int64_t)i * s * U.rows + (int64_t)b * s;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int j = lane + 64 * u;
-#pragma unroll
-    for (int c = 0; c < SP; ++c) {
-      const bool ok = c < s && j < s;
-      double w = 0.0;
-      if (top) w = ok && j == c ? 1.0 : 0.0;
-      else {
-        const double x = uq[ok ? (int64_t)c * U.rows + j : 0];
-        w = ok ? x : 0.0;
-      }
-      W[u][c] = w;
-    }
-  }
-  // reflectors in reverse order: register column e holds v_{s-1-e}; the columns
-  // move down one place after each step, so every register index is a constant
-  const double* Vb = L.V + ((int64_t)i * L.nblk + b) * s * kQrRows;
-  double Vr[2][SP];
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int e = 0; e < SP; ++e) {
-      const bool ok = e < s;
-      const double x = Vb[ok ? (int64_t)(s - 1 - e) * kQrRows + lane + 64 * u : 0];
-      Vr[u][e] = ok ? x : 0.0;
-    }
-  const double* tb = L.tau + ((int64_t)i * L.nblk + b) * s;
-  for (int k = s - 1; k >= 0; --k) {
-    const double t = tb[k];
-    const double v0 = Vr[0][0], v1 = Vr[1][0];
+  if (wv == 0) {
+    const bool top = level + 1 == a.nlev;
+    const QrLevel U = top ? a.L : a.X;
+    // all loads are issued before the first use (masked entries read a valid address)
+    double W[2][SP], Vr[2][SP];
+    const double* uq = U.Q + (int64_t)i * s * U.rows + (int64_t)b * s;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
+      const int j = lane + 64 * u;
 #pragma unroll
-      for (int e = 0; e + 1 < SP; ++e) Vr[u][e] = Vr[u][e + 1];
-      Vr[u][SP - 1] = 0.0;
-    }
-    if (t == 0.0) continue;                       // uniform
-    double pv[SP];
-#pragma unroll
-    for (int c = 0; c < SP; ++c) pv[c] = v0 * W[0][c] + v1 * W[1][c];
-    wave_vec_sum<SP>(pv, 0, red, tot);
-#pragma unroll
-    for (int c = 0; c < SP; ++c) {
-      W[0][c] -= t * v0 * pv[c];
-      W[1][c] -= t * v1 * pv[c];
-    }
-  }
-  if (level > 0) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = b * kQrRows + lane + 64 * u;
-      if (row < L.rows) {
-#pragma unroll
-        for (int c = 0; c < SP; ++c)
-          if (c < s) L.Q[((int64_t)i * s + c) * L.rows + row] = W[u][c];
+      for (int c = 0; c < SP; ++c) {
+        const bool ok = c < s && j < s;
+        double w = 0.0;
+        if (top) w = ok && j == c ? 1.0 : 0.0;
+        else {
+          const double x = uq[ok ? (int64_t)c * U.rows + j : 0];
+          w = ok ? x : 0.0;
+        }
+        W[u][c] = w;
       }
     }
-    return;
-  }
-  // level 0: rows of Q (rows >= m are zero: their reflector entries are zero)
+    const double* Vb = L.V + ((int64_t)i * L.nblk + b) * s * kQrRows;
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int64_t row = (int64_t)b * kQrRows + lane + 64 * u;
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int c = 0; c < SP; ++c) {
-      if (c < s) {
-        const double q = row < a.m ? W[u][c] : 0.0;
-        qs[c * (kQrRows + 1) + lane + 64 * u] = q;
-        if (a.Q && row < a.m) a.Q[(int64_t)i * a.q_ss + (int64_t)c * a.q_ld + row] = (float)q;
-        if (a.Qhi && row < a.qh_ld) {
-          uint32_t h, l;
-          split_bf16((float)q, h, l);
-          a.Qhi[(int64_t)i * a.qh_ss + (int64_t)c * a.qh_ld + row] = (uint16_t)h;
-          a.Qlo[(int64_t)i * a.qh_ss + (int64_t)c * a.qh_ld + row] = (uint16_t)l;
+      for (int k = 0; k < SP; ++k) Vr[u][k] = Vb[k < s ? (int64_t)k * kQrRows + lane + 64 * u : 0];
+    const double* tb = L.tau + ((int64_t)i * L.nblk + b) * s;
+    static_for<0, SP>([&](auto ec) __attribute__((always_inline)) {
+      constexpr int k = SP - 1 - decltype(ec)::value;      // reflectors in reverse order
+      if (k < s) {                                 // uniform
+        const double t = tb[k];
+        if (t != 0.0) {
+          double pv[SP];
+#pragma unroll
+          for (int c = 0; c < SP; ++c) pv[c] = Vr[0][k] * W[0][c] + Vr[1][k] * W[1][c];
+          wave_vec_sum<SP>(pv, 0, red, tot);
+          const double t0 = t * Vr[0][k], t1 = t * Vr[1][k];
+#pragma unroll
+          for (int c = 0; c < SP; ++c) {
+            W[0][c] -= t0 * pv[c];
+            W[1][c] -= t1 * pv[c];
+          }
+        }
+      }
+    });
+    if (level > 0) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int row = b * kQrRows + lane + 64 * u;
+        if (row < L.rows) {
+#pragma unroll
+          for (int c = 0; c < SP; ++c)
+            if (c < s) L.Q[((int64_t)i * s + c) * L.rows + row] = W[u][c];
+        }
+      }
+    } else {
+      // rows of Q (rows >= m are zero: their reflector entries are zero)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int64_t row = (int64_t)b * kQrRows + lane + 64 * u;
+#pragma unroll
+        for (int c = 0; c < SR; ++c) {
+          const double q = c < SP && c < s && row < a.m ? W[u][c < SP ? c : 0] : 0.0;
+          qs[c * QLd + lane + 64 * u] = q;
+          if (c < s) {
+            if (a.Q && row < a.m) a.Q[(int64_t)i * a.q_ss + (int64_t)c * a.q_ld + row] = (float)q;
+            if (a.Qhi && row < a.qh_ld) {
+              uint32_t h, l;
+              split_bf16((float)q, h, l);
+              a.Qhi[(int64_t)i * a.qh_ss + (int64_t)c * a.qh_ld + row] = (uint16_t)h;
+              a.Qlo[(int64_t)i * a.qh_ss + (int64_t)c * a.qh_ld + row] = (uint16_t)l;
+            }
+          }
         }
       }
     }
+  } else if (level == 0) {
+    // probe words of rows b*128 .. b*128+127 (one Philox block per column)
+    for (int cc = (int)threadIdx.x - 64; cc < a.r; cc += 192) {
+      const u32x4 v = rademacher_block(a.key0, a.key1, a.layer, kStreamProbe, (uint32_t)b, (uint32_t)cc);
+      zw[cc * 4 + 0] = v.x; zw[cc * 4 + 1] = v.y; zw[cc * 4 + 2] = v.z; zw[cc * 4 + 3] = v.w;
+    }
   }
-  // probe words of rows b*128 .. b*128+127 (one Philox block per column)
-  for (int cc = lane; cc < a.r; cc += 64) {
-    const u32x4 v = rademacher_block(a.key0, a.key1, a.layer, kStreamProbe, (uint32_t)b, (uint32_t)cc);
-    zw[cc * 4 + 0] = v.x; zw[cc * 4 + 1] = v.y; zw[cc * 4 + 2] = v.z; zw[cc * 4 + 3] = v.w;
-  }
-  qr_wave_fence();
-  // C_b[c][cc] = sum_j Q[j][c] z(j, cc) over this block's rows; a lane takes
-  // outputs pr = lane + 64 t, four at a time so that four sums advance together
+  if (level > 0) return;
+  __syncthreads();
+  // C_b[c][q] = sum_j Q[j][c] z(j, q): blocks of 16 x 16 entries dealt to the waves
   double* cp = a.Cpart + ((int64_t)i * L.nblk + b) * s * a.r;
-  for (int p0 = lane; p0 < s * a.r; p0 += 256) {
-    const double* qc[4];
-    uint32_t zoff[4];
-    bool on[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int pr = p0 + 64 * t;
-      on[t] = pr < s * a.r;
-      const int c = on[t] ? pr / a.r : 0, cc = on[t] ? pr - c * a.r : 0;
-      qc[t] = qs + c * (kQrRows + 1);
-      zoff[t] = (uint32_t)cc * 4;
-    }
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  const int g = lane >> 4, l16 = lane & 15;
+  const int nq = (a.r + 15) / 16, nblocks = (s + 15) / 16 * nq;
+  for (int e = wv; e < nblocks; e += 4) {
+    const int c0 = 16 * (e / nq), q0 = 16 * (e % nq);
+    const double* qa = qs + (c0 + l16) * QLd + g;
+    const uint32_t* zq = zw + 4 * min(q0 + l16, a.r - 1);
+    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
     for (int w = 0; w < 4; ++w) {
-      uint32_t bits[4];
+      const uint32_t bits = zq[w] >> g;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) bits[t] = zw[zoff[t] + w];
-#pragma unroll
-      for (int jj = 0; jj < 32; ++jj) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const double q = qc[t][32 * w + jj];
-          acc[t] += ((bits[t] >> jj) & 1u) ? -q : q;
-        }
+      for (int j4 = 0; j4 < 8; ++j4) {
+        const double z = (bits >> (4 * j4)) & 1u ? -1.0 : 1.0;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[32 * w + 4 * j4], z, acc, 0, 0, 0);
       }
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      if (on[t]) cp[p0 + 64 * t] = acc[t];
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + 4 * u + g, q = q0 + l16;
+      if (c < s && q < a.r) cp[c * a.r + q] = acc[u];
+    }
   }
 }
 
@@ -415,19 +382,21 @@ template <template <int> class K>
 static hipError_t launch_qr_sp(const QrBatch& bt, hipStream_t st) {
   if (bt.s < 1 || bt.s > 32 || bt.r > 256 || bt.njobs < 1 || bt.njobs > kQrMaxJobs || bt.blocks < 1)
     return hipErrorInvalidValue;
-  const dim3 grid((unsigned)bt.blocks);
-  if (bt.s <= 8) DPRC_LAUNCH(K<8>::fn, grid, dim3(64), 0, st, bt);
-  else if (bt.s <= 16) DPRC_LAUNCH(K<16>::fn, grid, dim3(64), 0, st, bt);
-  else DPRC_LAUNCH(K<32>::fn, grid, dim3(64), 0, st, bt);
+  const dim3 grid((unsigned)bt.blocks), blk((unsigned)K<8>::threads);
+  if (bt.s <= 8) DPRC_LAUNCH(K<8>::fn, grid, blk, 0, st, bt);
+  else if (bt.s <= 16) DPRC_LAUNCH(K<16>::fn, grid, blk, 0, st, bt);
+  else DPRC_LAUNCH(K<32>::fn, grid, blk, 0, st, bt);
   return hipGetLastError();
 }
 template <int SP>
 struct QrFactorK {
   static constexpr auto fn = qr_factor_kernel<SP>;
+  static constexpr int threads = 64;
 };
 template <int SP>
 struct QrExpandK {
   static constexpr auto fn = qr_expand_kernel<SP>;
+  static constexpr int threads = 256;
 };
 
 hipError_t launch_qr_factor(const QrBatch& bt, hipStream_t st) { return launch_qr_sp<QrFactorK>(bt, st); }
