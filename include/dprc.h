@@ -107,10 +107,12 @@ typedef struct {
  * Workspace: dprc_norm_hutch_workspace() bytes for the same arguments (0 when
  * they are invalid).  When every layer is bf16, up to 32 groups of layers
  * keep their own token-split partials in it at once (their split sums take one
- * launch), and with RADEMACHER or HADAMARD probes also their own projected Y
- * (B x T rounded up to 64, x 2 x the group's columns rounded up to 16, bf16),
- * so their projections and token reductions are batched too; it grows with the
- * number of layers up to that many groups.  Every group's tile sums (B x
+ * launch) and their own projected Y (B x T rounded up to 64, x 2 x the group's
+ * columns rounded up to 16, bf16; with GAUSSIAN probes also every layer's probe
+ * columns), so their projections and token reductions are batched too; it grows
+ * with the number of layers up to that many groups.  GAUSSIAN calls also run, with
+ * the same results, in a workspace that holds these only once (a probe buffer and a
+ * Y shared by the groups), with launches per group.  Every group's tile sums (B x
  * ceil(reduced width / 128) doubles per layer) stay in it until the per-sample
  * sums of all layers at the end of the call. */
 size_t dprc_norm_hutch_workspace(const dprc_layer* layers, int32_t num_layers, int32_t k,
@@ -136,7 +138,8 @@ dprc_status dprc_norm_hutch_clip(const dprc_layer* layers, int32_t num_layers, i
  * object holds on every device it runs on until the process ends; the call allocates
  * nothing and frees nothing.  A call whose dprc_norm_hutch_workspace() exceeds that
  * size returns DPRC_ERROR_SCRATCH_LIMIT and enqueues nothing (the 113-layer
- * Llama-3.2-1B stack at B = 8, T = 4096, k = 32 needs 136 MiB).  `stream` must belong
+ * Llama-3.2-1B stack at B = 8, T = 4096, k = 32 needs 136 MiB; GAUSSIAN calls that
+ * exceed it run with launches per group as long as those fit).  `stream` must belong
  * to the current device (else DPRC_ERROR_INVALID_VALUE); the first call on a device
  * looks up that device's copy of the array (hipGetSymbolAddress) and keeps its
  * address for the process, so make that first call outside graph capture.  Every

@@ -100,6 +100,7 @@ int pad_cols(int ncols) {
   return -1;
 }
 
+// rows: the token rows of every projection of the launch.
 int rows_per_wg(int64_t rows, int ncols_pad, bool dense = false) {
   const int nb = ncols_pad / 16;
   // 32-row workgroups while that still gives 256 or more of them (fixed per-workgroup
@@ -145,6 +146,7 @@ struct TokBufs {
   float* part;
   double* tilesq;
   uint16_t* Y = nullptr;     // a group's own Y (batched launches)
+  uint16_t* Z = nullptr;     // and its layers' Gaussian probe columns, hi then lo, layer by layer
 };
 
 TokBufs take_tok(Arena& ar, int64_t B, const TokPlan& tp, int ncols_pad, int nseg = 1) {
@@ -408,7 +410,7 @@ dprc_status hutch_f32(const View& v, int32_t k, int probe, uint32_t k0, uint32_t
 dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0, uint32_t k1, float* n2,
                         float* n2_layers, int accumulate, void* ws, hipStream_t st, float clipC = 0.f,
                         float* clip_c = nullptr, TokredArgs* defer = nullptr, const TokBufs* own = nullptr,
-                        ProjectArgs* pjobs = nullptr, int* npj = nullptr) {
+                        ProjectArgs* pjobs = nullptr, int* npj = nullptr, GaussBatch* gjobs = nullptr) {
   if (v[0].dtype != DPRC_BF16)
     return hutch_f32(v[0], k, probe, k0, k1, n2, n2_layers, accumulate, clipC, clip_c, ws, st);
   const bool gauss = probe == DPRC_PROBE_GAUSSIAN;
@@ -425,10 +427,16 @@ dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0,
   if (own && own->Y) Yt = own->Y;
   const int64_t yt_ld = B * tp.T_pad;
   hipError_t e = hipSuccess;
+  uint16_t* zown = own ? own->Z : nullptr;
   for (int l = 0; l < G; ++l) {
     const View& w = v[l];
     const int64_t ldz = round_up(w.m, kTile);
-    if (gauss && (e = traced(DPRC_KERNEL_PROBE_GAUSS, st, [&] {
+    if (gauss && zown) {                           // collected: one launch draws every layer's probes
+      gz.hi = zown;
+      gz.lo = zown + (int64_t)k * ldz;
+      zown += 2 * (int64_t)k * ldz;
+      gjobs->job[gjobs->njobs++] = GaussJob{w.layer_id, (int32_t)w.m, (int32_t)ldz, gz.hi, gz.lo};
+    } else if (gauss && (e = traced(DPRC_KERNEL_PROBE_GAUSS, st, [&] {
                     return launch_gauss_probe(k0, k1, w.layer_id, w.m, k, ldz, gz.hi, gz.lo, nullptr, st); })) != hipSuccess)
       return DPRC_ERROR_HIP;
     ProjectArgs pa;
@@ -701,7 +709,7 @@ dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int3
     const TokPlan tp = tok_plan(vs[q].B, vs[q].T, p.n);
     TokBufs own{tp.S > 1 ? bufs[q].part : nullptr, nullptr};
     pass_args(p, vs[q].B, vs[q].T, k0, k1, vs[q].layer_id, bufs[q].Y, own, tp, pas[q], def[q]);
-    rows = vs[q].B * tp.T_pad;
+    rows += vs[q].B * tp.T_pad;
   }
   // widest layers first, so that the narrow ones fill the tail of each launch
   int op[kProjMaxJobs], ot[kProjMaxJobs];
@@ -719,9 +727,11 @@ dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int3
     if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project_batch(pb, rpw, st); }) != hipSuccess)
       return DPRC_ERROR_HIP;
   } else {
-    for (int q = 0; q < ng; ++q)
-      if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project(pb.job[q], rpw, st); }) != hipSuccess)
+    for (int q = 0; q < ng; ++q) {
+      const int r1 = rows_per_wg((int64_t)pb.job[q].B * pb.job[q].T_pad, ncols_pad, p0.nd > 0);
+      if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project(pb.job[q], r1, st); }) != hipSuccess)
         return DPRC_ERROR_HIP;
+    }
   }
   return hip_status(traced(DPRC_KERNEL_TOKEN_REDUCE, st, [&] { return launch_tokred_batch(tb, st); }));
 }
@@ -912,8 +922,12 @@ dprc_status hutch_launch_batched(ProjectArgs* pj, int npj, const TokredBatch& gr
       return DPRC_ERROR_HIP;
   for (int c = 0; c < npj && pj[0].ncols_pad <= 64; c += kProjMaxJobs) {
     ProjectBatch pb{};
-    for (int q = c; q < std::min(npj, c + kProjMaxJobs); ++q) pb.job[pb.njobs++] = pj[q];
-    const int rpw = rows_per_wg((int64_t)pb.job[0].B * pb.job[0].T_pad, pb.job[0].ncols_pad, false);
+    int64_t rows = 0;
+    for (int q = c; q < std::min(npj, c + kProjMaxJobs); ++q) {
+      pb.job[pb.njobs++] = pj[q];
+      rows += (int64_t)pj[q].B * pj[q].T_pad;
+    }
+    const int rpw = rows_per_wg(rows, pb.job[0].ncols_pad, pb.job[0].nd > 0);
     if (traced(DPRC_KERNEL_PROJECT, st, [&] { return launch_project_batch(pb, rpw, st); }) != hipSuccess)
       return DPRC_ERROR_HIP;
   }
@@ -976,10 +990,11 @@ size_t hutch_tilesq_bytes(const dprc_layer* layers, int32_t n, int32_t k, dprc_s
 }
 
 // Up to kTokMaxJobs consecutive activation groups starting at layer l0: their bounds in
-// ends[], their own buffers (token-split partials and Y; the tile sums are the call's)
-// carved from ws (own may be null) after the shared scratch.  Returns the bytes used.
+// ends[], their own buffers (token-split partials and, with `batched` launches, Y and the
+// Gaussian probes; the tile sums are the call's) carved from ws (own may be null) after the
+// shared scratch.  Returns the bytes used.
 size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32_t k, int probe, dprc_side side,
-                          void* ws, int32_t* ends, int* ngroups, TokBufs* own) {
+                          bool batched, void* ws, int32_t* ends, int* ngroups, TokBufs* own) {
   View v[kMaxGroup];
   size_t shared = 0;
   int ng = 0;
@@ -997,7 +1012,7 @@ size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32
     const View v0 = view_of(layers[lq], side);
     pairs += v0.B * tok_plan(v0.B, v0.T, v0.n).ntiles;
   }
-  const bool unsplit = probe != DPRC_PROBE_GAUSSIAN && pairs >= kUnsplitPairs;
+  const bool unsplit = batched && pairs >= kUnsplitPairs;
   char* base = static_cast<char*>(ws);
   size_t off = (shared + kAlign - 1) / kAlign * kAlign;
   l = l0;
@@ -1008,11 +1023,16 @@ size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32
     const size_t pf = !unsplit && tp.S > 1 ? (size_t)v0.B * tp.ntiles * tp.S * pad_cols(G * k) * kTile : 0;
     if (own) own[q].part = base && pf ? reinterpret_cast<float*>(base + off) : nullptr;
     off = (off + pf * sizeof(float) + kAlign - 1) / kAlign * kAlign;
-    if (probe != DPRC_PROBE_GAUSSIAN) {          // its own Y: the groups' launches are batched
+    if (own) own[q].Y = own[q].Z = nullptr;
+    if (batched) {                               // its own Y: the groups' launches are batched
       if (own) own[q].Y = base ? reinterpret_cast<uint16_t*>(base + off) : nullptr;
       off = (off + (size_t)2 * pad_cols(G * k) * v0.B * tp.T_pad * sizeof(uint16_t) + kAlign - 1) / kAlign * kAlign;
-    } else if (own) {
-      own[q].Y = nullptr;
+      if (probe == DPRC_PROBE_GAUSSIAN) {        // and its layers' probe columns
+        if (own) own[q].Z = base ? reinterpret_cast<uint16_t*>(base + off) : nullptr;
+        for (int32_t j = l; j < ends[q]; ++j)
+          off += (size_t)2 * k * round_up(view_of(layers[j], side).m, kTile) * sizeof(uint16_t);
+        off = (off + kAlign - 1) / kAlign * kAlign;
+      }
     }
     l = ends[q];
   }
@@ -1020,11 +1040,10 @@ size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32
   return off;
 }
 
-size_t dprc_norm_hutch_workspace(const dprc_layer* layers, int32_t num_layers, int32_t k, dprc_probe probe,
-                                 dprc_side side) {
-  if (check_layers(layers, num_layers, side) != DPRC_SUCCESS || k < 1 || k > 256) return 0;
-  if (probe != DPRC_PROBE_RADEMACHER && probe != DPRC_PROBE_HADAMARD && probe != DPRC_PROBE_GAUSSIAN) return 0;
-  if (probe == DPRC_PROBE_GAUSSIAN && k > kMaxGaussK) return 0;
+// Workspace of a call whose groups' launches are `batched` (Gaussian probes also run without:
+// a probe buffer and a Y shared by the groups, launches per group).
+static size_t hutch_workspace(const dprc_layer* layers, int32_t num_layers, int32_t k, dprc_probe probe,
+                              dprc_side side, bool batched) {
   size_t need = 0;
   View v[kMaxGroup];
   for (int32_t l = 0; l < num_layers;) {
@@ -1037,12 +1056,20 @@ size_t dprc_norm_hutch_workspace(const dprc_layer* layers, int32_t num_layers, i
     int32_t ends[kTokMaxJobs];
     int ng = 0;
     for (int32_t l = 0; l < num_layers;) {
-      need = std::max(need, hutch_batch_layout(layers, l, num_layers, k, (int)probe, side, nullptr, ends, &ng, nullptr));
+      need = std::max(need, hutch_batch_layout(layers, l, num_layers, k, (int)probe, side, batched, nullptr, ends, &ng, nullptr));
       l = ends[ng - 1];
     }
     need += hutch_tilesq_bytes(layers, num_layers, k, side);   // the call's tile sums come first
   }
   return need;
+}
+
+size_t dprc_norm_hutch_workspace(const dprc_layer* layers, int32_t num_layers, int32_t k, dprc_probe probe,
+                                 dprc_side side) {
+  if (check_layers(layers, num_layers, side) != DPRC_SUCCESS || k < 1 || k > 256) return 0;
+  if (probe != DPRC_PROBE_RADEMACHER && probe != DPRC_PROBE_HADAMARD && probe != DPRC_PROBE_GAUSSIAN) return 0;
+  if (probe == DPRC_PROBE_GAUSSIAN && k > kMaxGaussK) return 0;
+  return hutch_workspace(layers, num_layers, k, probe, side, true);
 }
 
 static dprc_status norm_hutch(const dprc_layer* layers, int32_t num_layers, int32_t k, dprc_probe probe,
@@ -1054,8 +1081,9 @@ static dprc_status norm_hutch(const dprc_layer* layers, int32_t num_layers, int3
   if (probe != DPRC_PROBE_RADEMACHER && probe != DPRC_PROBE_HADAMARD && probe != DPRC_PROBE_GAUSSIAN)
     return DPRC_ERROR_INVALID_VALUE;
   if (probe == DPRC_PROBE_GAUSSIAN && k > kMaxGaussK) return DPRC_ERROR_NOT_SUPPORTED;
-  const size_t need = dprc_norm_hutch_workspace(layers, num_layers, k, probe, side);
-  if (ws_bytes < need) return DPRC_ERROR_WORKSPACE_TOO_SMALL;
+  // Gaussian calls with too little workspace for batched launches run without them
+  const bool own_launches = probe != DPRC_PROBE_GAUSSIAN || ws_bytes >= hutch_workspace(layers, num_layers, k, probe, side, true);
+  if (ws_bytes < hutch_workspace(layers, num_layers, k, probe, side, own_launches)) return DPRC_ERROR_WORKSPACE_TOO_SMALL;
   if (!ws || !aligned(ws, kAlign)) return DPRC_ERROR_INVALID_VALUE;
   uint32_t k0, k1;
   key_of(seed, k0, k1);
@@ -1085,7 +1113,7 @@ static dprc_status norm_hutch(const dprc_layer* layers, int32_t num_layers, int3
       int32_t ends[kTokMaxJobs];
       int ng = 0;
       TokBufs own[kTokMaxJobs];
-      hutch_batch_layout(layers, l, num_layers, k, (int)probe, side, ws, ends, &ng, own);
+      hutch_batch_layout(layers, l, num_layers, k, (int)probe, side, own_launches, ws, ends, &ng, own);
       for (int q = 0, lq = l; q < ng; lq = ends[q++]) {
         own[q].tilesq = reinterpret_cast<double*>(tq);
         tq += group_tilesq_bytes(layers, lq, ends[q], side);
@@ -1094,18 +1122,23 @@ static dprc_status norm_hutch(const dprc_layer* layers, int32_t num_layers, int3
       const bool batched = own[0].Y != nullptr;
       ProjectArgs pj[kTokMaxJobs * kMaxGroup];
       int npj = 0;
+      GaussBatch gb{};
+      gb.k = k; gb.key0 = k0; gb.key1 = k1;
       for (int q = 0; q < ng; ++q) {
         const int32_t le = ends[q];
         for (int32_t j = l; j < le; ++j) v[j - l] = view_of(layers[j], side);
         TokredArgs ta{};
         s = hutch_group(v, le - l, k, (int)probe, k0, k1, n2, n2_layers ? n2_layers + (int64_t)l * B : nullptr,
                         (accumulate || l > 0) ? 1 : 0, ws, stream, 0.f, nullptr, &ta, &own[q],
-                        batched ? pj : nullptr, batched ? &npj : nullptr);
+                        batched ? pj : nullptr, batched ? &npj : nullptr, &gb);
         if (s != DPRC_SUCCESS) return s;
         bt.blk0[bt.njobs] = bt.blocks;
         bt.job[bt.njobs++] = ta;
         l = le;
       }
+      if (gb.njobs > 0 &&
+          traced(DPRC_KERNEL_PROBE_GAUSS, stream, [&] { return launch_gauss_batch(gb, stream); }) != hipSuccess)
+        return DPRC_ERROR_HIP;
       if (batched) unsplit_large_batch(bt);       // (unbatched groups launched theirs already)
       if (batched && (s = hutch_launch_batched(pj, npj, bt, stream)) != DPRC_SUCCESS) return s;
       if ((s = run_splits_batch(bt.job, bt.njobs, stream)) != DPRC_SUCCESS) return s;
@@ -1150,7 +1183,8 @@ dprc_status dprc_norm_hutch_clip_static(const dprc_layer* layers, int32_t num_la
   if (!c || !(C > 0.f) || std::isinf(C)) return DPRC_ERROR_INVALID_VALUE;
   dprc_status s = check_layers(layers, num_layers, side);
   if (s != DPRC_SUCCESS) return s;
-  const size_t need = dprc_norm_hutch_workspace(layers, num_layers, k, probe, side);
+  size_t need = dprc_norm_hutch_workspace(layers, num_layers, k, probe, side);      // 0: invalid, refused below
+  if (need && probe == DPRC_PROBE_GAUSSIAN) need = hutch_workspace(layers, num_layers, k, probe, side, false);
   if (need > (size_t)DPRC_STATIC_SCRATCH_BYTES) return DPRC_ERROR_SCRATCH_LIMIT;
   void* ws = nullptr;
   if ((s = static_scratch(stream, &ws)) != DPRC_SUCCESS) return s;

@@ -350,6 +350,21 @@ hipError_t launch_private_adamw(const AdamArgs& a, hipStream_t st);
 // any of hi/lo (both or neither) and f32 may be null.
 hipError_t launch_gauss_probe(uint32_t key0, uint32_t key1, uint32_t layer, int64_t m, int32_t k, int64_t ld,
                               uint16_t* hi, uint16_t* lo, float* f32, hipStream_t st);
+// The hi/lo probe columns of several layers of one call in one launch.
+struct GaussJob {
+  uint32_t layer;
+  int32_t m, ld;
+  uint16_t* hi;
+  uint16_t* lo;
+};
+constexpr int kGaussMaxJobs = kTokMaxJobs * kMaxGroup;   // 4.6 KB of kernel arguments
+struct GaussBatch {
+  int32_t njobs, k;
+  uint32_t key0, key1;
+  int32_t blk0[kGaussMaxJobs];   // set by the launcher
+  GaussJob job[kGaussMaxJobs];
+};
+hipError_t launch_gauss_batch(GaussBatch bt, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_project(const ProjectArgs& a, int rows_per_wg, hipStream_t st);
 hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st);   // <= 64 columns

@@ -114,6 +114,31 @@ def test_hutch_gaussian_parity(D, B, T, d, p, k, side, dtype):
     assert np.all(_rel(n2.cpu().numpy(), ref) < NORM_RTOL)
 
 
+@pytest.mark.parametrize("n", [5, 37])
+def test_hutch_gaussian_batched_launches(D, n):
+    # Gaussian layers in one call: one probe launch, batched projections and reductions (37
+    # layers: two batches), against calls of one layer bit for bit; and in a workspace
+    # that only holds the unbatched form, with the same results
+    B, T, k = 2, 130, 20
+    pairs = [_draw(B, T, 40 + 8 * (j % 3), 56 + 100 * (j % 4), layer=600 + j) + (j,) for j in range(n)]
+    need = D.dprc_norm_hutch_workspace(pairs, k, probe=D.PROBE_GAUSSIAN)
+    per = torch.zeros(n, B, device="cuda")
+    n2, c = D.dprc_norm_hutch_clip(pairs, k, 5, 0.5, probe=D.PROBE_GAUSSIAN, n2_layers=per)
+    solo = torch.stack([D.dprc_norm_hutch([q], k, 5, probe=D.PROBE_GAUSSIAN) for q in pairs])
+    assert torch.equal(per, solo)
+    for j in (0, n - 1):
+        A, E, _ = pairs[j]
+        assert np.all(_rel(per[j].cpu().numpy(), est.hutch_layer(_np(A), _np(E), k, 5, j, probe="gaussian")) < NORM_RTOL)
+    arr, nl, _, dev = D._layers(pairs)
+    small = need - 2 * k * 128 * 2               # one layer's probe columns short of batched launches
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    m2, mc, mper = torch.zeros_like(n2), torch.zeros_like(c), torch.zeros_like(per)
+    status = D.lib().dprc_norm_hutch_clip(arr, nl, k, D.PROBE_GAUSSIAN, 5, 0, 0.5, m2.data_ptr(), mc.data_ptr(),
+                                          mper.data_ptr(), 0, ws.data_ptr(), small, D._stream(dev))
+    assert status == D.SUCCESS
+    assert torch.equal(m2, n2) and torch.equal(mc, c) and torch.equal(mper, per)
+
+
 def test_hutch_gaussian_multilayer_accumulate(D):
     # per-layer probes differ (layer id in the counter); the workspace is reused across layers
     A1, E1 = _draw(2, 300, 256, 200, layer=0)
