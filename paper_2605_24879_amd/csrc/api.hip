@@ -277,6 +277,31 @@ int64_t part_floats(int64_t B, int64_t T, int64_t n, int ncols) {
   return tp.S > 1 ? B * tp.ntiles * tp.S * pad_cols(ncols) * kTile : 0;
 }
 
+// Each job of a batched token reduction comes with token splits that give it about 256
+// workgroups of its own.  The jobs of one launch share the GPU, so a batch needs fewer: none
+// at all from kUnsplitPairs (sample, 128-column tile) pairs on (unsplit workgroups write
+// their tile sums directly; halves the start-up and finish costs of two-way splits), and, as
+// soon as the pairs give every CU one, none of fewer than 16 stages (1024 tokens): Hutch++ on
+// an attention block at B = 4, T = 1024 took 259 us with four splits of 4 stages and five
+// split-sum launches, 240 us without.  Longer splits stay: at T = 4096 and 32768 dropping
+// them was 3 to 5% slower, and with 128 pairs two splits instead of four were 5% slower.
+constexpr int64_t kUnsplitPairs = 1024;
+constexpr int64_t kMinSplitStages = 16;
+void limit_splits(TokredArgs* job, int n) {
+  int64_t pairs = 0;
+  for (int q = 0; q < n; ++q) pairs += (int64_t)job[q].B * job[q].ntiles;
+  if (pairs < 256) return;
+  for (int q = 0; q < n; ++q) {
+    TokredArgs& a = job[q];
+    const int64_t stages = ceil_div(a.T_pad, kStage);
+    const int64_t most = pairs >= kUnsplitPairs ? 1 : std::max<int64_t>(1, stages / kMinSplitStages);
+    if (a.S <= most) continue;
+    a.stages_per_split = (int32_t)ceil_div(stages, most);
+    a.S = (int32_t)ceil_div(stages, a.stages_per_split);
+    if (a.S == 1) a.part = nullptr;
+  }
+}
+
 // Split sums of deferred passes (those with token splits), up to kTokMaxJobs per launch.
 dprc_status run_splits_batch(const TokredArgs* ta, int n, hipStream_t st) {
   TokredBatch bt{};
@@ -711,6 +736,7 @@ dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int3
     pass_args(p, vs[q].B, vs[q].T, k0, k1, vs[q].layer_id, bufs[q].Y, own, tp, pas[q], def[q]);
     rows += vs[q].B * tp.T_pad;
   }
+  limit_splits(def, ng);
   // widest layers first, so that the narrow ones fill the tail of each launch
   int op[kProjMaxJobs], ot[kProjMaxJobs];
   for (int q = 0; q < ng; ++q) op[q] = ot[q] = q;
@@ -951,25 +977,6 @@ dprc_status hutch_launch_batched(ProjectArgs* pj, int npj, const TokredBatch& gr
   return DPRC_SUCCESS;
 }
 
-// A batch whose token reductions have at least kUnsplitPairs (sample, tile) pairs fills the
-// GPU without token splits: every job then runs unsplit (one workgroup per pair over all
-// tokens, writing its tile sum directly), which halves the per-workgroup start and finish
-// costs of two-way splits and drops the split-sum launch.  The batch layout reserves no
-// split partials for such a batch.
-constexpr int64_t kUnsplitPairs = 1024;
-void unsplit_large_batch(TokredBatch& bt) {
-  int64_t pairs = 0;
-  for (int q = 0; q < bt.njobs; ++q) pairs += (int64_t)bt.job[q].B * bt.job[q].ntiles;
-  if (pairs < kUnsplitPairs) return;
-  for (int q = 0; q < bt.njobs; ++q) {
-    TokredArgs& a = bt.job[q];
-    if (a.mode != 0) continue;
-    a.stages_per_split = a.S * a.stages_per_split;
-    a.S = 1;
-    a.part = nullptr;
-  }
-}
-
 // The tile sums of an activation group (layers l .. le - 1) of a batched call,
 // [nseg][B][ntiles] doubles, kept until the per-sample sums at the end of the call: the
 // bytes of its slice, and of all groups' slices in order.
@@ -1006,7 +1013,7 @@ size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32
     ends[ng++] = le;
     l = le;
   }
-  // a batch whose launches are batched and unsplit (unsplit_large_batch) needs no partials
+  // a batch whose launches are batched and unsplit (limit_splits) needs no partials
   int64_t pairs = 0;
   for (int q = 0, lq = l0; q < ng; lq = ends[q++]) {
     const View v0 = view_of(layers[lq], side);
@@ -1139,7 +1146,7 @@ static dprc_status norm_hutch(const dprc_layer* layers, int32_t num_layers, int3
       if (gb.njobs > 0 &&
           traced(DPRC_KERNEL_PROBE_GAUSS, stream, [&] { return launch_gauss_batch(gb, stream); }) != hipSuccess)
         return DPRC_ERROR_HIP;
-      if (batched) unsplit_large_batch(bt);       // (unbatched groups launched theirs already)
+      if (batched) limit_splits(bt.job, bt.njobs);   // (unbatched groups launched theirs already)
       if (batched && (s = hutch_launch_batched(pj, npj, bt, stream)) != DPRC_SUCCESS) return s;
       if ((s = run_splits_batch(bt.job, bt.njobs, stream)) != DPRC_SUCCESS) return s;
       for (int q = 0; q < bt.njobs; ++q) {
