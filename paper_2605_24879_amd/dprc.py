@@ -145,6 +145,11 @@ def _workspace(nbytes, dev, ws):
     return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=dev)
 
 
+def _new_n2(B, dev, accumulate):
+    """Estimates to start from: zeros to add to, else left to the call, which writes all of them."""
+    return (torch.zeros if accumulate else torch.empty)(B, dtype=torch.float32, device=dev)
+
+
 def dprc_norm_hutch_workspace(pairs, k, side=SIDE_OUT, probe=PROBE_RADEMACHER):
     arr, nl, _, _ = _layers(pairs)
     return lib().dprc_norm_hutch_workspace(arr, nl, k, probe, side)
@@ -155,7 +160,7 @@ def dprc_norm_hutch(pairs, k, seed, side=SIDE_OUT, probe=PROBE_RADEMACHER, n2=No
     """Hutchinson estimates summed over layers: returns n2 [B] (fp32).  pairs = [(A, E, layer_id), ...]."""
     arr, nl, B, dev = _layers(pairs)
     if n2 is None:
-        n2 = torch.zeros(B, dtype=torch.float32, device=dev)
+        n2 = _new_n2(B, dev, accumulate)
     need = lib().dprc_norm_hutch_workspace(arr, nl, k, probe, side)
     ws = _workspace(need, dev, ws)
     _check(lib().dprc_norm_hutch(arr, nl, k, probe, seed, side, n2.data_ptr(),
@@ -169,7 +174,7 @@ def dprc_norm_hutch_clip(pairs, k, seed, C, side=SIDE_OUT, probe=PROBE_RADEMACHE
     """Hutchinson estimates and their clip factors in one call: returns (n2 [B], c [B])."""
     arr, nl, B, dev = _layers(pairs)
     if n2 is None:
-        n2 = torch.zeros(B, dtype=torch.float32, device=dev)
+        n2 = _new_n2(B, dev, accumulate)
     if c is None:
         c = torch.empty(B, dtype=torch.float32, device=dev)
     need = lib().dprc_norm_hutch_workspace(arr, nl, k, probe, side)
@@ -192,7 +197,7 @@ def dprc_norm_hutch_clip_static(pairs, k, seed, C, side=SIDE_OUT, probe=PROBE_RA
     nothing."""
     arr, nl, B, dev = _layers(pairs)
     if n2 is None:
-        n2 = torch.zeros(B, dtype=torch.float32, device=dev)
+        n2 = _new_n2(B, dev, accumulate)
     if c is None:
         c = torch.empty(B, dtype=torch.float32, device=dev)
     _check(lib().dprc_norm_hutch_clip_static(arr, nl, k, probe, seed, side, C, n2.data_ptr(), c.data_ptr(),
@@ -205,7 +210,7 @@ def dprc_norm_hutchpp(pairs, s, r, seed, side=SIDE_OUT, n2=None, n2_layers=None,
     """Hutch++ estimates summed over layers: returns n2 [B] (fp32)."""
     arr, nl, B, dev = _layers(pairs)
     if n2 is None:
-        n2 = torch.zeros(B, dtype=torch.float32, device=dev)
+        n2 = _new_n2(B, dev, accumulate)
     need = lib().dprc_norm_hutchpp_workspace(arr, nl, s, r, side)
     ws = _workspace(need, dev, ws)
     _check(lib().dprc_norm_hutchpp(arr, nl, s, r, seed, side, n2.data_ptr(),
