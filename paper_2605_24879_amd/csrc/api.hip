@@ -818,6 +818,21 @@ dprc_status hpp_final(const View& v, int32_t s, int32_t r, const PPBufs& b, floa
 // ---- clipped accumulation ----------------------------------------------------------------------------
 GemmPlan gemm_plan(const dprc_layer& L) { return gemm_plan_v2(L.B, L.T, L.d, L.p); }
 
+// Every tile of one layer.  Unsplit layers whose last round of tiles (one per CU) is nearly
+// empty, or whose only round is, run that round as quarter tiles.
+dprc_status accumulate_tiles(const GemmArgs& a, hipStream_t st) {
+  const int64_t tiles = ceil_div(a.d, 256) * ceil_div(a.p, 256);
+  const int64_t last = a.S == 1 ? tiles % kGemmRoundTiles : 0;
+  const int64_t quarters = last <= kGemmQuarterTiles ? last : 0;
+  if (tiles > quarters &&
+      traced(DPRC_KERNEL_ACCUMULATE, st, [&] { return launch_gemm(a, tiles - quarters, st); }) != hipSuccess)
+    return DPRC_ERROR_HIP;
+  if (quarters > 0 &&
+      traced(DPRC_KERNEL_ACCUMULATE, st, [&] { return launch_gemm_quarters(a, tiles - quarters, quarters, st); }) != hipSuccess)
+    return DPRC_ERROR_HIP;
+  return DPRC_SUCCESS;
+}
+
 // n-point Gauss-Legendre nodes and weights on [-1, 1]: Newton iteration on the
 // roots of P_n, started from the Chebyshev-like guesses cos(pi (q + 3/4) / (n + 1/2)),
 // with P_n and P_n' from the three-term recurrence; w = 2 / ((1 - x^2) P_n'(x)^2).
@@ -1351,8 +1366,7 @@ dprc_status dprc_clip_accumulate(const dprc_layer* L, const float* c, float* gra
   a.part = (float*)ws;
   a.vec_a = rows16(L->A, L->lda);
   a.vec_e = rows16(L->E, L->lde);
-  hipError_t e = traced(DPRC_KERNEL_ACCUMULATE, stream, [&] { return launch_gemm(a, stream); });
-  if (e != hipSuccess) return DPRC_ERROR_HIP;
+  if ((s = accumulate_tiles(a, stream)) != DPRC_SUCCESS) return s;
   if (g.S > 1) return hip_status(traced(DPRC_KERNEL_SPLITK_REDUCE, stream, [&] { return launch_splitk_reduce(a.part, g.S, a.d, a.p, grad, ldg, accumulate, stream); }));
   return DPRC_SUCCESS;
 }
@@ -1397,8 +1411,8 @@ dprc_status dprc_clip_accumulate_layers(const dprc_layer* layers, int32_t num_la
   for (int32_t l = 0; l < num_layers; ++l) {
     const GemmArgs a = args_of(l);
     if (ceil_div(a.d, 256) * ceil_div(a.p, 256) >= kGemmRoundTiles) {
-      if (traced(DPRC_KERNEL_ACCUMULATE, stream, [&] { return launch_gemm(a, stream); }) != hipSuccess)
-        return DPRC_ERROR_HIP;
+      const dprc_status s = accumulate_tiles(a, stream);
+      if (s != DPRC_SUCCESS) return s;
       continue;
     }
     bt.job[bt.njobs++] = a;

@@ -28,32 +28,36 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 
 constexpr int kGM = 256;            // tile rows (d) and columns (p)
 constexpr int kGK = 32;             // tokens per slab (64-token slabs measured 5 to 15 percent slower)
-constexpr int kGLd = kGM + 32;      // LDS row: 576 bytes; the 4 rows x 2 column groups of a 32-lane transpose read hit distinct 32-byte bank groups
 
 __device__ __forceinline__ f32x16_t mfma32x32x16(const uint4& a, const uint4& b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                   c, 0, 0, 0);
 }
 
-// NW = 8: waves of 128 x 64 (2 x 4 of them); NW = 4: waves of 128 x 128 (2 x 2).
 template <int V>
 struct GInt {
   static constexpr int value = V;
 };
 
-// wg: the tile (before the XCD reordering), split: the token split.
-template <int NW, int NS, int LD>
-__device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) {
+// GM = 256: the 256 x 256 tile `wg` (before the XCD reordering), eight waves of 128 x 64.
+// GM = 128: quarter `sub` of that tile, four waves of 64 x 64; three such workgroups share a
+// CU.  A quarter's entries are summed in the same order as the whole tile's.  split: the
+// token split.
+template <int GM, int NS, int LD>
+__device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split, int sub = 0) {
+  constexpr int NW = GM == 256 ? 8 : 4;
   constexpr int kThreads = 64 * NW;
-  constexpr int WN = NW == 8 ? 64 : 128;             // wave tile columns
+  constexpr int WN = 64, XB = GM == 256 ? 4 : 2;     // wave tile: 32 XB rows, 64 columns
   constexpr int YB = WN / 32;                        // 32-column MFMA blocks per wave
-  constexpr int RP = kThreads / 32;                  // slab rows per load pass
+  constexpr int TPR = GM / 8;                        // threads per token row of a slab
+  constexpr int RP = kThreads / TPR;                 // slab rows per load pass
   constexpr int RQ = kGK / RP;                       // load passes per slab
+  constexpr int kGLd = GM + 32;                      // LDS row: 576 (320) bytes; the 4 rows x 2 column groups of a 32-lane transpose read hit distinct 32-byte bank groups
   __shared__ __attribute__((aligned(16))) uint16_t la[2][kGK * kGLd];
   __shared__ __attribute__((aligned(16))) uint16_t le[2][kGK * kGLd];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int g = lane >> 4, r4 = (lane & 15) >> 2, c4 = lane & 3;
-  const int wm = wv / (kGM / WN), wn = wv % (kGM / WN);   // wave tile rows wm*128, columns wn*WN
+  const int wm = wv / (GM / WN), wn = wv % (GM / WN);     // wave tile rows 32 XB wm, columns 64 wn
 
   // tile of this workgroup: consecutive ids of one XCD walk the smaller dimension first
   const int tm_n = (a.d + kGM - 1) / kGM, tn_n = (a.p + kGM - 1) / kGM;
@@ -62,12 +66,13 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
   const int lin = (ntiles & 7) == 0 ? (wg & 7) * (ntiles >> 3) + (wg >> 3) : wg;
   int tm, tn;
   if (a.d <= a.p) { tm = lin % tm_n; tn = lin / tm_n; } else { tn = lin % tn_n; tm = lin / tn_n; }
-  const int d0 = tm * kGM, p0 = tn * kGM;
+  const int d0 = tm * kGM + (GM < kGM ? GM * (sub & 1) : 0), p0 = tn * kGM + (GM < kGM ? GM * (sub >> 1) : 0);
+  if (GM < kGM && (d0 >= a.d || p0 >= a.p)) return;   // (the whole workgroup)
 
   const int sps = a.stages_per_sample;
   const int gs_begin = split * a.stages_per_split;
   const int gs_end = min(a.B * sps, gs_begin + a.stages_per_split);
-  const int lr = tid >> 5, lc = (tid & 31) * 8;             // loads: rows lr + RP q, 8 columns at lc
+  const int lr = tid / TPR, lc = (tid % TPR) * 8;          // loads: rows lr + RP q, 8 columns at lc
   const int64_t ja = (int64_t)d0 + lc, je = (int64_t)p0 + lc;
 
   uint4 ga[NS][RQ], ge[NS][RQ];                   // slabs in flight
@@ -118,7 +123,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
   auto swrite = [&](int sl, int buf, int i, int st, int st_end) __attribute__((always_inline)) {
     const int tok0 = st * kGK;
     const int rows = st < st_end ? min(kGK, a.T - tok0) : 0;
-    if (LD == kLoadAny && (rows < kGK || d0 + kGM > a.d || p0 + kGM > a.p)) {
+    if (LD == kLoadAny && (rows < kGK || d0 + GM > a.d || p0 + GM > a.p)) {
       const int64_t t0 = rows > 0 ? tok0 : 0;
       const int aroom = operand_room(a.A, a.B, a.T, a.lda, a.d, a.A + (int64_t)i * a.a_ss + t0 * a.lda + d0);
       const int eroom = operand_room(a.E, a.B, a.T, a.lde, a.p, a.E + (int64_t)i * a.e_ss + t0 * a.lde + p0);
@@ -140,9 +145,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     }
   };
 
-  f32x16_t acc[4][YB];
+  f32x16_t acc[XB][YB];
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
     for (int y = 0; y < YB; ++y)
 #pragma unroll
@@ -155,11 +160,11 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
   // other LDS buffer, then (after the step's one barrier) multiplies half 1 while
   // reading half 0 of the next slab, so a wave always has MFMAs whose operands are
   // already in registers.
-  uint4 f0a[4], f0b[YB], f1a[4], f1b[YB];
-  auto frag = [&](uint4 (&av)[4], uint4 (&bv)[YB], int buf, int ks) __attribute__((always_inline)) {
+  uint4 f0a[XB], f0b[YB], f1a[XB], f1b[YB];
+  auto frag = [&](uint4 (&av)[XB], uint4 (&bv)[YB], int buf, int ks) __attribute__((always_inline)) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const uint16_t* pa = &la[buf][(16 * ks + tr_row) * kGLd + wm * 128 + 32 * x + tr_col];
+    for (int x = 0; x < XB; ++x) {
+      const uint16_t* pa = &la[buf][(16 * ks + tr_row) * kGLd + wm * 32 * XB + 32 * x + tr_col];
       av[x] = make_u4(lds_read_tr16(pa), lds_read_tr16(pa + 4 * kGLd));
     }
 #pragma unroll
@@ -168,9 +173,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
       bv[y] = make_u4(lds_read_tr16(pe), lds_read_tr16(pe + 4 * kGLd));
     }
   };
-  auto mm = [&](const uint4 (&av)[4], const uint4 (&bv)[YB]) __attribute__((always_inline)) {
+  auto mm = [&](const uint4 (&av)[XB], const uint4 (&bv)[YB]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < XB; ++x)
 #pragma unroll
       for (int y = 0; y < YB; ++y) acc[x][y] = mfma32x32x16(av[x], bv[y], acc[x][y]);
   };
@@ -187,7 +192,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     if (started) {
       const float ratio = cur_c / ci;
 #pragma unroll
-      for (int x = 0; x < 4; ++x)
+      for (int x = 0; x < XB; ++x)
 #pragma unroll
         for (int y = 0; y < YB; ++y) acc[x][y] *= ratio;
     }
@@ -265,14 +270,14 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     ld = a.p;
   }
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
     for (int y = 0; y < YB; ++y) {
       const int col = p0 + wn * WN + 32 * y + (lane & 31);
       if (col >= a.p) continue;
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const int row = d0 + wm * 128 + 32 * x + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
+        const int row = d0 + wm * 32 * XB + 32 * x + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
         if (row >= a.d) continue;
         const float v = acc[x][y][q] * cur_c;
         float* o = dst + (int64_t)row * ld + col;
@@ -282,24 +287,32 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split) 
     }
 }
 
-template <int NW, int NS, int LD>
-__global__ __launch_bounds__(64 * NW, 1) void gemm_kernel(GemmArgs a) {
-  gemm_body<NW, NS, LD>(a, blockIdx.x, blockIdx.y);
+template <int NS, int LD>
+__global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs a) {
+  gemm_body<kGM, NS, LD>(a, blockIdx.x, blockIdx.y);
+}
+
+// Quarters of the tiles from `first` on, four workgroups each.
+template <int NS, int LD>
+__global__ __launch_bounds__(256) void gemm_quarters_kernel(GemmArgs a, int first) {
+  gemm_body<kGM / 2, NS, LD>(a, first + (int)blockIdx.x / 4, 0, (int)blockIdx.x % 4);
 }
 
 // Several layers in one launch, each unsplit (S = 1): job j owns blocks blk0[j] ..
 // blk0[j] + ntiles_j - 1, and blk0[j] is a multiple of 8, so that a job's blocks are
 // dealt to the XCDs as those of a launch of its own; blocks up to the next multiple of
-// 8 are idle.
-template <int NW, int NS, int LD>
-__global__ __launch_bounds__(64 * NW, 1) void gemm_batch_kernel(GemmBatch bt) {
+// 8 are idle.  QUARTERS: four workgroups per block.
+template <int NS, int LD, bool QUARTERS>
+__global__ __launch_bounds__(QUARTERS ? 256 : 512, 1) void gemm_batch_kernel(GemmBatch bt) {
+  const int blk = QUARTERS ? (int)blockIdx.x / 4 : (int)blockIdx.x;
   int jb = 0;
 #pragma unroll 8
-  for (int q = 1; q < kGemmMaxJobs; ++q) jb += (q < bt.njobs && (int)blockIdx.x >= bt.blk0[q]) ? 1 : 0;
+  for (int q = 1; q < kGemmMaxJobs; ++q) jb += (q < bt.njobs && blk >= bt.blk0[q]) ? 1 : 0;
   const GemmArgs& a = bt.job[jb];
-  const int wg = (int)blockIdx.x - bt.blk0[jb];
+  const int wg = blk - bt.blk0[jb];
   if (wg >= (int)(((int64_t)a.d + kGM - 1) / kGM * (((int64_t)a.p + kGM - 1) / kGM))) return;
-  gemm_body<NW, NS, LD>(a, wg, 0);
+  if constexpr (QUARTERS) gemm_body<kGM / 2, NS, LD>(a, wg, 0, (int)blockIdx.x % 4);
+  else gemm_body<kGM, NS, LD>(a, wg, 0);
 }
 
 GemmPlan gemm_plan_v2(int64_t B, int64_t T, int64_t d, int64_t p) {
@@ -319,34 +332,55 @@ static int gemm_load(const GemmArgs& a) {        // offsets within one slab stay
   return std::min(load_mode(a.vec_a, a.B, a.T, a.d, a.lda, kGK), load_mode(a.vec_e, a.B, a.T, a.p, a.lde, kGK));
 }
 
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
-  const int tiles = (int)(ceil_div(a.d, kGM) * ceil_div(a.p, kGM));
-  dim3 grid((unsigned)tiles, (unsigned)a.S);
-  constexpr int NW = 8, NS = 2;
+#define DPRC_GEMM_LOADS(KERNEL, GRID, BLOCK, ...)                                                          \
+  if (load == kLoadVec) DPRC_LAUNCH((KERNEL(kLoadVec)), GRID, BLOCK, 0, st, __VA_ARGS__);                  \
+  else if (load == kLoadAny) DPRC_LAUNCH((KERNEL(kLoadAny)), GRID, BLOCK, 0, st, __VA_ARGS__);             \
+  else DPRC_LAUNCH((KERNEL(kLoadElem)), GRID, BLOCK, 0, st, __VA_ARGS__);
+
+hipError_t launch_gemm(const GemmArgs& a, int64_t ntiles, hipStream_t st) {
+  const dim3 grid((unsigned)ntiles, (unsigned)a.S);
   const int load = gemm_load(a);
-  if (load == kLoadVec) DPRC_LAUNCH((gemm_kernel<NW, NS, kLoadVec>), grid, dim3(64 * NW), 0, st, a);
-  else if (load == kLoadAny) DPRC_LAUNCH((gemm_kernel<NW, NS, kLoadAny>), grid, dim3(64 * NW), 0, st, a);
-  else DPRC_LAUNCH((gemm_kernel<NW, NS, kLoadElem>), grid, dim3(64 * NW), 0, st, a);
+#define DPRC_K(LD) gemm_kernel<2, LD>
+  DPRC_GEMM_LOADS(DPRC_K, grid, dim3(512), a)
+#undef DPRC_K
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_quarters(const GemmArgs& a, int64_t first, int64_t ntiles, hipStream_t st) {
+  if (a.S != 1 || ntiles < 1 || 4 * ntiles >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(4 * ntiles));
+  const int load = gemm_load(a);
+#define DPRC_K(LD) gemm_quarters_kernel<2, LD>
+  DPRC_GEMM_LOADS(DPRC_K, grid, dim3(256), a, (int)first)
+#undef DPRC_K
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_batch(GemmBatch bt, hipStream_t st) {
   if (bt.njobs < 1 || bt.njobs > kGemmMaxJobs) return hipErrorInvalidValue;
-  constexpr int NW = 8, NS = 2;
   int load = kLoadVec;
-  int64_t blocks = 0;
+  int64_t blocks = 0, tiles = 0;
   for (int j = 0; j < bt.njobs; ++j) {
     const GemmArgs& a = bt.job[j];
     if (a.S != 1) return hipErrorInvalidValue;
     load = std::min(load, gemm_load(a));
     bt.blk0[j] = (int32_t)blocks;
+    tiles += ceil_div(a.d, kGM) * ceil_div(a.p, kGM);
     blocks += round_up(ceil_div(a.d, kGM) * ceil_div(a.p, kGM), 8);
   }
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks);
-  if (load == kLoadVec) DPRC_LAUNCH((gemm_batch_kernel<NW, NS, kLoadVec>), grid, dim3(64 * NW), 0, st, bt);
-  else if (load == kLoadAny) DPRC_LAUNCH((gemm_batch_kernel<NW, NS, kLoadAny>), grid, dim3(64 * NW), 0, st, bt);
-  else DPRC_LAUNCH((gemm_batch_kernel<NW, NS, kLoadElem>), grid, dim3(64 * NW), 0, st, bt);
+  if (4 * blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  if (tiles <= kGemmQuarterTiles) {
+    const dim3 grid((unsigned)(4 * blocks));
+#define DPRC_K(LD) gemm_batch_kernel<2, LD, true>
+    DPRC_GEMM_LOADS(DPRC_K, grid, dim3(256), bt)
+#undef DPRC_K
+  } else {
+    const dim3 grid((unsigned)blocks);
+#define DPRC_K(LD) gemm_batch_kernel<2, LD, false>
+    DPRC_GEMM_LOADS(DPRC_K, grid, dim3(512), bt)
+#undef DPRC_K
+  }
+#undef DPRC_GEMM_LOADS
   return hipGetLastError();
 }
 

@@ -162,6 +162,11 @@ struct GemmArgs {
 // Unsplit accumulations of several layers in one launch (the launcher sets blk0).
 constexpr int kGemmMaxJobs = 64;     // 8.7 KB of kernel arguments
 constexpr int64_t kGemmRoundTiles = 256;   // 256 x 256 tiles that occupy every CU once
+// A last (or only) round of at most this many tiles runs as quarter tiles of 128 x 128, three
+// workgroups to a CU: 20 of the 788 tiles of an output head over 50257 columns took a round
+// of 175 us, the quarters' launch 130.  Above it whole tiles are as fast: a quarter moves
+// twice the LDS bytes per multiplication.
+constexpr int64_t kGemmQuarterTiles = 128;
 struct GemmBatch {
   int32_t njobs;
   int32_t blk0[kGemmMaxJobs];
@@ -387,7 +392,9 @@ hipError_t launch_hpp_csum_batch(const FinalBatch& bt, hipStream_t st);
 hipError_t launch_hpp_rows_batch(const FinalBatch& bt, hipStream_t st);
 hipError_t launch_hpp_sum_batch(const FinalBatch& bt, hipStream_t st);
 hipError_t launch_clip_scale(const float* n2, int64_t B, float C, float* c, hipStream_t st);
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t st);
+// the first ntiles tiles; quarters of ntiles tiles from `first` on
+hipError_t launch_gemm(const GemmArgs& a, int64_t ntiles, hipStream_t st);
+hipError_t launch_gemm_quarters(const GemmArgs& a, int64_t first, int64_t ntiles, hipStream_t st);
 hipError_t launch_gemm_batch(GemmBatch bt, hipStream_t st);
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t st);
 hipError_t launch_splitk_reduce(const float* part, int32_t S, int32_t d, int32_t p, float* out,

@@ -686,6 +686,21 @@ def test_clip_accumulate_layers_parity(D, aligned):
         assert torch.allclose(gacc, g + 0.5, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("d,p,pad", [
+    (1025, 13200, 0),     # 260 tiles: a round of 256 whole ones, then four as quarters
+    (1032, 13057, 1),     # the same with odd rows
+    (520, 300, 0),        # six tiles, all as quarters, some of them past the edges
+])
+def test_clip_accumulate_quarter_tiles(D, d, p, pad):
+    A, E = _draw(2, 70, d, p, layer=560, row_pad_a=pad, row_pad_e=pad)
+    c = torch.tensor([0.25, 1.0], device="cuda")
+    ref = est.clip_accumulate(_np(A), _np(E), c.cpu().numpy().astype(np.float64))
+    g, = D.dprc_clip_accumulate_layers([(A, E)], c)
+    assert np.linalg.norm(g.cpu().numpy() - ref) < 1e-5 * np.linalg.norm(ref)
+    g = D.dprc_clip_accumulate(A, E, c, grad=torch.full((d, p), 0.5, device="cuda"), accumulate=True)
+    assert np.linalg.norm(g.cpu().numpy() - ref - 0.5) < 1e-5 * np.linalg.norm(ref + 0.5)
+
+
 def test_clip_accumulate_layers_two_launches(D):
     # 70 layers (64 per launch), gradients with row strides wider than p
     B, pairs, grads = 2, [], []
