@@ -198,7 +198,7 @@ def test_middle_region_single_forms(mods, k, d, i, j, lam):
         assert best.item() > form(x, i, j, lam) - 1e-11  # and no other form exceeds it
 
 
-@pytest.mark.parametrize("n_half,n_bins", [(1, 0), (33, 1), (100, 65), (700, 513)])
+@pytest.mark.parametrize("n_half,n_bins", [(1, 0), (33, 1), (100, 65), (383, 513), (385, 4), (700, 513)])
 def test_pld_small_grids(mods, n_half, n_bins):
     # grids shorter than a workgroup, bins that do not fill a wave's table
     D, A = mods
