@@ -15,8 +15,10 @@
 // integral of the polynomial through the derivative's 16 values (the integration
 // matrix), so a candidate needs at most one incomplete gamma, at the start of
 // its range.  Panels are at most six standard deviations of the second term
-// wide.  Bound by fp64 logs and exponentials: 102816 forms (k = 32, d = 64) took 7.1 ms with
-// an incomplete gamma per node and take 0.43 ms here (0.61 with one lane per candidate).
+// wide.  Bound by fp64 logs and exponentials (short series about the densities' centres,
+// log_ratio and exp_neg): 102816 forms (k = 32, d = 64) took 7.1 ms with an incomplete gamma
+// per node and take 0.34 ms here (0.61 with one lane per candidate and 0.43 with the math
+// library's log and exp).
 // Against 200 panels of 32 nodes the errors are rounding, 1e-12 at most up to k d = 2048 and
 // 1e-11 at k = 64, d = 1024, where 16 panels without the width rule were off by 1e-5.  P_reg(a, y) is the power series for
 // y < a + 1 and Lentz's evaluation of the Legendre continued fraction for the
@@ -33,6 +35,46 @@ namespace dprc {
 constexpr int kEnvBlock = 256;
 constexpr int kEnvLanes = 4;       // lanes per candidate, so that a few thousand candidates still fill the GPU
 constexpr int kEnvRedBlock = 256;
+
+// log(x / c) for positive normal x and c, given inv = 1 / c: with the e that puts x / (2^e c)
+// in [sqrt(1/2), sqrt(2)), log(x / (2^e c)) = 2 atanh(s), s = (x - 2^e c) / (x + 2^e c) (the
+// difference is exact), by its series to s^23 (|s| <= 0.172: the next term is below 1e-18).
+__device__ __forceinline__ double log_ratio(double x, double c, double inv) {
+  const double q = x * inv;
+  int e = __builtin_amdgcn_frexp_exp(q);
+  e = __builtin_amdgcn_frexp_mant(q) < 0.70710678118654752440 ? e - 1 : e;
+  const double ce = __builtin_amdgcn_ldexp(c, e), f = x - ce, d = x + ce;
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  r = fma(fma(-d, r, 1.0), r, r);
+  double s = f * r;
+  s = fma(fma(-d, s, f), r, s);
+  const double z = s * s;
+  double p = 1.0 / 23.0;
+#pragma unroll
+  for (int k = 21; k >= 3; k -= 2) p = fma(p, z, 1.0 / k);
+  const double ed = (double)e, l = fma(2.0 * s, z * p, 2.0 * s);
+  return fma(ed, 0x1.62e42fefa39efp-1, fma(ed, 0x1.abc9e3b39803fp-56, l));   // ln 2 in two parts
+}
+
+// log Gamma(h) - [(h - 1/2) log h - h + log(2 pi) / 2], by Stirling's series for large h.
+__device__ __forceinline__ double stirling_rest(double h) {
+  if (h < 16.0) return lgamma(h) - ((h - 0.5) * log(h) - h + 0.91893853320467274178);
+  const double r = 1.0 / h, z = r * r;
+  return r * (1.0 / 12 - z * (1.0 / 360 - z * (1.0 / 1260 - z * (1.0 / 1680 - z * (1.0 / 1188)))));
+}
+
+// e^x for x below 700 (0 where it underflows): x = n ln 2 + r, |r| <= 0.347, Taylor to r^13.
+__device__ __forceinline__ double exp_neg(double x) {
+  const double n = rint(x * 1.4426950408889634074);
+  const double r = fma(-n, 0x1.abc9e3b39803fp-56, fma(-n, 0x1.62e42fefa39efp-1, x));
+  constexpr double c[14] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320,
+                            1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800.0};
+  double v = c[13];
+#pragma unroll
+  for (int k = 12; k >= 0; --k) v = fma(v, r, c[k]);
+  return __builtin_amdgcn_ldexp(v, (int)fmax(n, -4000.0));
+}
 
 __device__ double gamma_p(double a, double y) {
   if (y <= 0.0) return 0.0;
@@ -77,11 +119,15 @@ __device__ double two_level_cdf(double x, int i, int j, double lam, int k, int p
   const double reach = n1 >= 8.0 ? 7.5 : 10.0;
   const double lo = fmax(0.0, c - reach), hi = fmin(smax, c + reach);
   if (hi <= lo) return 0.0;
-  // logs of the constant factors of the chi density 2 s f_{n1}(s^2) = 2 s^(n1-1) e^(-s^2/2) /
-  // (2^(n1/2) Gamma(n1/2)) and of the gamma density y^(n2/2-1) e^-y / Gamma(n2/2)
-  const double al = n2 / 2.0, inv2b = 1.0 / (2.0 * b);
-  const double lc = log(2.0) - (n1 / 2.0) * log(2.0) - lgamma(n1 / 2.0);
-  const double lg = log(2.0 * a * inv2b) - lgamma(al);      // with |dy/ds| = s 2a / (2b)
+  // The chi density 2 s f_{n1}(s^2) and the gamma density of n2/2 relative to their centres
+  // c = sqrt(n1) and al = n2/2, where Stirling's formula leaves small constants:
+  //   log chi   = (n1 - 1) log(s / c) - (s^2 - n1) / 2 - log(pi) / 2 - rest(n1 / 2),
+  //   log gamma = (al - 1) log(y / al) - (y - al) - log(2 pi al) / 2 - rest(al)
+  // (summing terms of the size of n log n instead would round at 1e-16 of that).
+  const double al = n2 / 2.0, inv2b = 1.0 / (2.0 * b), invc = 1.0 / c, inval = 1.0 / al;
+  const double lc = -0.57236494292470008707 - stirling_rest(n1 / 2.0);
+  const double lg = -0.5 * log(6.28318530717958647693 * al) - stirling_rest(al);
+  const double ab = 2.0 * a * inv2b;                         // |dy/ds| = s 2a / (2b)
   // When the range runs to the end of the support (s = sqrt(x/a)) G vanishes
   // there like (sqrt(x/a) - s)^(n2/2); with s = sqrt(x/a) - t^2 the
   // integrand is smooth in t for every n2.
@@ -107,9 +153,10 @@ __device__ double two_level_cdf(double x, int i, int j, double lam, int k, int p
       // x - a s^2 without its cancellation near the end of the support
       const double rest = edge ? a * t * t * (2.0 * smax - t * t) : x - a * s * s;
       const bool ok = s > 0.0 && rest > 0.0;
-      const double y = rest * inv2b, ls = log(ok ? s : 1.0);
-      const double dens = jac * exp(lc + (n1 - 1.0) * ls - 0.5 * s * s);
-      const double der = (edge ? jac : -1.0) * exp(lg + ls + (al - 1.0) * log(ok ? y : 1.0) - y);
+      const double so = ok ? s : c, y = ok ? rest * inv2b : al;
+      const double dens = jac * exp_neg(lc + ((n1 - 1.0) * log_ratio(so, c, invc) - 0.5 * (so - c) * (so + c)));
+      const double der = (edge ? jac : -1.0) * ab * so *
+                         exp_neg(lg + ((al - 1.0) * log_ratio(y, al, inval) - (y - al)));
       D[q] = ok ? g.gw[q] * dens : 0.0;
       gd[q] = ok ? der : 0.0;
     }
