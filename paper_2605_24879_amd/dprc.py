@@ -102,7 +102,10 @@ def _check(status):
 
 
 def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    """torch's current stream on `dev`, as a pointer.  Read directly: building a torch.cuda.Stream
+    object for it took 1.9 us of each call's 3 to 7 us on the host."""
+    index = dev.index if dev.index is not None else torch.cuda.current_device()
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(index))
 
 
 def _dtype_code(t):
