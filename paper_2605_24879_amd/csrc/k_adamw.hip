@@ -14,6 +14,28 @@ namespace dprc {
 
 constexpr int kAT = 64;
 
+// Layers whose arrays (28 bytes per element) exceed the 256 MB Infinity Cache are streamed
+// with non-temporal loads and stores: the seven layers of a decoder block, 1.8 GB, went from
+// 392 to 375 us; with only the loads or only the stores marked they stayed at 392.  Smaller
+// layers may still be cached from the accumulation or the step before, and were 8 to 20%
+// slower marked (2048 x 2048: 20.2 us against 24.3, repeated).
+constexpr int64_t kStreamBytes = 256 << 20;
+
+typedef float f4_t __attribute__((ext_vector_type(4)));
+template <bool NT>
+__device__ __forceinline__ void load4(const float* p, float (&x)[4]) {
+  const f4_t* q = reinterpret_cast<const f4_t*>(p);
+  const f4_t v = NT ? __builtin_nontemporal_load(q) : *q;
+  x[0] = v[0]; x[1] = v[1]; x[2] = v[2]; x[3] = v[3];
+}
+template <bool NT>
+__device__ __forceinline__ void store4f(float* p, const float (&x)[4]) {
+  const f4_t v = {x[0], x[1], x[2], x[3]};
+  f4_t* q = reinterpret_cast<f4_t*>(p);
+  if (NT) __builtin_nontemporal_store(v, q);
+  else *q = v;
+}
+
 __device__ __forceinline__ float noise_elem(uint32_t key0, uint32_t key1, uint32_t tensor, int64_t e) {
   const uint64_t q = (uint64_t)e >> 2;
   const u32x4 x = philox4x32_10(u32x4{(uint32_t)q, (uint32_t)(q >> 32), tensor, kStreamNoise}, key0, key1);
@@ -33,7 +55,7 @@ __device__ __forceinline__ void adamw1(const AdamArgs& a, float g, float& th, fl
 
 // VEC: p, ldt, ldg multiples of 4 and 16-byte aligned bases (float4 access,
 // whole noise blocks); otherwise element access with bounds checks.
-template <bool VEC>
+template <bool VEC, bool NT>
 __global__ __launch_bounds__(256) void private_adamw_kernel(AdamArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t wt[kAT][kAT + 8];          // [column][row] of the bf16 tile
   const int tid = threadIdx.x;
@@ -53,14 +75,10 @@ __global__ __launch_bounds__(256) void private_adamw_kernel(AdamArgs a) {
       const float* gp = a.G + r * a.ldg + c;
       float g[4], m[4], v[4], n[4] = {0.f, 0.f, 0.f, 0.f};
       if (VEC && c + 4 <= a.p) {
-        const float4 g4 = *reinterpret_cast<const float4*>(gp);
-        const float4 t4 = *reinterpret_cast<const float4*>(tp);
-        const float4 m4 = *reinterpret_cast<const float4*>(mp);
-        const float4 v4 = *reinterpret_cast<const float4*>(vp);
-        g[0] = g4.x; g[1] = g4.y; g[2] = g4.z; g[3] = g4.w;
-        th[0] = t4.x; th[1] = t4.y; th[2] = t4.z; th[3] = t4.w;
-        m[0] = m4.x; m[1] = m4.y; m[2] = m4.z; m[3] = m4.w;
-        v[0] = v4.x; v[1] = v4.y; v[2] = v4.z; v[3] = v4.w;
+        load4<NT>(gp, g);
+        load4<NT>(tp, th);
+        load4<NT>(mp, m);
+        load4<NT>(vp, v);
         if (noise) {
           const uint64_t q = (uint64_t)(r * a.p + c) >> 2;
           const u32x4 x = philox4x32_10(u32x4{(uint32_t)q, (uint32_t)(q >> 32), a.tensor, kStreamNoise}, a.key0, a.key1);
@@ -69,9 +87,9 @@ __global__ __launch_bounds__(256) void private_adamw_kernel(AdamArgs a) {
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) adamw1(a, fmaf(a.noise_scale, n[j], g[j]) * a.inv_batch, th[j], m[j], v[j]);
-        *reinterpret_cast<float4*>(tp) = float4{th[0], th[1], th[2], th[3]};
-        *reinterpret_cast<float4*>(mp) = float4{m[0], m[1], m[2], m[3]};
-        *reinterpret_cast<float4*>(vp) = float4{v[0], v[1], v[2], v[3]};
+        store4f<NT>(tp, th);
+        store4f<NT>(mp, m);
+        store4f<NT>(vp, v);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -111,8 +129,9 @@ __global__ __launch_bounds__(256) void private_adamw_kernel(AdamArgs a) {
 hipError_t launch_private_adamw(const AdamArgs& a, hipStream_t st) {
   if (a.d == 0 || a.p == 0) return hipSuccess;
   const dim3 grid((unsigned)ceil_div(a.p, kAT), (unsigned)ceil_div(a.d, kAT));
-  if (a.vec) DPRC_LAUNCH(private_adamw_kernel<true>, grid, dim3(256), 0, st, a);
-  else DPRC_LAUNCH(private_adamw_kernel<false>, grid, dim3(256), 0, st, a);
+  if (a.vec && 28 * a.d * a.p > kStreamBytes) DPRC_LAUNCH((private_adamw_kernel<true, true>), grid, dim3(256), 0, st, a);
+  else if (a.vec) DPRC_LAUNCH((private_adamw_kernel<true, false>), grid, dim3(256), 0, st, a);
+  else DPRC_LAUNCH((private_adamw_kernel<false, false>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

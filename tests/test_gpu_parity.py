@@ -784,6 +784,7 @@ def test_add_noise_moments(D):
     (67, 130, 3, 0.5, 2, True),       # p not a multiple of 4, padded rows: element path, ragged tiles
     (64, 64, 4, 0.0, 1, False),       # no noise, no weight copy, padded rows
     (1, 5, 0, 1.0, 1, True),
+    (3080, 3200, 0, 0.7, 1, True),    # more than 256 MB of arrays: non-temporal accesses, ragged tiles
 ])
 def test_private_adamw_parity(D, d, p, ld_pad, sigma, steps, wout):
     r = np.random.default_rng(1000 * d + p)
