@@ -359,8 +359,14 @@ __device__ __forceinline__ void tokred_body(const TokredArgs& a, int bx, int by)
     }
 }
 
+// Waves per SIMD the registers are held to: two one-tile workgroups fit a CU's LDS up to 64
+// columns, which the allocator would not give 48 and 64 columns by itself (260 to 302
+// registers; eight groups of 64 columns 85 -> 76 us).  The loads at any alignment spill then.
 template <int NB, int LD>
-__global__ __launch_bounds__(kBlock) void tokred_kernel(TokredArgs a) {
+constexpr int kTokWaves = NB <= 3 ? (LD == kLoadElem ? 1 : 2) : (NB == 4 && LD == kLoadVec ? 2 : 1);
+
+template <int NB, int LD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kTokWaves<NB, LD>))) void tokred_kernel(TokredArgs a) {
   tokred_body<NB, LD>(a, blockIdx.x, blockIdx.y);
 }
 
@@ -376,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void tokred_kernel(TokredArgs a) {
 // is padded to whole windows.
 constexpr int kXcdRun = 16;
 template <int NB, int LD, int TT>
-__global__ __launch_bounds__(kBlock * TT) void tokred_batch_kernel(TokredBatch bt) {
+__global__ __launch_bounds__(kBlock * TT) __attribute__((amdgpu_waves_per_eu(kTokWaves<NB, LD>))) void tokred_batch_kernel(TokredBatch bt) {
   constexpr int W = 8 * kXcdRun;
   const int id = (int)blockIdx.x;
   const int b = bt.job[0].S == 1 ? id / W * W + (id & 7) * kXcdRun + (id % W) / 8 : id;
