@@ -121,21 +121,27 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
   // (kb, nbd) of a lane is R[16 nbd + l16][c0 + 32 kb + 8 g .. + 7] (R rows are
   // zero-padded to a multiple of 128 columns); a lane past the dense columns or a
   // slice past the width reads a valid address, and its value is not used.
-  auto gload = [&](uint4 (&dst)[NL], uint4 (&dh)[ND], uint4 (&dl)[ND], int st, int col_end)
-                   __attribute__((always_inline)) {
+  auto gload = [&](uint4 (&dst)[NL], int st, int col_end) __attribute__((always_inline)) {
     const int c0 = st * kProjStage + kProjSlice * wv;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       const int col = c0 + 8 * lpiece[j];
       if constexpr (LD == kLoadVec) {
-        const bool ok = col < col_end;
-        dst[j] = buffer_load16_nt(xr, ok ? roff[j] + 2u * (uint32_t)col : kOobOffset);
+        // rows 16 apart share their piece: four lane offsets, the rest is uniform
+        const bool ok = c0 + 8 * lpiece[j & 3] < col_end;
+        const uint32_t uni = (uint32_t)((j >> 2) * 16 * a.ldx + c0) * 2u;
+        dst[j] = buffer_load16_nt(xr, ok ? roff[j & 3] + 16u * (uint32_t)lpiece[j & 3] + uni : kOobOffset);
       } else if constexpr (LD == kLoadAny) {       // lanes past the width all read the block's first piece
         dst[j] = load16_any(xb, min(room, col < col_end ? (int)roff[j] + col : 0));
       } else {
         dst[j] = load8_elem(rowp[j], col, col_end, t0 + 4 * j + lrow < a.T);
       }
     }
+  };
+  // Issued after the multiply, into the fragments it has just used: loaded with X before it, they
+  // needed a second set of registers and copies (Hutch++ on a decoder block 1860 -> 1839 us).
+  auto rload = [&](uint4 (&dh)[ND], uint4 (&dl)[ND], int st, int col_end) __attribute__((always_inline)) {
+    const int c0 = st * kProjStage + kProjSlice * wv;
     if constexpr (DENSE) {
       const int cb = c0 < col_end ? c0 : 0;
 #pragma unroll
@@ -201,7 +207,10 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
     const int nst = (col_end - uc + kProjStage - 1) / kProjStage;
     uint4 ring[P][NL], rdh[P][ND], rdl[P][ND];
 #pragma unroll
-    for (int q = 0; q < P; ++q) gload(ring[q], rdh[q], rdl[q], s0 + q, q < nst ? col_end : 0);
+    for (int q = 0; q < P; ++q) {
+      gload(ring[q], s0 + q, q < nst ? col_end : 0);
+      rload(rdh[q], rdl[q], s0 + q, q < nst ? col_end : 0);
+    }
     if (a.nz > 0) {                                // generated while the first stages are in flight
       __syncthreads();
       const int nblk = wpc >> 2;
@@ -225,15 +234,10 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
     auto step = [&](int k, auto ph) __attribute__((always_inline)) {
       constexpr int q = decltype(ph)::value;
       const int st = s0 + k;
-      uint4 dh[ND], dl[ND];
-#pragma unroll
-      for (int e = 0; e < ND; ++e) {
-        dh[e] = rdh[q][e];
-        dl[e] = rdl[q][e];
-      }
       to_lds(ring[q], st);
-      gload(ring[q], rdh[q], rdl[q], st + P, k + P < nst ? col_end : 0);
-      mult(st, uc, dh, dl);
+      gload(ring[q], st + P, k + P < nst ? col_end : 0);
+      mult(st, uc, rdh[q], rdl[q]);
+      rload(rdh[q], rdl[q], st + P, k + P < nst ? col_end : 0);   // into the fragments just used
     };
     // whole groups of P stages in the loop (no early exit reaches its back edge,
     // so the compiler's wait counting stays exact), the remainder after it
