@@ -709,10 +709,10 @@ def run_accountant(args, torch, D):
            "value": big["candidates_per_s"], "unit": "forms/s", "n_gpus": 1, "steps": 1, "warmup": 1,
            "ms_per_step": big["ms"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
            "dtype": "f64", "data": "none (closed-form distributions)",
-           "config": {"workload": "accountant", "k": k, "n_lambda": nl, "quadrature": "16 panels x 16 nodes"},
+           "config": {"workload": "accountant", "k": k, "n_lambda": nl, "quadrature": "at least 16 panels x 16 nodes"},
            "roofline": {"bound": "alu", "achieved": None, "peak": 78.6, "unit": "TFLOP/s", "frac": None,
                         "traffic": None, "kernel": "envelope",
-                        "note": "fp64 series / continued fractions of the incomplete gamma per node"},
+                        "note": "fp64 densities at the nodes, integrated along each panel; at most one incomplete gamma per form"},
            "extra": {"middle_region": rows, "x_plus_d128_s": round(xp_s, 2), "x_plus_d128": xp,
                      "x_plus_asymptotic": 1 + 2 / (128 * k), "envelope_law_d128_s": round(env_s, 2),
                      "epsilon_s": round(eps_s, 3),

@@ -31,8 +31,9 @@
  *     A + (i*T + t)*lda + j.  Pointers must be aligned to their element size
  *     (else DPRC_ERROR_NOT_SUPPORTED).  bf16 rows that start on 16-byte
  *     boundaries (16-byte aligned base, stride a multiple of 8) with a width
- *     that is a multiple of 8 take 16-byte loads; other layouts are correct
- *     but slower (element loads).
+ *     that is a multiple of 8 take 16-byte buffer loads; other layouts take
+ *     16-byte loads at the element's own address, somewhat slower (element
+ *     loads for operands of fewer than 8 elements).
  *
  * Probes: +-1 (Rademacher) entries from Philox4x32-10 (Salmon et al., SC'11)
  * keyed by (seed, layer_id, stream), shared by all samples of a layer and
