@@ -122,6 +122,7 @@ __global__ __launch_bounds__(kPldBlock) void envelope_bins_kernel(const double* 
 
 constexpr int kSurvWaves = 8;
 constexpr int kSurvCuts = 16;
+constexpr double kFarU = 300.0;    // losses above it take an exponential for each tail
 __global__ __launch_bounds__(64 * kSurvWaves) void pld_survival_kernel(PldArgs a) {
   __shared__ double tab[kSurvWaves][64][3];      // a wave's next 64 bins: 1/mu, mu/2, weight
   __shared__ double sums[kSurvWaves][kSurvCuts][2];
@@ -130,7 +131,9 @@ __global__ __launch_bounds__(64 * kSurvWaves) void pld_survival_kernel(PldArgs a
   const double t = ((double)(c - a.n) + 0.5) * a.h;
   const bool inside = c < 2 * a.n && t > a.t_min;
   const double u = inside && a.p < 1.0 ? t + log(1.0 / a.p - (1.0 - a.p) / a.p * exp(-t)) : t;
-  const double eu = exp(u);
+  // e^u leaves the doubles at u = 709.8, and e1 (below) what they resolve before that
+  const bool far = u > kFarU;
+  const double eu = far ? 0.0 : exp(u);
   double al = 0.0, beb = 0.0;
   if (a.n_bins == 0) {
     const double mu = 1.0 / a.sigma;
@@ -151,11 +154,13 @@ __global__ __launch_bounds__(64 * kSurvWaves) void pld_survival_kernel(PldArgs a
       const int m = min(64, i1 - i0);
       for (int k = g; k < m; k += 64 / kSurvCuts) {
         // arguments z + h and z - h with z = u / mu, h = mu / 2: 2 z h = u, so one exponential
-        // (and e^u, the same for every bin) serves both tails
-        const double wi = tab[wv][k][2], hm = tab[wv][k][1], z = u * tab[wv][k][0], w1 = z + hm;
+        // (and e^u, the same for every bin) serves both tails up to kFarU
+        const double wi = tab[wv][k][2], hm = tab[wv][k][1], z = u * tab[wv][k][0], w1 = z + hm, w2 = z - hm;
         const double e1 = 0.5 * exp(-0.5 * w1 * w1);
+        double e2 = e1 * eu;
+        if (far) e2 = 0.5 * exp(-0.5 * w2 * w2);
         al += wi * upper_tail(w1, e1);
-        beb += wi * upper_tail(z - hm, e1 * eu);
+        beb += wi * upper_tail(w2, e2);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();

@@ -218,3 +218,17 @@ def test_pld_small_grids(mods, n_half, n_bins):
     q2, qi2 = D.dprc_pld_fold(r, len(qr), qi, qi)
     r2, ri2 = ac._conv_truncated(qr, qir, qr, qir)
     assert np.max(np.abs(q2.cpu().numpy() - r2)) < 1e-13 and abs(qi2.item() - ri2) < 1e-13
+
+
+@pytest.mark.parametrize("sigma", [0.02, 0.5])
+def test_step_pld_beyond_the_range_of_exp(mods, sigma):
+    # losses past 709, where e^u is not a double: at sigma = 0.02 probability is left there
+    D, _ = mods
+    h, t_max, p, k, nb = 0.25, 1000.0, 0.0256, 32, 400
+    y, w = ac.envelope_bins(lambda v: ac.vertex_cdf(v, k), 0.0, 1.0 + 12.0 * math.sqrt(2.0 / k), nb)
+    q, qi = D.dprc_pld_step(sigma, p, h, int(round(t_max / h)), _t(y), _t(w))
+    grid, qr, qir = ac.single_step_pld(sigma, p, h, t_max, y, w)
+    assert np.max(np.abs(q.cpu().numpy() - qr)) < 1e-13 and abs(qi.item() - qir) < 1e-13
+    eps = [0.0, 299.75, 500.0, 720.25, 990.0]
+    got = D.dprc_pld_delta(q, h, qi, _t(eps)).cpu().numpy()
+    assert np.max(np.abs(got - [ac.delta_of_eps(grid, qr, qir, e) for e in eps])) < 1e-12
