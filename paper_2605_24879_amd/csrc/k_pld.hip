@@ -144,10 +144,12 @@ __global__ __launch_bounds__(64 * kSurvWaves) void pld_survival_kernel(PldArgs a
     const int32_t i1 = min(a.n_bins, (wv + 1) * per);
     for (int32_t i0 = wv * per; i0 < i1; i0 += 64) {
       const int32_t i = i0 + lane;
-      const double inv = i < i1 ? sqrt(a.ybar[i]) * a.sigma : 1.0;
+      // a bin without weight has no part in the sums, whatever its point (padding may hold NaN)
+      const double wi = i < i1 ? a.w[i] : 0.0;
+      const double inv = wi != 0.0 ? sqrt(a.ybar[i]) * a.sigma : 1.0;
       tab[wv][lane][0] = inv;
       tab[wv][lane][1] = 0.5 / inv;
-      tab[wv][lane][2] = i < i1 ? a.w[i] : 0.0;
+      tab[wv][lane][2] = wi;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -232,3 +232,15 @@ def test_step_pld_beyond_the_range_of_exp(mods, sigma):
     eps = [0.0, 299.75, 500.0, 720.25, 990.0]
     got = D.dprc_pld_delta(q, h, qi, _t(eps)).cpu().numpy()
     assert np.max(np.abs(got - [ac.delta_of_eps(grid, qr, qir, e) for e in eps])) < 1e-12
+
+
+def test_step_pld_ignores_bins_without_weight(mods):
+    # padding bins of weight zero, whatever their points hold, change nothing
+    D, _ = mods
+    y, w = np.linspace(0.4, 1.8, 70), np.linspace(1.0, 2.0, 70)
+    w /= w.sum()
+    pad = np.array([np.nan, -1.0, 0.0, np.inf] * 10)
+    q, qi = D.dprc_pld_step(0.9, 0.2, 0.01, 700, _t(np.concatenate([pad, y, pad])),
+                            _t(np.concatenate([0 * w[:40], w, 0 * w[:40]])))
+    grid, qr, qir = ac.single_step_pld(0.9, 0.2, 0.01, 7.0, y, w)
+    assert np.max(np.abs(q.cpu().numpy() - qr)) < 1e-13 and abs(qi.item() - qir) < 1e-13
