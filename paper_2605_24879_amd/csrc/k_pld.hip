@@ -312,17 +312,18 @@ __global__ __launch_bounds__(kPldBlock) void pld_delta_kernel(const double* q, i
   const double e = eps[blockIdx.x];
   const int64_t c = (L - 1) / 2;
   // the cells from two below eps on, in runs of 16 per thread: one exponential per run, the
-  // others by the constant ratio between a thread's cells
+  // others by the constant ratio between a thread's cells.  The first exponent, at most 3 h,
+  // is kept where e^x is a double: beyond that the ratio is 0, and 0 has to follow.
   constexpr int U = 16;
   const double ratio = exp(-(double)blockDim.x * h);
   const double first = floor(e / h) + (double)(c - 2);
-  const int64_t j1 = first <= 0.0 ? 0 : (first >= (double)L ? L : (int64_t)first);
+  const int64_t j1 = first <= 0.0 ? 0 : (first < (double)L ? (int64_t)first : L);   // eps not a number: no cell
   double s = 0.0;
   for (int64_t j0 = j1 + threadIdx.x; j0 < L; j0 += (int64_t)U * blockDim.x) {
     double v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = q[min(j0 + (int64_t)u * blockDim.x, L - 1)];
-    double ex = exp(e - (double)(j0 - c) * h);
+    double ex = exp(fmin(e - (double)(j0 - c) * h, 700.0));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t j = j0 + (int64_t)u * blockDim.x;

@@ -244,3 +244,18 @@ def test_step_pld_ignores_bins_without_weight(mods):
                             _t(np.concatenate([0 * w[:40], w, 0 * w[:40]])))
     grid, qr, qir = ac.single_step_pld(0.9, 0.2, 0.01, 7.0, y, w)
     assert np.max(np.abs(q.cpu().numpy() - qr)) < 1e-13 and abs(qi.item() - qir) < 1e-13
+
+
+@pytest.mark.parametrize("h", [1e-3, 100.0, 400.0])
+def test_pld_delta_at_any_cell_width(mods, h):
+    # cells so wide that e^(2h) is not a double; eps below, at, between and beyond the cells
+    D, _ = mods
+    L = 3001
+    q = np.random.default_rng(3).random(L)
+    q /= 1.01 * q.sum()
+    qi = 1.0 - q.sum()
+    grid = (np.arange(L) - (L - 1) // 2) * h
+    eps = np.array([-1e308, -1000 * h, -h, 0.0, 0.5 * h, 700 * h, 1e308])
+    got = D.dprc_pld_delta(_t(q), h, _t([qi]), _t(eps)).cpu().numpy()
+    assert np.max(np.abs(got - [ac.delta_of_eps(grid, q, qi, e) for e in eps])) < 1e-12
+    assert D.dprc_pld_delta(_t(q), h, _t([qi]), _t([np.nan])).item() == qi
