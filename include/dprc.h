@@ -289,7 +289,8 @@ dprc_status dprc_chi2_cdf(const double* x, int64_t n, double dof, double scale, 
  * (r[j] sits at cell j - (L - 1)/2 of the result grid): negatives clipped; the
  * L centred cells kept, the mass below them added to the lowest one; the atom
  * becomes 1 - (1 - ainf)(1 - binf) plus the mass above them, rescaled with the
- * cells so that the total stays one.  q [L] and q_inf [1] must not overlap r.
+ * cells so that the total stays one.  q [L] and q_inf [1] must not overlap r, nor q
+ * the atoms; q_inf may be ainf or binf.
  *
  * dprc_pld_delta: delta[e] = sum over t_j >= eps[e] of q_j (1 - e^(eps[e] - t_j))
  * + q_inf[0], clipped to [0, 1], t_j = (j - (L - 1)/2) h, for 1 <= n_eps <= 65535.

@@ -268,7 +268,9 @@ __device__ __forceinline__ void fold_cells(const double* r, int64_t L, const dou
     const double v = fmax(r[f.c + j], 0.0);
     q[j] = (j == 0 ? v + s[0] : v) * scale;
   }
-  if (atom && threadIdx.x == 0) q_inf[0] = fin > 0.0 ? inf0 + s[2] * scale : inf0;
+  if (!atom) return;
+  __syncthreads();                                    // q_inf may be ainf or binf: every wave has read them
+  if (threadIdx.x == 0) q_inf[0] = fin > 0.0 ? inf0 + s[2] * scale : inf0;
 }
 
 __global__ __launch_bounds__(kFoldBlock) void pld_fold_sums_kernel(const double* r, int64_t L, double* q) {

@@ -259,3 +259,25 @@ def test_pld_delta_at_any_cell_width(mods, h):
     got = D.dprc_pld_delta(_t(q), h, _t([qi]), _t(eps)).cpu().numpy()
     assert np.max(np.abs(got - [ac.delta_of_eps(grid, q, qi, e) for e in eps])) < 1e-12
     assert D.dprc_pld_delta(_t(q), h, _t([qi]), _t([np.nan])).item() == qi
+
+
+@pytest.mark.parametrize("L", [1, 501, 4001])
+def test_pld_fold_with_the_atom_in_place(mods, L):
+    # q_inf may be one of the atoms that the call reads, or both
+    D, _ = mods
+    rng = np.random.default_rng(L)
+    r = _t(rng.random(2 * L - 1) / L)
+    ainf, binf = _t([0.125]), _t([0.25])
+    q, qi = D.dprc_pld_fold(r, L, ainf, binf)
+    out = torch.empty_like(q)
+    for a, b in ((ainf, binf), (binf, _t([0.125]))):
+        atom = a.clone()
+        pair = (atom, b) if a is ainf else (b, atom)
+        assert D.lib().dprc_pld_fold(r.data_ptr(), L, pair[0].data_ptr(), pair[1].data_ptr(), out.data_ptr(),
+                                     atom.data_ptr(), D._stream(r.device)) == D.SUCCESS
+        assert torch.equal(out, q) and torch.equal(atom, qi)
+    half = D.dprc_pld_fold(r, L, ainf, ainf)
+    both = ainf.clone()
+    assert D.lib().dprc_pld_fold(r.data_ptr(), L, both.data_ptr(), both.data_ptr(), out.data_ptr(), both.data_ptr(),
+                                 D._stream(r.device)) == D.SUCCESS
+    assert torch.equal(out, half[0]) and torch.equal(both, half[1])
