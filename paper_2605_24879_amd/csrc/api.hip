@@ -164,22 +164,20 @@ struct Trace {
   int32_t* kinds = nullptr;
   int32_t capacity = 0;
   int32_t* count = nullptr;
+  int32_t kind = 0;          // of the launches under way (0: none)
 };
 thread_local Trace g_trace;
-thread_local LaunchEvents g_next_events;
 
-// The start/stop events ride on the launch itself (hipExtLaunchKernelGGL in DPRC_LAUNCH).
+// The launches that `launch` makes are recorded as `kind`, each with events of its own (its
+// start/stop events ride on the launch itself: hipExtLaunchKernelGGL in DPRC_LAUNCH).
 template <class F>
 hipError_t traced(int kind, hipStream_t, F&& launch) {
   Trace& t = g_trace;
-  const bool on = t.events && t.count && *t.count < t.capacity;
-  if (on) g_next_events = LaunchEvents{t.events[2 * *t.count], t.events[2 * *t.count + 1]};
+  const int32_t before = t.count ? *t.count : 0;
+  t.kind = kind;
   const hipError_t e = launch();
-  g_next_events = LaunchEvents{};
-  if (on && e == hipSuccess) {
-    if (t.kinds) t.kinds[*t.count] = kind;
-    ++*t.count;
-  }
+  t.kind = 0;
+  if (t.count && e != hipSuccess) *t.count = before;
   return e;
 }
 
@@ -908,7 +906,13 @@ dprc_status static_scratch(hipStream_t stream, void** out) {
 }  // namespace
 
 namespace dprc {
-LaunchEvents& next_launch_events() { return g_next_events; }
+LaunchEvents next_launch_events() {
+  Trace& t = g_trace;
+  if (!t.kind || !t.count || *t.count >= t.capacity) return {};
+  const int32_t j = (*t.count)++;
+  if (t.kinds) t.kinds[j] = t.kind;
+  return {t.events[2 * j], t.events[2 * j + 1]};
+}
 }  // namespace dprc
 
 extern "C" {

@@ -8,18 +8,18 @@
 
 namespace dprc {
 
-// Start/stop events for the next launch on this host thread, set by the
-// launch-trace hook of the C ABI (null otherwise).  With events, the kernel is
+// Start/stop events of the next launch on this host thread, one pair per launch, from the
+// launch-trace hook of the C ABI (null without it).  With events, the kernel is
 // launched through hipExtLaunchKernelGGL, which stamps them from the dispatch
 // itself (no extra packets, so no timing overhead is added to the kernel).
 struct LaunchEvents {
   hipEvent_t start = nullptr, stop = nullptr;
 };
-LaunchEvents& next_launch_events();
+LaunchEvents next_launch_events();   // takes the pair
 
 #define DPRC_LAUNCH(kernel, grid, block, lds, st, ...)                                            \
   do {                                                                                             \
-    ::dprc::LaunchEvents& ev_ = ::dprc::next_launch_events();                                      \
+    const ::dprc::LaunchEvents ev_ = ::dprc::next_launch_events();                                 \
     if (ev_.start)                                                                                 \
       hipExtLaunchKernelGGL(kernel, grid, block, lds, st, ev_.start, ev_.stop, 0u, __VA_ARGS__);   \
     else                                                                                           \
