@@ -139,7 +139,7 @@ dprc_status dprc_norm_hutch_clip(const dprc_layer* layers, int32_t num_layers, i
  * object holds on every device it runs on until the process ends; the call allocates
  * nothing and frees nothing.  A call whose dprc_norm_hutch_workspace() exceeds that
  * size returns DPRC_ERROR_SCRATCH_LIMIT and enqueues nothing (the 113-layer
- * Llama-3.2-1B stack at B = 8, T = 4096, k = 32 needs 136 MiB; GAUSSIAN calls that
+ * Llama-3.2-1B stack at B = 8, T = 4096, k = 32 needs 224 MiB; GAUSSIAN calls that
  * exceed it run with launches per group as long as those fit).  `stream` must belong
  * to the current device (else DPRC_ERROR_INVALID_VALUE); the first call on a device
  * looks up that device's copy of the array (hipGetSymbolAddress) and keeps its

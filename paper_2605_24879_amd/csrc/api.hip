@@ -142,9 +142,33 @@ TokPlan tok_plan(int64_t B, int64_t T, int64_t n) {
   return p;
 }
 
+// Each reduction of a batch comes with token splits that give it about 256 workgroups of its
+// own.  The reductions of one launch share the GPU, so a batch needs fewer: none at all from
+// kUnsplitPairs (sample, 128-column tile) pairs on (unsplit workgroups write their tile sums
+// directly; halves the start-up and finish costs of two-way splits), and, as soon as the
+// pairs give every CU one, none of fewer than 16 stages (1024 tokens): Hutch++ on an attention
+// block at B = 4, T = 1024 took 259 us with four splits of 4 stages and five split-sum
+// launches, 240 us without.  Longer splits stay: at T = 4096 and 32768 dropping them was 3 to
+// 5% slower, and with 128 pairs two splits instead of four were 5% slower.
+constexpr int64_t kUnsplitPairs = 1024;
+constexpr int64_t kMinSplitStages = 16;
+void limit_splits(TokPlan* tp, int64_t B, int n) {
+  int64_t pairs = 0;
+  for (int q = 0; q < n; ++q) pairs += B * tp[q].ntiles;
+  if (pairs < 256) return;
+  for (int q = 0; q < n; ++q) {
+    const int64_t stages = tp[q].T_pad / kStage;
+    const int64_t most = pairs >= kUnsplitPairs ? 1 : std::max<int64_t>(1, stages / kMinSplitStages);
+    if (tp[q].S <= most) continue;
+    tp[q].sps = (int32_t)ceil_div(stages, most);
+    tp[q].S = (int32_t)ceil_div(stages, tp[q].sps);
+  }
+}
+
 struct TokBufs {
-  float* part;
-  double* tilesq;
+  float* part = nullptr;
+  double* tilesq = nullptr;
+  TokPlan tp{};              // a group's plan among the groups of its batch
   uint16_t* Y = nullptr;     // a group's own Y (batched launches)
   uint16_t* Z = nullptr;     // and its layers' Gaussian probe columns, hi then lo, layer by layer
 };
@@ -275,31 +299,6 @@ int64_t part_floats(int64_t B, int64_t T, int64_t n, int ncols) {
   return tp.S > 1 ? B * tp.ntiles * tp.S * pad_cols(ncols) * kTile : 0;
 }
 
-// Each job of a batched token reduction comes with token splits that give it about 256
-// workgroups of its own.  The jobs of one launch share the GPU, so a batch needs fewer: none
-// at all from kUnsplitPairs (sample, 128-column tile) pairs on (unsplit workgroups write
-// their tile sums directly; halves the start-up and finish costs of two-way splits), and, as
-// soon as the pairs give every CU one, none of fewer than 16 stages (1024 tokens): Hutch++ on
-// an attention block at B = 4, T = 1024 took 259 us with four splits of 4 stages and five
-// split-sum launches, 240 us without.  Longer splits stay: at T = 4096 and 32768 dropping
-// them was 3 to 5% slower, and with 128 pairs two splits instead of four were 5% slower.
-constexpr int64_t kUnsplitPairs = 1024;
-constexpr int64_t kMinSplitStages = 16;
-void limit_splits(TokredArgs* job, int n) {
-  int64_t pairs = 0;
-  for (int q = 0; q < n; ++q) pairs += (int64_t)job[q].B * job[q].ntiles;
-  if (pairs < 256) return;
-  for (int q = 0; q < n; ++q) {
-    TokredArgs& a = job[q];
-    const int64_t stages = ceil_div(a.T_pad, kStage);
-    const int64_t most = pairs >= kUnsplitPairs ? 1 : std::max<int64_t>(1, stages / kMinSplitStages);
-    if (a.S <= most) continue;
-    a.stages_per_split = (int32_t)ceil_div(stages, most);
-    a.S = (int32_t)ceil_div(stages, a.stages_per_split);
-    if (a.S == 1) a.part = nullptr;
-  }
-}
-
 // Split sums of deferred passes (those with token splits), up to kTokMaxJobs per launch.
 dprc_status run_splits_batch(const TokredArgs* ta, int n, hipStream_t st) {
   TokredBatch bt{};
@@ -372,6 +371,16 @@ int64_t max_m(const View* v, int G) {
   return m;
 }
 
+// The probes of one layer of a bf16 group and the group's Y: the front of its scratch.
+size_t hutch_group_y(const View* v, int G, int32_t k, int probe) {
+  Arena ar(nullptr);
+  View vm = v[0];
+  vm.m = max_m(v, G);
+  if (probe == DPRC_PROBE_GAUSSIAN) take_gauss(ar, vm, k);
+  ar.take<uint16_t>((size_t)2 * pad_cols(G * k) * v[0].B * tok_plan(v[0].B, v[0].T, v[0].n).T_pad);
+  return ar.off;
+}
+
 size_t hutch_group_ws(const View* v, int G, int32_t k, int probe) {
   Arena ar(nullptr);
   View vm = v[0];
@@ -428,8 +437,8 @@ dprc_status hutch_f32(const View& v, int32_t k, int probe, uint32_t k0, uint32_t
 // G layers (G = 1, or a shared-activation group of bf16 OUT layers): one projection
 // per layer into its columns of a shared Y, then one token reduction.
 // With `defer` (bf16 layers), the split sums and the estimate are not launched: the
-// token-reduction arguments are returned for a batched launch, and the group's token-split
-// partials and tile sums go to `own` instead of the scratch.
+// token-reduction arguments are returned for a batched launch, with the plan, the token-split
+// partials, the tile sums and (unless null) the Y of `own` instead of the scratch.
 dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0, uint32_t k1, float* n2,
                         float* n2_layers, int accumulate, void* ws, hipStream_t st, float clipC = 0.f,
                         float* clip_c = nullptr, TokredArgs* defer = nullptr, const TokBufs* own = nullptr,
@@ -441,13 +450,16 @@ dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0,
   Arena ar(ws);
   View vm = v[0];
   vm.m = max_m(v, G);
-  GaussBufs gz = gauss ? take_gauss(ar, vm, k) : GaussBufs{};
   const int ncols = G * k, ncols_pad = pad_cols(ncols);
-  uint16_t* Yt;
-  TokBufs tb;
-  TokPlan tp;
-  pass_ws(ar, B, T, v[0].n, ncols_pad, &Yt, &tb, &tp, G);
-  if (own && own->Y) Yt = own->Y;
+  GaussBufs gz{};
+  uint16_t* Yt = own ? own->Y : nullptr;
+  TokBufs tb = own ? *own : TokBufs{};
+  TokPlan tp = tb.tp;
+  if (!Yt) {                                       // the front of the scratch, and with no `own` the rest of it
+    if (gauss) gz = take_gauss(ar, vm, k);
+    if (own) Yt = ar.take<uint16_t>((size_t)2 * ncols_pad * B * tp.T_pad);
+    else pass_ws(ar, B, T, v[0].n, ncols_pad, &Yt, &tb, &tp, G);
+  }
   const int64_t yt_ld = B * tp.T_pad;
   hipError_t e = hipSuccess;
   uint16_t* zown = own ? own->Z : nullptr;
@@ -492,10 +504,6 @@ dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0,
   ta.scale = 1.0f / (float)k; ta.n2 = n2; ta.n2_layer = n2_layers; ta.accumulate = accumulate;
   ta.clip_C = clipC; ta.clip_c = clip_c;
   ta.vec = rows16(v[0].Xo, v[0].ldo);
-  if (own) {
-    ta.part = own->part;
-    ta.tilesq = own->tilesq;
-  }
   if (pjobs) {
     *defer = ta;
     return DPRC_SUCCESS;
@@ -727,14 +735,15 @@ dprc_status hpp_pass_group(int which, const View* vs, PPBufs* bufs, int ng, int3
   }
   ProjectArgs pas[kProjMaxJobs];
   int64_t rows = 0;
+  TokPlan tps[kProjMaxJobs];
+  for (int q = 0; q < ng; ++q) tps[q] = tok_plan(vs[q].B, vs[q].T, hpp_spec(which, vs[q], s, r, bufs[q]).n);
+  limit_splits(tps, vs[0].B, ng);
   for (int q = 0; q < ng; ++q) {
     const PassSpec p = hpp_spec(which, vs[q], s, r, bufs[q]);
-    const TokPlan tp = tok_plan(vs[q].B, vs[q].T, p.n);
-    TokBufs own{tp.S > 1 ? bufs[q].part : nullptr, nullptr};
-    pass_args(p, vs[q].B, vs[q].T, k0, k1, vs[q].layer_id, bufs[q].Y, own, tp, pas[q], def[q]);
-    rows += vs[q].B * tp.T_pad;
+    TokBufs own{tps[q].S > 1 ? bufs[q].part : nullptr, nullptr};
+    pass_args(p, vs[q].B, vs[q].T, k0, k1, vs[q].layer_id, bufs[q].Y, own, tps[q], pas[q], def[q]);
+    rows += vs[q].B * tps[q].T_pad;
   }
-  limit_splits(def, ng);
   // widest layers first, so that the narrow ones fill the tail of each launch
   int op[kProjMaxJobs], ot[kProjMaxJobs];
   for (int q = 0; q < ng; ++q) op[q] = ot[q] = q;
@@ -1016,9 +1025,11 @@ size_t hutch_tilesq_bytes(const dprc_layer* layers, int32_t n, int32_t k, dprc_s
 }
 
 // Up to kTokMaxJobs consecutive activation groups starting at layer l0: their bounds in
-// ends[], their own buffers (token-split partials and, with `batched` launches, Y and the
-// Gaussian probes; the tile sums are the call's) carved from ws (own may be null) after the
-// shared scratch.  Returns the bytes used.
+// ends[], their plans (the same with and without `batched` launches, so that both give the
+// same sums) and their own buffers (token-split partials and, with `batched` launches, Y and
+// the Gaussian probes; the tile sums are the call's) carved from ws (own may be null).
+// Without batched launches a Y and a probe buffer that the groups use in turn come first.
+// Returns the bytes used.
 size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32_t k, int probe, dprc_side side,
                           bool batched, void* ws, int32_t* ends, int* ngroups, TokBufs* own) {
   View v[kMaxGroup];
@@ -1027,26 +1038,28 @@ size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32
   int32_t l = l0;
   while (l < n && ng < kTokMaxJobs) {
     const int32_t le = group_end(layers, l, n, k, side);
-    for (int32_t j = l; j < le; ++j) v[j - l] = view_of(layers[j], side);
-    shared = std::max(shared, hutch_group_ws(v, le - l, k, probe));
+    if (!batched) {
+      for (int32_t j = l; j < le; ++j) v[j - l] = view_of(layers[j], side);
+      shared = std::max(shared, hutch_group_y(v, le - l, k, probe));
+    }
     ends[ng++] = le;
     l = le;
   }
-  // a batch whose launches are batched and unsplit (limit_splits) needs no partials
-  int64_t pairs = 0;
+  TokPlan plan[kTokMaxJobs];
   for (int q = 0, lq = l0; q < ng; lq = ends[q++]) {
     const View v0 = view_of(layers[lq], side);
-    pairs += v0.B * tok_plan(v0.B, v0.T, v0.n).ntiles;
+    plan[q] = tok_plan(v0.B, v0.T, v0.n);
   }
-  const bool unsplit = batched && pairs >= kUnsplitPairs;
+  limit_splits(plan, layers[l0].B, ng);
   char* base = static_cast<char*>(ws);
   size_t off = (shared + kAlign - 1) / kAlign * kAlign;
   l = l0;
   for (int q = 0; q < ng; ++q) {
     const View v0 = view_of(layers[l], side);
     const int G = ends[q] - l;
-    const TokPlan tp = tok_plan(v0.B, v0.T, v0.n);
-    const size_t pf = !unsplit && tp.S > 1 ? (size_t)v0.B * tp.ntiles * tp.S * pad_cols(G * k) * kTile : 0;
+    const TokPlan& tp = plan[q];
+    const size_t pf = tp.S > 1 ? (size_t)v0.B * tp.ntiles * tp.S * pad_cols(G * k) * kTile : 0;
+    if (own) own[q].tp = tp;
     if (own) own[q].part = base && pf ? reinterpret_cast<float*>(base + off) : nullptr;
     off = (off + pf * sizeof(float) + kAlign - 1) / kAlign * kAlign;
     if (own) own[q].Y = own[q].Z = nullptr;
@@ -1071,13 +1084,6 @@ size_t hutch_batch_layout(const dprc_layer* layers, int32_t l0, int32_t n, int32
 static size_t hutch_workspace(const dprc_layer* layers, int32_t num_layers, int32_t k, dprc_probe probe,
                               dprc_side side, bool batched) {
   size_t need = 0;
-  View v[kMaxGroup];
-  for (int32_t l = 0; l < num_layers;) {
-    const int32_t le = group_end(layers, l, num_layers, k, side);
-    for (int32_t j = l; j < le; ++j) v[j - l] = view_of(layers[j], side);
-    need = std::max(need, hutch_group_ws(v, le - l, k, (int)probe));
-    l = le;
-  }
   if (hutch_batched(layers, num_layers)) {
     int32_t ends[kTokMaxJobs];
     int ng = 0;
@@ -1085,7 +1091,14 @@ static size_t hutch_workspace(const dprc_layer* layers, int32_t num_layers, int3
       need = std::max(need, hutch_batch_layout(layers, l, num_layers, k, (int)probe, side, batched, nullptr, ends, &ng, nullptr));
       l = ends[ng - 1];
     }
-    need += hutch_tilesq_bytes(layers, num_layers, k, side);   // the call's tile sums come first
+    return need + hutch_tilesq_bytes(layers, num_layers, k, side);   // the call's tile sums come first
+  }
+  View v[kMaxGroup];
+  for (int32_t l = 0; l < num_layers;) {
+    const int32_t le = group_end(layers, l, num_layers, k, side);
+    for (int32_t j = l; j < le; ++j) v[j - l] = view_of(layers[j], side);
+    need = std::max(need, hutch_group_ws(v, le - l, k, (int)probe));
+    l = le;
   }
   return need;
 }
@@ -1165,7 +1178,6 @@ static dprc_status norm_hutch(const dprc_layer* layers, int32_t num_layers, int3
       if (gb.njobs > 0 &&
           traced(DPRC_KERNEL_PROBE_GAUSS, stream, [&] { return launch_gauss_batch(gb, stream); }) != hipSuccess)
         return DPRC_ERROR_HIP;
-      if (batched) limit_splits(bt.job, bt.njobs);   // (unbatched groups launched theirs already)
       if (batched && (s = hutch_launch_batched(pj, npj, bt, stream)) != DPRC_SUCCESS) return s;
       if ((s = run_splits_batch(bt.job, bt.njobs, stream)) != DPRC_SUCCESS) return s;
       for (int q = 0; q < bt.njobs; ++q) {

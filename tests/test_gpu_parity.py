@@ -139,6 +139,36 @@ def test_hutch_gaussian_batched_launches(D, n):
     assert torch.equal(m2, n2) and torch.equal(mc, c) and torch.equal(mper, per)
 
 
+@pytest.mark.parametrize("n,B,T,d,p,k", [
+    (8, 32, 1024, 8, 72, 1),        # 256 pairs of samples and tiles: four token splits of 4 stages become one
+    (3, 90, 4096, 8, 40, 1),        # 270 pairs, 64 stages: splits of at least 16 stages
+    (32, 5, 512, 6528, 128, 32),    # 1024 pairs and more: none
+])
+def test_hutch_gaussian_forms_agree_where_splits_are_limited(D, n, B, T, d, p, k):
+    # batched launches, the smaller workspace's launches per group and the static scratch all
+    # split the tokens alike, so their estimates agree bit for bit (few entries per sample: a
+    # different split would show)
+    pairs = [_draw(B, T, d, p, layer=700 + j) + (j,) for j in range(n)]
+    arr, nl, _, dev = D._layers(pairs)
+    need = D.dprc_norm_hutch_workspace(pairs, k, probe=D.PROBE_GAUSSIAN)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    outs = []
+    for form in ("batched", "per group", "static"):
+        n2, c, per = (torch.full(s, -1.0, device="cuda") for s in ((B,), (B,), (n, B)))
+        out = (n2.data_ptr(), c.data_ptr(), per.data_ptr(), 0)
+        if form == "static":
+            status = D.lib().dprc_norm_hutch_clip_static(arr, nl, k, D.PROBE_GAUSSIAN, 5, 0, 0.5, *out, D._stream(dev))
+        else:
+            status = D.lib().dprc_norm_hutch_clip(arr, nl, k, D.PROBE_GAUSSIAN, 5, 0, 0.5, *out, ws.data_ptr(),
+                                                  need - (form == "per group"), D._stream(dev))
+        assert status == D.SUCCESS, form
+        outs.append(torch.cat([n2, c, per.flatten()]))
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    A, E, _ = pairs[1]
+    ref = est.hutch_layer(_np(A[:2]), _np(E[:2]), k, 5, 1, probe="gaussian")
+    assert np.all(_rel(outs[0][2 * B:].view(n, B)[1, :2].cpu().numpy(), ref) < NORM_RTOL)
+
+
 def test_hutch_gaussian_multilayer_accumulate(D):
     # per-layer probes differ (layer id in the counter); the workspace is reused across layers
     A1, E1 = _draw(2, 300, 256, 200, layer=0)

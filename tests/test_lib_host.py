@@ -227,6 +227,32 @@ def test_static_scratch_entry_point_limits():
     assert L.dprc_status_string(5).decode().startswith("DPRC_ERROR_SCRATCH_LIMIT")
 
 
+def test_static_scratch_holds_what_needs_no_more():
+    # split partials are reserved for the splits that a batch of layers runs with, in both forms of
+    # a Gaussian call: no form's need exceeds the query.  (An unaligned workspace is refused
+    # with 1, after a too small one with 3, so nothing is enqueued here.)
+    L = dprc.lib()
+    limit = 256 << 20
+
+    def layers(n, share, **kw):
+        return (dprc.Layer * n)(*[_fake_layer(A=0x1000000 + 0x10000 * (j // share), E=0x90000000 + 0x10000 * j,
+                                              layer_id=j, **kw) for j in range(n)])
+    # 32 Gaussian layers: 1024 pairs of samples and tiles and more, so no splits
+    arr = layers(32, 1, B=5, T=512, d=6528, p=2048, lda=6528, lde=2048)
+    need = L.dprc_norm_hutch_workspace(arr, 32, 32, dprc.PROBE_GAUSSIAN, 0)
+    assert need < 32 << 20
+    for size in (need, need - 1, limit):
+        assert L.dprc_norm_hutch(arr, 32, 32, dprc.PROBE_GAUSSIAN, 0, 0, 0x40000, None, 0, 0x30010, size, None) == 1
+    assert L.dprc_norm_hutch(arr, 32, 32, dprc.PROBE_GAUSSIAN, 0, 0, 0x40000, None, 0, 0x30010, need // 64, None) == 3
+    # sign probes: a batch of 32 narrow groups of the stack reserves the splits that it runs with
+    stack = []
+    for j in range(200):
+        d, p = ((19183, 110)[j // 3 % 2], (274, 1351)[j % 2])
+        stack.append(_fake_layer(A=0x1000000 + 0x10000 * (j // 3), E=0x90000000 + 0x10000 * j, B=9, T=708, d=d, p=p,
+                                 lda=d, lde=p, layer_id=j))
+    assert L.dprc_norm_hutch_workspace((dprc.Layer * 200)(*stack), 200, 128, dprc.PROBE_RADEMACHER, 2) <= limit
+
+
 def test_accountant_entry_points_validation():
     L = dprc.lib()
     P = 0x10000
