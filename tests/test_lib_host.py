@@ -5,8 +5,10 @@ enqueues anything (so these calls never reach a kernel)."""
 import ctypes
 import os
 import re
+import types
 
 import pytest
+import torch
 
 from paper_2605_24879_amd import dprc
 
@@ -276,3 +278,26 @@ def test_accountant_entry_points_validation():
     assert L.dprc_pld_fold(P, 10, P, P, P, P, None) == 1                     # even L
     assert L.dprc_pld_delta(P, 11, 1e-3, P, P, 0, P, None) == 1              # no eps
     assert L.dprc_pld_delta(P, 11, 0.0, P, P, 3, P, None) == 1               # h = 0
+
+
+def test_tensors_that_are_not_on_a_gpu_are_refused(monkeypatch):
+    # the binding takes the stream of a tensor's device: a host tensor has none, also where a GPU is current
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 0, raising=False)
+    monkeypatch.setattr(dprc, "_raw_stream", lambda index: 0, raising=False)
+    assert dprc._stream(torch.device("cuda")).value is None and dprc._stream(torch.device("cuda", 0)).value is None
+    with pytest.raises(ValueError):
+        dprc._stream(torch.device("cpu"))
+    monkeypatch.setattr(dprc, "_lib", None)            # nothing may be enqueued: no entry point is looked up
+    monkeypatch.setattr(dprc, "lib", lambda: types.SimpleNamespace(
+        **{n: (lambda *a, n=n: 1 << 20 if n.endswith("_workspace") else pytest.fail(n)) for n in dprc.EXPORTS}))
+    host = torch.zeros(4, 8)
+    for call in (lambda: dprc.dprc_clip_scale(host[0], 1.0), lambda: dprc.dprc_add_noise(host, 1.0, 1.0, 0, 0),
+                 lambda: dprc.dprc_private_adamw(host, host.clone(), host.clone(), host.clone(), 1.0, 1.0, 0, 0, 1.0,
+                                                 1e-3, 0.9, 0.999, 1e-8, 0.0, 1),
+                 lambda: dprc.dprc_envelope_middle(host[0].double(), 4, 3, 5), lambda: dprc.dprc_chi2_cdf(host[0].double(), 4),
+                 lambda: dprc.dprc_probe_bits(0, 0, 0, 0, 32, 4, out=torch.zeros(4, 1, dtype=torch.int32)),
+                 lambda: dprc.dprc_probe_gaussian(0, 0, 8, 4, out=host), lambda: dprc.dprc_pld_step(1.0, 0.1, 0.1, 3, device="cpu"),
+                 lambda: dprc.dprc_norm_hutch([(host[None], host[None], 0)], 4, 0)):
+        with pytest.raises(ValueError):
+            call()
