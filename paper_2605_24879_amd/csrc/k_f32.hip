@@ -60,7 +60,8 @@ __global__ __launch_bounds__(64 * kPfWaves) void project_f32_kernel(ProjectF32Ar
   constexpr int RNB = NB < 4 ? NB : 4;           // column blocks summed per pass over the waves
   float* red = reinterpret_cast<float*>(smem);   // [kPfWaves][RNB][16][17]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, l16 = lane & 15;
-  const int i = blockIdx.y, t0 = 16 * blockIdx.x;
+  const int i = blockIdx.y, t0 = 16 * (int)(blockIdx.z * kFlatGridX + blockIdx.x);
+  if (t0 >= a.T) return;
   const int wpc = a.words_per_chunk;             // a multiple of 4
   const int t = t0 + l16;
   const float* x = a.X + (int64_t)i * a.x_ss + (int64_t)(t < a.T ? t : t0) * a.ldx;
@@ -151,7 +152,8 @@ hipError_t launch_project_f32(ProjectF32Args a, hipStream_t st) {
   const int rnb = std::min(need, 4);
   const size_t lds = std::max((size_t)(a.nz > 0 ? a.nz * (a.words_per_chunk + 1) * 4 : 0),
                               (size_t)kPfWaves * (need > 2 ? 4 : rnb) * 16 * 17 * 4);
-  const dim3 grid((unsigned)ceil_div(a.T, 16), (unsigned)a.B), blk(64 * kPfWaves);
+  const dim3 rows = flat_grid(ceil_div(a.T, 16));
+  const dim3 grid(rows.x, (unsigned)a.B, rows.y), blk(64 * kPfWaves);
   if (need <= 1) DPRC_LAUNCH(project_f32_kernel<1>, grid, blk, lds, st, a);
   else if (need <= 2) DPRC_LAUNCH(project_f32_kernel<2>, grid, blk, lds, st, a);
   else if (need <= 4) DPRC_LAUNCH(project_f32_kernel<4>, grid, blk, lds, st, a);
@@ -176,7 +178,10 @@ __global__ __launch_bounds__(64 * kTfWaves) void tokred_f32_kernel(TokredF32Args
   __shared__ float red[kTfWaves][kTfTile][17];
   __shared__ double dred[kTfWaves];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, l16 = lane & 15;
-  const int j0 = kTfTile * blockIdx.x, c0 = 16 * NB * blockIdx.y, i = blockIdx.z;
+  const int tn = (a.ncols + 16 * NB - 1) / (16 * NB);              // tiles of columns
+  const int jt = (int)(blockIdx.y / tn * kFlatGridX + blockIdx.x), ct = blockIdx.y % tn, i = blockIdx.z;
+  const int j0 = kTfTile * jt, c0 = 16 * NB * ct;
+  if (j0 >= a.n) return;
   const float* xs = a.X + (int64_t)i * a.x_ss + j0 + 4 * l16;
   const float* ys = a.Y + (int64_t)i * a.T * a.ncols;
   int ycol[NB];
@@ -235,7 +240,7 @@ __global__ __launch_bounds__(64 * kTfWaves) void tokred_f32_kernel(TokredF32Args
   if (tid == 0) {
     double s = 0.0;
     for (int w = 0; w < kTfWaves; ++w) s += dred[w];
-    a.tilesq[((int64_t)i * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = s;
+    a.tilesq[((int64_t)i * tn + ct) * ((a.n + kTfTile - 1) / kTfTile) + jt] = s;
   }
 }
 
@@ -249,7 +254,8 @@ int32_t tokred_f32_tiles(int64_t n, int32_t ncols) {
 hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st) {
   if (a.ncols < 1 || (!a.M && !a.tilesq)) return hipErrorInvalidValue;
   const int nb = tokred_f32_nb(a.ncols);
-  const dim3 grid((unsigned)ceil_div(a.n, kTfTile), (unsigned)ceil_div(a.ncols, 16 * nb), (unsigned)a.B);
+  const dim3 rows = flat_grid(ceil_div(a.n, kTfTile));
+  const dim3 grid(rows.x, rows.y * (unsigned)ceil_div(a.ncols, 16 * nb), (unsigned)a.B);
   const dim3 blk(64 * kTfWaves);
   if (nb == 1) DPRC_LAUNCH(tokred_f32_kernel<1>, grid, blk, 0, st, a);
   else if (nb == 2) DPRC_LAUNCH(tokred_f32_kernel<2>, grid, blk, 0, st, a);

@@ -50,12 +50,13 @@ __global__ void gauss_probe_kernel(uint32_t key0, uint32_t key1, uint32_t layer,
 
 // Several layers' columns (an attention block's four launches of 3.5 to 3.9 us become one).
 __global__ __launch_bounds__(256) void gauss_batch_kernel(GaussBatch bt) {
+  const int blk = flat_block();
   int jb = 0;
 #pragma unroll 8
-  for (int q = 1; q < kGaussMaxJobs; ++q) jb += (q < bt.njobs && (int)blockIdx.x >= bt.blk0[q]) ? 1 : 0;
+  for (int q = 1; q < kGaussMaxJobs; ++q) jb += (q < bt.njobs && blk >= bt.blk0[q]) ? 1 : 0;
   const GaussJob& a = bt.job[jb];
   const int nq = a.ld >> 2;                        // ld is a multiple of 128
-  const int64_t idx = (int64_t)((int)blockIdx.x - bt.blk0[jb]) * 256 + threadIdx.x;
+  const int64_t idx = (int64_t)(blk - bt.blk0[jb]) * 256 + threadIdx.x;
   if (idx >= (int64_t)nq * bt.k) return;
   const int j = (int)(idx / nq);
   gauss_quad(bt.key0, bt.key1, a.layer, a.m, a.ld, j, idx - (int64_t)j * nq, a.hi, a.lo, nullptr);
@@ -69,7 +70,7 @@ hipError_t launch_gauss_batch(GaussBatch bt, hipStream_t st) {
     blocks += ceil_div((int64_t)(bt.job[q].ld / 4) * bt.k, 256);
   }
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  DPRC_LAUNCH(gauss_batch_kernel, dim3((unsigned)blocks), dim3(256), 0, st, bt);
+  DPRC_LAUNCH(gauss_batch_kernel, flat_grid(blocks), dim3(256), 0, st, bt);
   return hipGetLastError();
 }
 

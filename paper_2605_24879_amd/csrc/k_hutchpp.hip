@@ -113,7 +113,7 @@ __device__ __forceinline__ void wave_vec_sum(double (&v)[SP], int c_lo, double* 
 __device__ __forceinline__ int qr_job_index(const QrBatch& bt) {
   int jb = 0;
 #pragma unroll
-  for (int q = 1; q < kQrMaxJobs; ++q) jb += (q < bt.njobs && (int)blockIdx.x >= bt.job[q].blk0) ? 1 : 0;
+  for (int q = 1; q < kQrMaxJobs; ++q) jb += (q < bt.njobs && flat_block() >= bt.job[q].blk0) ? 1 : 0;
   return jb;
 }
 
@@ -143,9 +143,10 @@ template <int SP>
 __global__ __launch_bounds__(64) void qr_factor_kernel(QrBatch bt) {
   __shared__ double red[SP * kRedLd];
   __shared__ double tot[SP];
+  if (flat_block() >= bt.blocks) return;
   const QrJob& a = bt.job[qr_job_index(bt)];
   const int level = a.level;
-  const int rel = (int)blockIdx.x - a.blk0;
+  const int rel = flat_block() - a.blk0;
   const int b = rel % a.L.nblk, i = rel / a.L.nblk, lane = threadIdx.x;
   const int s = a.s;
   const QrLevel L = a.L;
@@ -245,9 +246,10 @@ __global__ __launch_bounds__(256) void qr_expand_kernel(QrBatch bt) {
   constexpr int QLd = kQrRows + 1;
   __shared__ double qs[SR * QLd];
   __shared__ uint32_t zw[256 * 4];
+  if (flat_block() >= bt.blocks) return;
   const QrJob& a = bt.job[qr_job_index(bt)];
   const int level = a.level;
-  const int rel = (int)blockIdx.x - a.blk0;
+  const int rel = flat_block() - a.blk0;
   const int b = rel % a.L.nblk, i = rel / a.L.nblk, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int s = a.s;
   const QrLevel L = a.L;
@@ -382,7 +384,7 @@ template <template <int> class K>
 static hipError_t launch_qr_sp(const QrBatch& bt, hipStream_t st) {
   if (bt.s < 1 || bt.s > 32 || bt.r > 256 || bt.njobs < 1 || bt.njobs > kQrMaxJobs || bt.blocks < 1)
     return hipErrorInvalidValue;
-  const dim3 grid((unsigned)bt.blocks), blk((unsigned)K<8>::threads);
+  const dim3 grid = flat_grid(bt.blocks), blk((unsigned)K<8>::threads);
   if (bt.s <= 8) DPRC_LAUNCH(K<8>::fn, grid, blk, 0, st, bt);
   else if (bt.s <= 16) DPRC_LAUNCH(K<16>::fn, grid, blk, 0, st, bt);
   else DPRC_LAUNCH(K<32>::fn, grid, blk, 0, st, bt);

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * kSurvWaves) void pld_survival_kernel(PldArgs a
   __shared__ double tab[kSurvWaves][64][3];      // a wave's next 64 bins: 1/mu, mu/2, weight
   __shared__ double sums[kSurvWaves][kSurvCuts][2];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, cut = lane % kSurvCuts, g = lane / kSurvCuts;
-  const int64_t c = (int64_t)blockIdx.x * kSurvCuts + cut;
+  const int64_t c = (int64_t)flat_block() * kSurvCuts + cut;
   const double t = ((double)(c - a.n) + 0.5) * a.h;
   const bool inside = c < 2 * a.n && t > a.t_min;
   const double u = inside && a.p < 1.0 ? t + log(1.0 / a.p - (1.0 - a.p) / a.p * exp(-t)) : t;
@@ -344,7 +344,7 @@ hipError_t launch_envelope_bins(const double* F, int32_t M, double y_min, double
 }
 
 hipError_t launch_pld_step(const PldArgs& a, hipStream_t st) {
-  DPRC_LAUNCH(pld_survival_kernel, dim3((unsigned)ceil_div(2 * a.n, kSurvCuts)), dim3(64 * kSurvWaves), 0, st, a);
+  DPRC_LAUNCH(pld_survival_kernel, flat_grid(ceil_div(2 * a.n, kSurvCuts)), dim3(64 * kSurvWaves), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   DPRC_LAUNCH(pld_masses_kernel, dim3(kPldParts), dim3(kPldBlock), 0, st, a);

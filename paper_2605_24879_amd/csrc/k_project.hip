@@ -544,12 +544,14 @@ void project_kernel(ProjectArgs a) {
 template <int RB, int NB, int NBD, int LD>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_batch_kernel(ProjectBatch bt) {
+  const int blk = flat_block();
+  if (blk >= bt.blocks) return;
   int jb = 0;
 #pragma unroll
-  for (int q = 1; q < kProjMaxJobs; ++q) jb += (q < bt.njobs && (int)blockIdx.x >= bt.blk0[q]) ? 1 : 0;
+  for (int q = 1; q < kProjMaxJobs; ++q) jb += (q < bt.njobs && blk >= bt.blk0[q]) ? 1 : 0;
   const ProjectArgs& a = bt.job[jb];
   const int gx = a.T_pad / (16 * RB * a.rblocks);
-  const int rel = (int)blockIdx.x - bt.blk0[jb];
+  const int rel = blk - bt.blk0[jb];
   project_dispatch<RB, NB, NBD, LD>(a, rel % gx, rel / gx);
 }
 
@@ -633,9 +635,9 @@ static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
   const bool dense = bt.job[0].nd > 0;
 #define DPRC_PROJECT_BATCH_CASE(NBDV)                                                                             \
   if (load == kLoadVec)                                                                                            \
-    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);       \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
   else                                                                                                             \
-    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny>), dim3(bt.blocks), dim3(kBlock), lds, st, bt);       \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
   return hipGetLastError();
   if (!dense) {
     if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_BATCH_CASE(0) }

@@ -384,7 +384,7 @@ constexpr int kXcdRun = 16;
 template <int NB, int LD, int TT>
 __global__ __launch_bounds__(kBlock * TT) __attribute__((amdgpu_waves_per_eu(kTokWaves<NB, LD>))) void tokred_batch_kernel(TokredBatch bt) {
   constexpr int W = 8 * kXcdRun;
-  const int id = (int)blockIdx.x;
+  const int id = flat_block();
   const int b = bt.job[0].S == 1 ? id / W * W + (id & 7) * kXcdRun + (id % W) / 8 : id;
   if (b >= bt.blocks) return;
   int jb = 0;
@@ -626,7 +626,7 @@ hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
     bt.blk0[j] = bt.blocks;
     bt.blocks += (a.ntiles + tt - 1) / tt * a.S * a.B;
   }
-  const dim3 grid((unsigned)round_up(bt.blocks, 8 * kXcdRun));   // whole windows (see the kernel)
+  const dim3 grid = flat_grid(round_up(bt.blocks, 8 * kXcdRun));   // whole windows (see the kernel)
 #define DPRC_TOKRED_BATCH_LAUNCH(NB, TT)                                                                  \
   if (load == kLoadVec) DPRC_LAUNCH((tokred_batch_kernel<NB, kLoadVec, TT>), grid, dim3(kBlock * TT), 0, st, bt); \
   else if (load == kLoadAny)                                                                                        \

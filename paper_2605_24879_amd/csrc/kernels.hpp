@@ -41,6 +41,17 @@ __host__ __device__ constexpr int lds_swz(int row, int col) { return col ^ (((ro
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
+// The grid of a launch of `blocks` numbered workgroups (flat_block).  A grid dimension takes
+// fewer than 2^32 threads, and a larger one is cut short without an error, so from
+// kFlatGridX workgroups (of at most 1024 threads) on they fill rows of that many.
+constexpr int64_t kFlatGridX = 1 << 21;
+inline dim3 flat_grid(int64_t blocks) {
+  return dim3((unsigned)(blocks < kFlatGridX ? blocks : kFlatGridX), (unsigned)ceil_div(blocks, kFlatGridX));
+}
+
+// The number of this workgroup in a launch over flat_grid (the last row may hold more than there are).
+__device__ __forceinline__ int flat_block() { return (int)(blockIdx.y * (uint32_t)kFlatGridX + blockIdx.x); }
+
 // The load mode (device.hpp) of an operand of B * T token rows of `width` bf16, stride ld,
 // when a workgroup's offsets span `rows` rows.
 inline int load_mode(int vec, int64_t B, int64_t T, int64_t width, int64_t ld, int64_t rows) {
