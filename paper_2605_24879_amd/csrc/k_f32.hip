@@ -45,20 +45,19 @@ __device__ __forceinline__ f4u load4_f32(const float* p, int64_t u, int64_t lim)
 }
 
 // ---- Y = X R ------------------------------------------------------------------------------
-// A workgroup of eight waves owns 16 token rows of one sample; the waves take the 64-column
+// A workgroup of eight waves (fewer: see the launcher) owns 16 token rows of one sample; the waves take the 64-column
 // groups of the width in turn and their partial Y are added in wave order.  The +-1 probe
 // words of a chunk of the width are generated into LDS first.  Bound by reading X (a row is
 // read once) for up to about 50 columns, by the fp32 matrix rate above.  2048 rows of 4096
 // columns and 16 probes took 304 us with one thread per (row, column), 10 us here (3.4 TB/s).
-constexpr int kPfWaves = 8;
 constexpr int kPfWords = 8192;                   // probe words in LDS (32 KB)
 
-template <int NB>
-__global__ __launch_bounds__(64 * kPfWaves) void project_f32_kernel(ProjectF32Args a) {
+template <int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void project_f32_kernel(ProjectF32Args a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   uint32_t* zw = smem;                           // [nz][wpc + 1], later the partial tiles
   constexpr int RNB = NB < 4 ? NB : 4;           // column blocks summed per pass over the waves
-  float* red = reinterpret_cast<float*>(smem);   // [kPfWaves][RNB][16][17]
+  float* red = reinterpret_cast<float*>(smem);   // [NW][RNB][16][17]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, l16 = lane & 15;
   const int i = blockIdx.y, t0 = 16 * (int)(blockIdx.z * kFlatGridX + blockIdx.x);
   if (t0 >= a.T) return;
@@ -85,7 +84,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void project_f32_kernel(ProjectF32Ar
     if (a.nz > 0) {
       __syncthreads();                           // the previous chunk's words are used up
       const int nblk = wpc >> 2;
-      for (int idx = tid; idx < a.nz * nblk; idx += 64 * kPfWaves) {
+      for (int idx = tid; idx < a.nz * nblk; idx += 64 * NW) {
         const int c = idx / nblk, b = idx - c * nblk;
         const uint32_t w0 = (uint32_t)(uc >> 5) + 4u * (uint32_t)b;
         const u32x4 v = a.probe_kind == kProbeRademacher
@@ -96,9 +95,9 @@ __global__ __launch_bounds__(64 * kPfWaves) void project_f32_kernel(ProjectF32Ar
       }
       __syncthreads();
     }
-    for (int gi = wv; gi < ngrp; gi += kPfWaves) {
+    for (int gi = wv; gi < ngrp; gi += NW) {
       const int u0 = uc + 64 * gi;
-      if (gi + kPfWaves < ngrp) load(nxt, u0 + 64 * kPfWaves);
+      if (gi + NW < ngrp) load(nxt, u0 + 64 * NW);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int u = u0 + 16 * q + 4 * g;
@@ -132,51 +131,67 @@ __global__ __launch_bounds__(64 * kPfWaves) void project_f32_kernel(ProjectF32Ar
 #pragma unroll
         for (int e = 0; e < 4; ++e) red[((wv * RNB + nb - n0) * 16 + 4 * g + e) * 17 + l16] = acc[nb][e];
     __syncthreads();
-    for (int idx = tid; idx < RNB * 256; idx += 64 * kPfWaves) {
+    for (int idx = tid; idx < RNB * 256; idx += 64 * NW) {
       const int c = 16 * n0 + idx % (16 * RNB), r = idx / (16 * RNB);
       if (c >= a.ncols || r >= rows) continue;
       const int nb = (idx % (16 * RNB)) >> 4;
       float s = 0.f;
 #pragma unroll
-      for (int w = 0; w < kPfWaves; ++w) s += red[((w * RNB + nb) * 16 + r) * 17 + (c & 15)];
+      for (int w = 0; w < NW; ++w) s += red[((w * RNB + nb) * 16 + r) * 17 + (c & 15)];
       y[(int64_t)r * a.ncols + c] = s;
     }
   }
 }
 
-hipError_t launch_project_f32(ProjectF32Args a, hipStream_t st) {
-  if (a.ncols < 1 || a.ncols > 256 || a.nd + a.nz != a.ncols) return hipErrorInvalidValue;
-  a.words_per_chunk = (int32_t)std::min<int64_t>(round_up(ceil_div(a.m, 32), 4),
-                                                 a.nz > 0 ? std::max(16, (kPfWords / a.nz) & ~15) : 1 << 24);
+template <int NW>
+static hipError_t launch_project_f32_w(const ProjectF32Args& a, hipStream_t st) {
   const int need = (a.ncols + 15) / 16;
-  const int rnb = std::min(need, 4);
   const size_t lds = std::max((size_t)(a.nz > 0 ? a.nz * (a.words_per_chunk + 1) * 4 : 0),
-                              (size_t)kPfWaves * (need > 2 ? 4 : rnb) * 16 * 17 * 4);
+                              (size_t)NW * (need > 2 ? 4 : need) * 16 * 17 * 4);
   const dim3 rows = flat_grid(ceil_div(a.T, 16));
-  const dim3 grid(rows.x, (unsigned)a.B, rows.y), blk(64 * kPfWaves);
-  if (need <= 1) DPRC_LAUNCH(project_f32_kernel<1>, grid, blk, lds, st, a);
-  else if (need <= 2) DPRC_LAUNCH(project_f32_kernel<2>, grid, blk, lds, st, a);
-  else if (need <= 4) DPRC_LAUNCH(project_f32_kernel<4>, grid, blk, lds, st, a);
-  else if (need <= 8) DPRC_LAUNCH(project_f32_kernel<8>, grid, blk, lds, st, a);
-  else DPRC_LAUNCH(project_f32_kernel<16>, grid, blk, lds, st, a);
+  const dim3 grid(rows.x, (unsigned)a.B, rows.y), blk(64 * NW);
+  if (need <= 1) DPRC_LAUNCH((project_f32_kernel<1, NW>), grid, blk, lds, st, a);
+  else if (need <= 2) DPRC_LAUNCH((project_f32_kernel<2, NW>), grid, blk, lds, st, a);
+  else if (need <= 4) DPRC_LAUNCH((project_f32_kernel<4, NW>), grid, blk, lds, st, a);
+  else if (need <= 8) DPRC_LAUNCH((project_f32_kernel<8, NW>), grid, blk, lds, st, a);
+  else DPRC_LAUNCH((project_f32_kernel<16, NW>), grid, blk, lds, st, a);
   return hipGetLastError();
 }
 
+// Samples that share their columns lie one row stride apart, so short ones share workgroups
+// of 16 rows: 3608 one-token samples of 1480 and 8 columns, 350 us in two norm calls of 8
+// probes, take 102 us.  A width of 64 (128) columns occupies one (two) of the waves; from
+// kManyWgs workgroups on the launch fills the GPU without the others (fewer workgroups are
+// faster with all eight: 86 us against 48 for three rows of blocks of 355 tokens).
+constexpr int64_t kManyWgs = 512;
+hipError_t launch_project_f32(ProjectF32Args a, hipStream_t st) {
+  if (a.ncols < 1 || a.ncols > 256 || a.nd + a.nz != a.ncols) return hipErrorInvalidValue;
+  if (a.T % 16 != 0 && (a.nd == 0 || a.r_ss == 0) && (int64_t)a.B * a.T <= (1 << 30)) {
+    a.T *= a.B;
+    a.B = 1;
+  }
+  a.words_per_chunk = (int32_t)std::min<int64_t>(round_up(ceil_div(a.m, 32), 4),
+                                                 a.nz > 0 ? std::max(16, (kPfWords / a.nz) & ~15) : 1 << 24);
+  const bool many = ceil_div(a.T, 16) * a.B >= kManyWgs;
+  if (many && a.m <= 64) return launch_project_f32_w<1>(a, st);
+  if (many && a.m <= 128) return launch_project_f32_w<2>(a, st);
+  return launch_project_f32_w<8>(a, st);
+}
+
 // ---- M = X^T Y ---------------------------------------------------------------------------------
-// A workgroup of eight waves owns 64 result rows (columns of X) and up to 64 result columns
+// A workgroup of eight waves (fewer for short samples) owns 64 result rows (columns of X) and up to 64 result columns
 // of one sample; the waves take the token quads in turn, read both operands straight from
 // global memory in the MFMA layout, and their partial sums are added in wave order.  The
 // result is squared and summed (tilesq) or stored.  Latency-bound at ordinary sizes (512
 // tokens are 16 quads per wave): 125 us with one thread per result, 7 us here for a
 // 1024-wide operand (its 64 workgroups leave most CUs idle) and 9 us for a 4096-wide one.
-constexpr int kTfWaves = 8;
 constexpr int kTfTile = 64;
 
-template <int NB>
-__global__ __launch_bounds__(64 * kTfWaves) void tokred_f32_kernel(TokredF32Args a) {
+template <int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void tokred_f32_kernel(TokredF32Args a) {
   constexpr int U = 4;                           // token quads in flight per wave
-  __shared__ float red[kTfWaves][kTfTile][17];
-  __shared__ double dred[kTfWaves];
+  __shared__ float red[NW][kTfTile][17];
+  __shared__ double dred[NW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, l16 = lane & 15;
   const int tn = (a.ncols + 16 * NB - 1) / (16 * NB);              // tiles of columns
   const int jt = (int)(blockIdx.y / tn * kFlatGridX + blockIdx.x), ct = blockIdx.y % tn, i = blockIdx.z;
@@ -193,12 +208,12 @@ __global__ __launch_bounds__(64 * kTfWaves) void tokred_f32_kernel(TokredF32Args
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[x][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int nq = (a.T + 3) / 4;
-  for (int q0 = wv; q0 < nq; q0 += U * kTfWaves) {
+  for (int q0 = wv; q0 < nq; q0 += U * NW) {
     f4u xv[U];
     float yv[U][NB];
 #pragma unroll
     for (int u = 0; u < U; ++u) {                // tokens past the last add zeros
-      const int t = 4 * (q0 + u * kTfWaves) + g;
+      const int t = 4 * (q0 + u * NW) + g;
       const int64_t tt = t < a.T ? t : 0;
       xv[u] = load4_f32(xs + tt * a.ldx, j0 + 4 * l16, t < a.T ? a.n : 0);
 #pragma unroll
@@ -223,12 +238,12 @@ __global__ __launch_bounds__(64 * kTfWaves) void tokred_f32_kernel(TokredF32Args
 #pragma unroll
       for (int e = 0; e < 4; ++e) red[wv][4 * (4 * g + e) + x][l16] = acc[x][nb][e];
     __syncthreads();
-    for (int idx = tid; idx < kTfTile * 16; idx += 64 * kTfWaves) {
+    for (int idx = tid; idx < kTfTile * min(16, a.ncols - c0 - 16 * nb); idx += 64 * NW) {
       const int jl = idx % kTfTile, cl = idx / kTfTile, c = c0 + 16 * nb + cl, j = j0 + jl;
-      if (c >= a.ncols || j >= a.n) continue;
+      if (j >= a.n) continue;
       float s = 0.f;
 #pragma unroll
-      for (int w = 0; w < kTfWaves; ++w) s += red[w][jl][cl];
+      for (int w = 0; w < NW; ++w) s += red[w][jl][cl];
       if (a.M) a.M[(int64_t)i * a.m_ss + (int64_t)c * a.m_ld + j] = s;
       else sq += (double)s * (double)s;
     }
@@ -239,7 +254,7 @@ __global__ __launch_bounds__(64 * kTfWaves) void tokred_f32_kernel(TokredF32Args
   __syncthreads();
   if (tid == 0) {
     double s = 0.0;
-    for (int w = 0; w < kTfWaves; ++w) s += dred[w];
+    for (int w = 0; w < NW; ++w) s += dred[w];
     a.tilesq[((int64_t)i * tn + ct) * ((a.n + kTfTile - 1) / kTfTile) + jt] = s;
   }
 }
@@ -251,16 +266,29 @@ int32_t tokred_f32_tiles(int64_t n, int32_t ncols) {
   return (int32_t)(ceil_div(n, kTfTile) * ceil_div(ncols, 16 * tokred_f32_nb(ncols)));
 }
 
-hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st) {
-  if (a.ncols < 1 || (!a.M && !a.tilesq)) return hipErrorInvalidValue;
+template <int NW>
+static hipError_t launch_tokred_f32_w(const TokredF32Args& a, hipStream_t st) {
   const int nb = tokred_f32_nb(a.ncols);
   const dim3 rows = flat_grid(ceil_div(a.n, kTfTile));
   const dim3 grid(rows.x, rows.y * (unsigned)ceil_div(a.ncols, 16 * nb), (unsigned)a.B);
-  const dim3 blk(64 * kTfWaves);
-  if (nb == 1) DPRC_LAUNCH(tokred_f32_kernel<1>, grid, blk, 0, st, a);
-  else if (nb == 2) DPRC_LAUNCH(tokred_f32_kernel<2>, grid, blk, 0, st, a);
-  else DPRC_LAUNCH(tokred_f32_kernel<4>, grid, blk, 0, st, a);
+  const dim3 blk(64 * NW);
+  if (nb == 1) DPRC_LAUNCH((tokred_f32_kernel<1, NW>), grid, blk, 0, st, a);
+  else if (nb == 2) DPRC_LAUNCH((tokred_f32_kernel<2, NW>), grid, blk, 0, st, a);
+  else DPRC_LAUNCH((tokred_f32_kernel<4, NW>), grid, blk, 0, st, a);
   return hipGetLastError();
+}
+
+// Short samples leave most of eight waves without token quads, and what is left of their work
+// is the sum over the waves: up to 16 tokens (one step of one wave) a workgroup is one wave,
+// up to 256 two, if there are enough workgroups to fill the GPU without the others.  1979
+// samples of 11 tokens, 4248 > 8, one probe: 507 us with eight waves, 108 with one; 307 of
+// 34 tokens, 2344 > 584, 32 probes: 222 and 121 with two.  At 385 tokens two were 17% slower.
+hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st) {
+  if (a.ncols < 1 || (!a.M && !a.tilesq)) return hipErrorInvalidValue;
+  const bool many = (int64_t)a.B * tokred_f32_tiles(a.n, a.ncols) >= kManyWgs;
+  if (many && a.T <= 16) return launch_tokred_f32_w<1>(a, st);
+  if (many && a.T <= 256) return launch_tokred_f32_w<2>(a, st);
+  return launch_tokred_f32_w<8>(a, st);
 }
 
 // ---- sum_i c_i A_i^T E_i ----------------------------------------------------------------------
@@ -277,7 +305,12 @@ hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st) {
 constexpr int kFK = 32;                          // tokens per slab
 
 // NARROW: operands less than 4 wide (or strides past 32-bit offsets), read by element.
-template <int W, int MW, int NW, int KS, bool NARROW>
+// PACKED, for samples of at most 16 tokens (half a slab): a slab holds several samples, each on
+// as many of its token quads (1, 2 or 4) as it needs.  A sample's sum is still formed by
+// itself and scaled as a whole; rows of samples with factor 0 become zeros.  128 one-token
+// samples of 1024 > 1024: 64 us with one thread per entry, 207 with a slab per sample, 40 here;
+// of 16 tokens 1017, 198 and 142.
+template <int W, int MW, int NW, int KS, bool NARROW, bool PACKED>
 __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args a) {
   constexpr int TM = 16 * W * MW, TN = 16 * W * NW;
   constexpr int NT = 64 * MW * NW * KS;
@@ -288,48 +321,59 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
   __shared__ __attribute__((aligned(16))) float le[2][kFK][TN];
   __shared__ float red[MW * NW * KS][16][16 * W + 1];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, l16 = lane & 15;
-  const int kg = wv / (MW * NW), wi = wv % (MW * NW);
+  const int kg = wv / (MW * NW), wi = wv % (MW * NW), kgu = __builtin_amdgcn_readfirstlane(kg);
   const int tn_n = (a.p + TN - 1) / TN;
   const int d0 = (int)(blockIdx.x / tn_n) * TM, p0 = (int)(blockIdx.x % tn_n) * TN;
   const int wm = (wi / NW) * 16 * W, wn = (wi % NW) * 16 * W;
-  const int sps = (a.T + kFK - 1) / kFK;
+  // PACKED: 1 << lq quads per sample, kFK / 4 >> lq samples per slab
+  const int lq = a.T <= 4 ? 0 : (a.T <= 8 ? 1 : 2), per_slab = (kFK / 4) >> lq;
+  const int sps = PACKED ? (a.B + per_slab - 1) / per_slab : (a.T + kFK - 1) / kFK;
   // piece r of this thread: operand A for r < NA, else E; token row and column of the
   // slab.  A piece that would cross the end of its row starts at width - 4 instead and is
   // shifted down in registers; one past the end is the row's last, and what it brings only
   // reaches entries that are not stored.
-  int prow[NP], pcol[NP], psh[NP];
+  int prow[NP], lrow[NP], pcol[NP], psh[NP], psam[PACKED ? NP : 1];   // prow in memory, lrow in LDS
   int32_t poff[NP];
+  constexpr int kNoRow = 1 << 30;                // an LDS row that no token has
 #pragma unroll
   for (int r = 0; r < NP; ++r) {
     const int id = tid + NT * (r < NA ? r : r - NA), ppr = (r < NA ? TM : TN) / 4;
-    prow[r] = id / ppr;
+    prow[r] = lrow[r] = id / ppr;
     pcol[r] = 4 * (id % ppr);
+    if constexpr (PACKED) {
+      psam[r] = lrow[r] >> (2 + lq);
+      const int t = lrow[r] & ((4 << lq) - 1);
+      prow[r] = t < a.T ? psam[r] * a.T + t : kNoRow;
+    }
     const int room = (r < NA ? a.d - d0 : a.p - p0) - 4;     // the last start of a whole piece
     psh[r] = NARROW ? 0 : min(3, max(0, pcol[r] - room));
-    poff[r] = NARROW ? 0 : 4 * ((int32_t)(prow[r] * (r < NA ? a.lda : a.lde)) + min(pcol[r], room));
+    poff[r] = NARROW ? 0 : 4 * ((int32_t)((prow[r] < kNoRow ? prow[r] : 0) * (r < NA ? a.lda : a.lde)) + min(pcol[r], room));
   }
   f4u ring[2][NP];
+  float fac[2][PACKED ? NP : 1];                 // the factors of the pieces' samples
   int rows[2];                                   // token rows of the slabs in the ring
   // Every step issues the same loads (past the last slab: that slab again), so that the
   // waits on the in-order load counter count exactly.
-  auto gload = [&](f4u (&dst)[NP], int& nrow, int i, int st) __attribute__((always_inline)) {
-    const float* ab = a.A + (int64_t)i * a.a_ss + (int64_t)st * kFK * a.lda + d0;
-    const float* eb = a.E + (int64_t)i * a.e_ss + (int64_t)st * kFK * a.lde + p0;
-    nrow = min(kFK, a.T - st * kFK);
+  auto gload = [&](f4u (&dst)[NP], float (&f)[PACKED ? NP : 1], int& nrow, int i, int st) __attribute__((always_inline)) {
+    const int64_t row0 = PACKED ? (int64_t)st * per_slab * a.T : (int64_t)st * kFK;
+    const float* ab = a.A + (int64_t)i * a.a_ss + row0 * a.lda + d0;
+    const float* eb = a.E + (int64_t)i * a.e_ss + row0 * a.lde + p0;
+    nrow = PACKED ? min(per_slab, a.B - st * per_slab) * a.T : min(kFK, a.T - st * kFK);
 #pragma unroll
     for (int r = 0; r < NP; ++r) {
       const bool ok = prow[r] < nrow;
+      if constexpr (PACKED) f[r] = a.c[min(st * per_slab + psam[r], a.B - 1)];
       if constexpr (NARROW) {
         dst[r] = load4_f32((r < NA ? ab : eb) + (int64_t)(ok ? prow[r] : 0) * (r < NA ? a.lda : a.lde) + pcol[r],
                            (r < NA ? d0 : p0) + pcol[r], ok ? (r < NA ? a.d : a.p) : 0);
       } else {                                   // a row past the sample reads the slab's first
-        const int32_t back = 4 * (int32_t)(prow[r] * (r < NA ? a.lda : a.lde));
+        const int32_t back = 4 * (int32_t)((prow[r] < kNoRow ? prow[r] : 0) * (r < NA ? a.lda : a.lde));
         dst[r] = *reinterpret_cast<const f4u*>(reinterpret_cast<const char*>(r < NA ? ab : eb) +
                                                (ok ? poff[r] : poff[r] - back));
       }
     }
   };
-  auto swrite = [&](const f4u (&src)[NP], int nrow, int buf) __attribute__((always_inline)) {
+  auto swrite = [&](const f4u (&src)[NP], const float (&f)[PACKED ? NP : 1], int nrow, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < NP; ++r) {
       f4u v = src[r];
@@ -337,8 +381,8 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
         if (psh[r] & 1) v = f4u{v[1], v[2], v[3], v[3]};
         if (psh[r] & 2) v = f4u{v[2], v[3], v[3], v[3]};
       }
-      const bool ok = prow[r] < nrow;            // rows past the sample add zeros
-      *reinterpret_cast<float4*>(r < NA ? &la[buf][prow[r]][pcol[r]] : &le[buf][prow[r]][pcol[r]]) =
+      const bool ok = prow[r] < nrow && !(PACKED && f[PACKED ? r : 0] == 0.f);   // rows past the sample add zeros
+      *reinterpret_cast<float4*>(r < NA ? &la[buf][lrow[r]][pcol[r]] : &le[buf][lrow[r]][pcol[r]]) =
           float4{ok ? v[0] : 0.f, ok ? v[1] : 0.f, ok ? v[2] : 0.f, ok ? v[3] : 0.f};
     }
   };
@@ -348,6 +392,7 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
 #pragma unroll
     for (int y = 0; y < W; ++y) acc[x][y] = tot[x][y] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   auto next_sample = [&](int i) {                // first sample >= i with a factor other than zero
+    if (PACKED) return i > 0 ? a.B : 0;          // (all of them in one)
     while (i < a.B && a.c[i] == 0.f) ++i;
     return i;
   };
@@ -359,8 +404,8 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
       i = next_sample(i + 1);
     }
   };
-  auto load_next = [&](f4u (&dst)[NP], int& nrow) __attribute__((always_inline)) {
-    gload(dst, nrow, li, ls);
+  auto load_next = [&](int slot) __attribute__((always_inline)) {
+    gload(ring[slot], fac[slot], rows[slot], li, ls);
     int i = li, st = ls;
     advance(i, st);
     if (i < a.B) {
@@ -380,18 +425,35 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
 #pragma unroll
       for (int y = 0; y < W; ++y) acc[x][y] = mfma_f32(av[x], ev[y], acc[x][y]);
   };
+  auto fold = [&](float f) __attribute__((always_inline)) {          // a sample's sum joins the total
+#pragma unroll
+    for (int x = 0; x < W; ++x)
+#pragma unroll
+      for (int y = 0; y < W; ++y)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          tot[x][y][e] = fmaf(f, acc[x][y][e], tot[x][y][e]);
+          acc[x][y][e] = 0.f;
+        }
+  };
+  // PACKED: after quad ks of this wave, the last of its sample here
+  auto fold_quad = [&](int ks) __attribute__((always_inline)) {
+    const int fq = min(1 << lq, KQ);
+    if (PACKED && ((ks + 1) & (fq - 1)) == 0) fold(a.c[min(cs * per_slab + ((KQ * kgu + ks) >> lq), a.B - 1)]);
+  };
   auto step = [&](auto b) __attribute__((always_inline)) {
     constexpr int buf = decltype(b)::value;
     // ring slot `buf` held the slab now in LDS buffer `buf`; the other slot holds the next
-    load_next(ring[buf], rows[buf]);
+    load_next(buf);
     // the fragments of a quad are read while the one before is multiplied, those of the next
     // slab's first quad (after the step's one barrier) while the last is
 #pragma unroll
     for (int ks = 0; ks + 1 < KQ; ++ks) {
       frag(fa[(ks + 1) & 1], fe[(ks + 1) & 1], buf, ks + 1);
       mm(fa[ks & 1], fe[ks & 1]);
+      fold_quad(ks);
     }
-    swrite(ring[buf ^ 1], rows[buf ^ 1], buf ^ 1);
+    swrite(ring[buf ^ 1], fac[buf ^ 1], rows[buf ^ 1], buf ^ 1);
     __syncthreads();
     if constexpr (KQ % 2 == 0) {
       frag(fa[0], fe[0], buf ^ 1, 0);
@@ -400,24 +462,14 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
       mm(fa[0], fe[0]);
       frag(fa[0], fe[0], buf ^ 1, 0);
     }
-    if (cs + 1 == sps) {                         // the sample's last slab
-      const float f = a.c[ci];
-#pragma unroll
-      for (int x = 0; x < W; ++x)
-#pragma unroll
-        for (int y = 0; y < W; ++y)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            tot[x][y][e] = fmaf(f, acc[x][y][e], tot[x][y][e]);
-            acc[x][y][e] = 0.f;
-          }
-    }
+    if constexpr (PACKED) fold_quad(KQ - 1);
+    else if (cs + 1 == sps) fold(a.c[ci]);       // the sample's last slab
     advance(ci, cs);
   };
   if (ci < a.B) {
-    load_next(ring[0], rows[0]);
-    load_next(ring[1], rows[1]);
-    swrite(ring[0], rows[0], 0);
+    load_next(0);
+    load_next(1);
+    swrite(ring[0], fac[0], rows[0], 0);
     __syncthreads();
     frag(fa[0], fe[0], 0, 0);
     while (ci < a.B) {
@@ -428,8 +480,8 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
   }
   // a lane's entries: rows wm + W (4 g + e) + x, columns wn + W l16 + y of the tile.  Block x
   // of every wave goes through LDS, and the KS sums of an entry are added in order.
-  constexpr int NC = 16 * W / (4 * KS);          // columns per thread and block x
-  const int tw = tid / (64 * KS), tr = tid % (64 * KS) / (4 * KS), tc = NC * (tid % (4 * KS));
+  constexpr int NC = 16 * W / (4 * KS), V = NC < 4 ? NC : 4;   // columns per thread and block x, per store
+  const int tw = tid / (64 * KS), tr = tid % (64 * KS) / (4 * KS), tc = V * (tid % (4 * KS));
   for (int x = 0; x < W; ++x) {
     __syncthreads();
 #pragma unroll
@@ -440,37 +492,50 @@ __global__ __launch_bounds__(64 * MW * NW * KS) void gemm_f32_kernel(GemmF32Args
 #pragma unroll
           for (int e = 0; e < 4; ++e) red[wv][4 * g + e][W * l16 + y] = tot[xx][y][e];
     __syncthreads();
-    const int row = d0 + (tw / NW) * 16 * W + W * tr + x, col = p0 + (tw % NW) * 16 * W + tc;
+    const int row = d0 + (tw / NW) * 16 * W + W * tr + x;
     if (row >= a.d) continue;
-    float* o = a.out + (int64_t)row * a.ldo + col;
 #pragma unroll
-    for (int n = 0; n < NC; ++n) {
-      if (col + n >= a.p) break;
-      float v = red[tw][tr][tc + n];
+    for (int c = tc; c < 16 * W; c += V * 4 * KS) {            // the threads of a row store next to each other
+      const int col = p0 + (tw % NW) * 16 * W + c;
+      float* o = a.out + (int64_t)row * a.ldo + col;
+      typename FVec<V>::type v;
 #pragma unroll
-      for (int q = 1; q < KS; ++q) v += red[q * MW * NW + tw][tr][tc + n];
-      o[n] = a.accumulate ? o[n] + v : v;
+      for (int n = 0; n < V; ++n) {
+        v[n] = red[tw][tr][c + n];
+#pragma unroll
+        for (int q = 1; q < KS; ++q) v[n] += red[q * MW * NW + tw][tr][c + n];
+      }
+      if (col + V <= a.p) {
+        auto* ov = reinterpret_cast<typename FVec<V>::type*>(o);
+        *ov = a.accumulate ? *ov + v : v;
+      } else {
+#pragma unroll
+        for (int n = 0; n < V; ++n)
+          if (col + n < a.p) o[n] = a.accumulate ? o[n] + v[n] : v[n];
+      }
     }
   }
 }
 
 // The largest tile that still gives every CU a workgroup.
-template <bool NARROW>
+template <bool NARROW, bool PACKED>
 static hipError_t launch_gemm_f32_n(const GemmF32Args& a, hipStream_t st) {
   auto tiles = [&](int64_t m, int64_t n) { return ceil_div(a.d, m) * ceil_div(a.p, n); };
   if (tiles(128, 128) >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   if (tiles(128, 128) >= 256)
-    DPRC_LAUNCH((gemm_f32_kernel<4, 2, 2, 2, NARROW>), dim3((unsigned)tiles(128, 128)), dim3(512), 0, st, a);
+    DPRC_LAUNCH((gemm_f32_kernel<4, 2, 2, 2, NARROW, PACKED>), dim3((unsigned)tiles(128, 128)), dim3(512), 0, st, a);
   else if (tiles(64, 64) >= 256)
-    DPRC_LAUNCH((gemm_f32_kernel<4, 1, 1, 4, NARROW>), dim3((unsigned)tiles(64, 64)), dim3(256), 0, st, a);
+    DPRC_LAUNCH((gemm_f32_kernel<4, 1, 1, 4, NARROW, PACKED>), dim3((unsigned)tiles(64, 64)), dim3(256), 0, st, a);
   else
-    DPRC_LAUNCH((gemm_f32_kernel<2, 1, 1, 4, NARROW>), dim3((unsigned)tiles(32, 32)), dim3(256), 0, st, a);
+    DPRC_LAUNCH((gemm_f32_kernel<2, 1, 1, 4, NARROW, PACKED>), dim3((unsigned)tiles(32, 32)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t st) {
   const bool narrow = a.d < 4 || a.p < 4 || std::max(a.lda, a.lde) >= ((int64_t)1 << 23);
-  return narrow ? launch_gemm_f32_n<true>(a, st) : launch_gemm_f32_n<false>(a, st);
+  const bool packed = a.B > 1 && a.T <= 16;
+  if (packed) return narrow ? launch_gemm_f32_n<true, true>(a, st) : launch_gemm_f32_n<false, true>(a, st);
+  return narrow ? launch_gemm_f32_n<true, false>(a, st) : launch_gemm_f32_n<false, false>(a, st);
 }
 
 }  // namespace dprc

@@ -184,6 +184,51 @@ def test_hutch_gaussian_multilayer_accumulate(D):
     assert np.all(_rel(n2.cpu().numpy(), np.array([0.5, 1.0]) + r1 + r2) < NORM_RTOL)
 
 
+# ---- short fp32 samples -----------------------------------------------------------------------
+
+@pytest.mark.parametrize("B,d,p", [(2, 64, 48), (11, 130, 37), (37, 3, 5), (9, 1030, 4100), (700, 72, 8)])
+@pytest.mark.parametrize("T", [1, 3, 4, 5, 8, 9, 13, 16, 17])
+def test_clip_accumulate_short_fp32_samples(D, B, T, d, p):
+    # up to 16 tokens a slab holds several samples (8, 4 or 2); the last slab is ragged, samples with
+    # factor 0 hold infinities, and the result is written and added to
+    A, E = _draw(B, T, d, p, dtype="f32", layer=9)
+    c = torch.rand(B, device="cuda")
+    c[1::4] = 0.0
+    ref = est.clip_accumulate(_np(A), _np(E), _np(c))
+    A[1::4] = float("inf")
+    E[1::4] = float("nan")
+    g = D.dprc_clip_accumulate(A, E, c)
+    base = torch.randn(d, p + 3, device="cuda")
+    h = base.clone()
+    D.dprc_clip_accumulate(A, E, c, grad=h[:, 2:2 + p], accumulate=True)
+    norm = np.linalg.norm(ref)
+    assert np.linalg.norm(g.cpu().numpy() - ref) < 2e-6 * norm
+    err = h[:, 2:2 + p].double().cpu().numpy() - base[:, 2:2 + p].double().cpu().numpy() - ref
+    assert np.linalg.norm(err) < 2e-6 * (norm + base.norm().item())
+    assert torch.equal(h[:, :2], base[:, :2]) and torch.equal(h[:, 2 + p:], base[:, 2 + p:])
+
+
+@pytest.mark.parametrize("B,T,d,p,k", [
+    (600, 1, 70, 9, 5),          # one wave in both kernels, 38 workgroups of rows of several samples
+    (523, 16, 40, 64, 17),       # whole blocks of 16 rows, the widest one-wave projection
+    (520, 17, 130, 65, 33),      # two waves in both, rows of several samples
+    (60, 130, 600, 128, 70),     # two waves, 10 x 2 tiles
+    (600, 257, 8, 129, 4),       # eight waves again
+])
+@pytest.mark.parametrize("probe", ["rademacher", "gaussian", "hutchpp"])
+def test_norms_of_many_short_fp32_samples(D, B, T, d, p, k, probe):
+    A, E = _draw(B, T, d, p, dtype="f32", layer=3)
+    rows = [0, 1, B // 2, B - 1]
+    An, En = _np(A[rows]), _np(E[rows])
+    if probe == "hutchpp":
+        n2, ref = D.dprc_norm_hutchpp([(A, E, 2)], 4, k, 6), est.hutchpp_layer(An, En, 4, k, 6, 2)
+    else:
+        k = min(k, 32) if probe == "gaussian" else k
+        code = D.PROBE_GAUSSIAN if probe == "gaussian" else D.PROBE_RADEMACHER
+        n2, ref = D.dprc_norm_hutch([(A, E, 2)], k, 6, probe=code), est.hutch_layer(An, En, k, 6, 2, probe=probe)
+    assert np.all(_rel(n2[rows].cpu().numpy(), ref) < 2e-5)
+
+
 # ---- rows at any 2-byte alignment -----------------------------------------------------------
 
 def _in_nans(X, pad, lead):
