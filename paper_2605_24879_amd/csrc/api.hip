@@ -882,6 +882,15 @@ void integration_matrix(int n, const double* x, const double* w, double* gi) {
     }
 }
 
+// The constants of a panel of the envelope's quadrature (EnvArgs).
+struct EnvQuadrature {
+  double gx[kEnvNodes], gw[kEnvNodes], gi[kEnvNodes][kEnvNodes];
+  EnvQuadrature() {
+    gauss_legendre(kEnvNodes, gx, gw);
+    integration_matrix(kEnvNodes, gx, gw, &gi[0][0]);
+  }
+};
+
 // Scratch of dprc_norm_hutch_clip_static: one array on every device the library runs
 // on, held until the process ends.  In host code the name `scratch` is a host-side
 // stand-in, not a device address: the address comes from hipGetSymbolAddress, taken
@@ -1499,8 +1508,8 @@ size_t dprc_envelope_middle_workspace(int32_t nx, int32_t d, int32_t n_lambda) {
   if (nx < 1 || nx > 65535 || d < 2 || n_lambda < 1 || n_lambda > 4096) return 0;
   const int64_t ncand = (int64_t)d * (d - 1) / 2 * n_lambda;
   Arena ar(nullptr);
-  ar.take<double>((size_t)nx * env_blocks(ncand));
-  ar.take<int64_t>((size_t)nx * env_blocks(ncand));
+  ar.take<double>((size_t)nx * env_blocks(ncand, n_lambda));
+  ar.take<int64_t>((size_t)nx * env_blocks(ncand, n_lambda));
   return ar.off;
 }
 
@@ -1516,10 +1525,12 @@ dprc_status dprc_envelope_middle(const double* x, int32_t nx, int32_t k, int32_t
   EnvArgs a;
   a.x = x; a.nx = nx; a.k = k; a.d = d; a.n_lambda = n_lambda;
   a.ncand = (int64_t)d * (d - 1) / 2 * n_lambda;
-  gauss_legendre(kEnvNodes, a.gx, a.gw);
-  integration_matrix(kEnvNodes, a.gx, a.gw, &a.gi[0][0]);
+  static const EnvQuadrature quad;               // computed once: 6 us of host time
+  std::memcpy(a.gx, quad.gx, sizeof a.gx);
+  std::memcpy(a.gw, quad.gw, sizeof a.gw);
+  std::memcpy(a.gi, quad.gi, sizeof a.gi);
   Arena ar(ws);
-  const int nblk = env_blocks(a.ncand);
+  const int nblk = env_blocks(a.ncand, n_lambda);
   a.part_v = ar.take<double>((size_t)nx * nblk);
   a.part_c = ar.take<int64_t>((size_t)nx * nblk);
   a.best = best; a.arg = arg;

@@ -33,7 +33,11 @@
 namespace dprc {
 
 constexpr int kEnvBlock = 256;
-constexpr int kEnvLanes = 4;       // lanes per candidate, so that a few thousand candidates still fill the GPU
+// Lanes per candidate: four, so that a few thousand candidates still fill the GPU, unless
+// every form is a single incomplete gamma (lam = 0 only), which four lanes would each compute,
+// in a kernel with room for the quadrature: 1540 such forms at 60 points took 55 us that way,
+// 18 with a lane each and a kernel of their own.
+static int env_lanes(int n_lambda) { return n_lambda > 1 ? 4 : 1; }
 constexpr int kEnvRedBlock = 256;
 
 // log(x / c) for positive normal x and c, given inv = 1 / c: with the e that puts x / (2^e c)
@@ -106,13 +110,19 @@ __device__ double gamma_p(double a, double y) {
   return fmax(0.0, 1.0 - exp(lpre) * h);
 }
 
-// The value is returned to all kEnvLanes consecutive lanes of the candidate; lane `part` of
-// them takes every kEnvLanes-th run of the panels.
+// P((1 - lam)/n2 chi^2(n2) <= x)
+__device__ double second_term_cdf(double x, double n2, double lam) {
+  return gamma_p(n2 / 2.0, x / (2.0 * ((1.0 - lam) / n2)));
+}
+
+// The value is returned to all LANES consecutive lanes of the candidate; lane `part` of
+// them takes every LANES-th run of the panels.
+template <int LANES>
 __device__ double two_level_cdf(double x, int i, int j, double lam, int k, int part, const EnvArgs& g) {
   if (x <= 0.0) return 0.0;
   const double n1 = (double)i * k, n2 = (double)j * k;
   const double b = (1.0 - lam) / n2;
-  if (lam == 0.0) return gamma_p(n2 / 2.0, x / (2.0 * b));
+  if (lam == 0.0) return second_term_cdf(x, n2, lam);
   const double a = lam / n1;
   const double smax = sqrt(x / a), c = sqrt(n1);
   // beyond 7.5 of its centre the chi density of 8 or more degrees is below 1e-15
@@ -140,7 +150,7 @@ __device__ double two_level_cdf(double x, int i, int j, double lam, int k, int p
   const double pw = (thi - tlo) / panels, half = 0.5 * pw;
   // Over this lane's run of panels: the integral of the chi density (dtot), that of the
   // density times the growth of G since the run's start (ptot), and the growth (gtot).
-  const int per = (panels + kEnvLanes - 1) / kEnvLanes;
+  const int per = (panels + LANES - 1) / LANES;
   double dtot = 0.0, ptot = 0.0, gtot = 0.0;
   for (int pn = part * per; pn < min(panels, (part + 1) * per); ++pn) {
     const double mid = tlo + (pn + 0.5) * pw;
@@ -178,7 +188,7 @@ __device__ double two_level_cdf(double x, int i, int j, double lam, int k, int p
   double sum = 0.0;
   const int lane0 = (threadIdx.x & 63) - part;
 #pragma unroll
-  for (int r = 0; r < kEnvLanes; ++r) {            // the runs in order, each from G at its start
+  for (int r = 0; r < LANES; ++r) {                // the runs in order, each from G at its start
     sum += G0 * __shfl(dtot, lane0 + r, 64) + __shfl(ptot, lane0 + r, 64);
     G0 += __shfl(gtot, lane0 + r, 64);
   }
@@ -205,6 +215,7 @@ __device__ __forceinline__ void better(double v, int64_t c, double& bv, int64_t&
   if (v > bv || (v == bv && c < bc)) { bv = v; bc = c; }
 }
 
+template <int LANES>
 __global__ __launch_bounds__(kEnvBlock) __attribute__((amdgpu_waves_per_eu(2))) void env_middle_kernel(EnvArgs a) {
   __shared__ double sv[kEnvBlock];
   __shared__ int64_t sc[kEnvBlock];
@@ -213,12 +224,15 @@ __global__ __launch_bounds__(kEnvBlock) __attribute__((amdgpu_waves_per_eu(2))) 
   double bv = -1.0;
   int64_t bc = INT64_MAX;
   // (the lanes of a candidate share c, so they leave the loop and return early together)
-  for (int64_t c = (int64_t)blockIdx.x * (kEnvBlock / kEnvLanes) + threadIdx.x / kEnvLanes; c < a.ncand;
-       c += (int64_t)gridDim.x * (kEnvBlock / kEnvLanes)) {
+  for (int64_t c = (int64_t)blockIdx.x * (kEnvBlock / LANES) + threadIdx.x / LANES; c < a.ncand;
+       c += (int64_t)gridDim.x * (kEnvBlock / LANES)) {
     int i, j, l;
     candidate(c, a.d, a.n_lambda, i, j, l);
     const double lam = a.n_lambda > 1 ? 0.5 * l / (a.n_lambda - 1) : 0.0;
-    better(two_level_cdf(x, i, j, lam, a.k, threadIdx.x % kEnvLanes, a), c, bv, bc);
+    double v;
+    if constexpr (LANES > 1) v = two_level_cdf<LANES>(x, i, j, lam, a.k, threadIdx.x % LANES, a);
+    else v = second_term_cdf(x, (double)j * a.k, lam);
+    better(v, c, bv, bc);
   }
   sv[threadIdx.x] = bv;
   sc[threadIdx.x] = bc;
@@ -278,11 +292,15 @@ hipError_t launch_chi2_cdf(const double* x, int64_t n, double dof, double scale,
   return hipGetLastError();
 }
 
-int env_blocks(int64_t ncand) { return (int)std::min<int64_t>(2048, ceil_div(ncand, kEnvBlock / kEnvLanes)); }
+int env_blocks(int64_t ncand, int n_lambda) {
+  return (int)std::min<int64_t>(2048, ceil_div(ncand, kEnvBlock / env_lanes(n_lambda)));
+}
 
 hipError_t launch_env_middle(const EnvArgs& a, hipStream_t st) {
-  const int nblk = env_blocks(a.ncand);
-  DPRC_LAUNCH(env_middle_kernel, dim3((unsigned)nblk, (unsigned)a.nx), dim3(kEnvBlock), 0, st, a);
+  const int nblk = env_blocks(a.ncand, a.n_lambda);
+  const dim3 grid((unsigned)nblk, (unsigned)a.nx);
+  if (env_lanes(a.n_lambda) == 4) DPRC_LAUNCH(env_middle_kernel<4>, grid, dim3(kEnvBlock), 0, st, a);
+  else DPRC_LAUNCH(env_middle_kernel<1>, grid, dim3(kEnvBlock), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   DPRC_LAUNCH(env_reduce_kernel, dim3((unsigned)a.nx), dim3(kEnvRedBlock), 0, st, a, nblk);

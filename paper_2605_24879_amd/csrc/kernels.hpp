@@ -315,7 +315,7 @@ struct EnvArgs {
   double* best;           // [nx]
   int32_t* arg;           // [nx][3] or null
 };
-int env_blocks(int64_t ncand);
+int env_blocks(int64_t ncand, int n_lambda);
 hipError_t launch_env_middle(const EnvArgs& a, hipStream_t st);
 hipError_t launch_chi2_cdf(const double* x, int64_t n, double dof, double scale, double* out, hipStream_t st);
 

@@ -59,6 +59,21 @@ def test_middle_region_matches_brute_force(mods, k, d, nl, xs):
         assert abs(ac.two_level_cdf(x, int(i), int(j), float(lam[l]), k) - ref) < 1e-10
 
 
+@pytest.mark.parametrize("k,d,nx", [(1, 2, 1), (4, 17, 60), (32, 60, 7)])
+def test_middle_region_of_single_terms(mods, k, d, nx):
+    # n_lambda = 1: lam = 0 only, one incomplete gamma per form
+    D, _ = mods
+    from scipy import special
+    xs = np.concatenate([[-1.0, 0.0], np.linspace(0.3, 2.5, nx)])
+    best, arg = D.dprc_envelope_middle(_t(xs), k, d, 1)
+    n2 = k * np.arange(1, d)
+    ref = special.gammainc(n2 / 2, np.maximum(xs, 0.0)[:, None] * n2 / 2)
+    assert np.max(np.abs(best.cpu().numpy() - ref.max(axis=1))) < 1e-12
+    i, j, l = arg.cpu().numpy().T
+    assert np.all(l == 0) and np.all(i >= 1) and np.all(i + j <= d)
+    assert np.max(np.abs(ref[np.arange(len(xs)), j - 1] - ref.max(axis=1))) < 1e-12
+
+
 def test_szekely_counterexample_on_gpu(mods):
     # d = 3, k = 1 at x = 1.5: the best two-level form puts 0.7 on one coordinate and 0.15 on each
     # of the others, above the uniform form 0.7877 and every rank-2 form (0.7872)
