@@ -35,8 +35,8 @@ namespace dprc {
 constexpr int kEnvBlock = 256;
 // Lanes per candidate: four, so that a few thousand candidates still fill the GPU, unless
 // every form is a single incomplete gamma (lam = 0 only), which four lanes would each compute,
-// in a kernel with room for the quadrature: 1540 such forms at 60 points took 55 us that way,
-// 18 with a lane each and a kernel of their own.
+// in a kernel with room for the quadrature: 1540 such forms at 60 points took 56 us that way,
+// 20 with a lane each and a kernel of their own.
 static int env_lanes(int n_lambda) { return n_lambda > 1 ? 4 : 1; }
 constexpr int kEnvRedBlock = 256;
 

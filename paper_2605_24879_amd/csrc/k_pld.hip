@@ -237,9 +237,12 @@ __global__ __launch_bounds__(kPldBlock) void pld_masses_kernel(PldArgs a) {
 // The fold reads twice as much as it writes, and one CU streams about 45 GB/s (1.3 MB took
 // 28 us that way), so its sums are split over kFoldParts workgroups.  There is no scratch
 // memory: the partial sums go to the front of q, a second launch turns every other cell
-// out, and a third, of one workgroup, the cells that held them.  Grids too short for that
-// take the second and third kernels' work in one workgroup.
+// out, and a third, of one workgroup, the cells that held them.  Below kFoldWhole cells one
+// workgroup does it all (12001 cells: 11.8 us against 13.3, 2001: 8.0 and 13.7; 20001: 15.5
+// and 13.6).
 constexpr int kFoldParts = 64, kFoldBlock = 256, kFoldHead = 3 * kFoldParts;
+constexpr int64_t kFoldWhole = 15000;
+static_assert(kFoldWhole > kFoldHead, "the partial sums fit the grid");
 
 struct FoldRange {                                    // r[j] sits at cell j - c of the kept grid
   int64_t n, c;
@@ -282,10 +285,10 @@ __global__ __launch_bounds__(kFoldBlock) void pld_fold_sums_kernel(const double*
 
 // head = false: the cells from kFoldHead on, one part per workgroup; head = true: those
 // before it, after every workgroup of the other launch has read the partial sums there.
-__global__ __launch_bounds__(kFoldBlock) void pld_fold_kernel(const double* r, int64_t L, const double* ainf,
+__global__ __launch_bounds__(kPldBlock) void pld_fold_kernel(const double* r, int64_t L, const double* ainf,
                                                               const double* binf, double* q, double* q_inf, bool head,
                                                               bool whole) {
-  __shared__ double red[kFoldBlock / 64];
+  __shared__ double red[kPldBlock / 64];
   __shared__ double part[kFoldHead];
   double s[3] = {0.0, 0.0, 0.0};
   if (whole) {
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(kFoldBlock) void pld_fold_kernel(const double* r, i
     fold_cells(r, L, ainf, binf, s, 0, L, true, q, q_inf);
     return;
   }
-  for (int k = threadIdx.x; k < kFoldHead; k += kFoldBlock) part[k] = q[k];
+  for (int k = threadIdx.x; k < kFoldHead; k += blockDim.x) part[k] = q[k];
   __syncthreads();
   for (int b = 0; b < kFoldParts; ++b)                // every thread, in part order
 #pragma unroll
@@ -353,20 +356,24 @@ hipError_t launch_pld_step(const PldArgs& a, hipStream_t st) {
 
 hipError_t launch_pld_fold(const double* r, int64_t L, const double* ainf, const double* binf, double* q,
                            double* q_inf, hipStream_t st) {
-  const bool whole = L < 4 * kFoldHead;
+  const bool whole = L < kFoldWhole;
   if (!whole) {
     DPRC_LAUNCH(pld_fold_sums_kernel, dim3(kFoldParts), dim3(kFoldBlock), 0, st, r, L, q);
     DPRC_LAUNCH(pld_fold_kernel, dim3(kFoldParts), dim3(kFoldBlock), 0, st, r, L, ainf, binf, q, q_inf, false, false);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  DPRC_LAUNCH(pld_fold_kernel, dim3(1), dim3(kFoldBlock), 0, st, r, L, ainf, binf, q, q_inf, true, whole);
+  DPRC_LAUNCH(pld_fold_kernel, dim3(1), dim3(whole ? kPldBlock : kFoldBlock), 0, st, r, L, ainf, binf, q, q_inf, true,
+              whole);
   return hipGetLastError();
 }
 
 hipError_t launch_pld_delta(const double* q, int64_t L, double h, const double* q_inf, const double* eps,
                             int32_t n_eps, double* delta, hipStream_t st) {
-  DPRC_LAUNCH(pld_delta_kernel, dim3((unsigned)n_eps), dim3(kPldBlock), 0, st, q, L, h, q_inf, eps, delta);
+  // One workgroup per eps: of 1024 threads while a CU has at most two, of 256 where many eps
+  // fill the GPU anyway (1000 eps: 17.8 us on 16383 cells, 24.7 on 39999 and 10.4 on one with
+  // 1024 threads, 8.3, 15.8 and 7.0 with 256; 64 eps on 400001 cells: 36 and 73).
+  DPRC_LAUNCH(pld_delta_kernel, dim3((unsigned)n_eps), dim3(n_eps > 512 ? 256 : kPldBlock), 0, st, q, L, h, q_inf, eps, delta);
   return hipGetLastError();
 }
 

@@ -276,7 +276,7 @@ def test_pld_delta_at_any_cell_width(mods, h):
     assert D.dprc_pld_delta(_t(q), h, _t([qi]), _t([np.nan])).item() == qi
 
 
-@pytest.mark.parametrize("L", [1, 501, 4001])
+@pytest.mark.parametrize("L", [1, 501, 14999, 15001])
 def test_pld_fold_with_the_atom_in_place(mods, L):
     # q_inf may be one of the atoms that the call reads, or both
     D, _ = mods
@@ -296,3 +296,30 @@ def test_pld_fold_with_the_atom_in_place(mods, L):
     assert D.lib().dprc_pld_fold(r.data_ptr(), L, both.data_ptr(), both.data_ptr(), out.data_ptr(), both.data_ptr(),
                                  D._stream(r.device)) == D.SUCCESS
     assert torch.equal(out, half[0]) and torch.equal(both, half[1])
+
+
+@pytest.mark.parametrize("L,n_eps", [(1, 1), (255, 512), (1023, 513), (4097, 700), (16385, 600), (20001, 3)])
+def test_pld_delta_of_few_and_many_eps(mods, L, n_eps):
+    # workgroups of 1024 and 256 threads, runs of 16 cells per thread that end inside the grid
+    D, _ = mods
+    q = np.random.default_rng(L).random(L)
+    q /= 1.25 * q.sum()
+    qi, h = 1.0 - q.sum(), 7.0 / L
+    grid = (np.arange(L) - (L - 1) // 2) * h
+    eps = np.linspace(-3.6, 3.6, n_eps)
+    got = D.dprc_pld_delta(_t(q), h, _t([qi]), _t(eps)).cpu().numpy()
+    assert np.max(np.abs(got - [ac.delta_of_eps(grid, q, qi, e) for e in eps])) < 1e-12
+
+
+@pytest.mark.parametrize("L", [1, 191, 193, 14999, 15001, 40001])
+def test_pld_fold_on_either_side_of_one_workgroup(mods, L):
+    D, _ = mods
+    r = np.random.default_rng(L).standard_normal(2 * L - 1)          # negatives are clipped
+    q, qi = D.dprc_pld_fold(_t(r), L, _t([0.1]), _t([0.2]))
+    v, c = np.maximum(r, 0.0), (L - 1) // 2
+    ref = v[c:c + L].copy()
+    ref[0] += v[:c].sum()
+    inf0 = 1.0 - 0.9 * 0.8
+    scale = (1.0 - inf0) / v.sum() if v.sum() > 0 else 0.0
+    assert np.max(np.abs(q.cpu().numpy() - ref * scale)) < 1e-13
+    assert abs(qi.item() - (inf0 + v[c + L:].sum() * scale)) < 1e-13

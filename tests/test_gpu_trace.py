@@ -50,7 +50,7 @@ def _one_by_one(j):
 
 
 CALLS = {
-    "fold": (lambda D: D.dprc_pld_fold(torch.rand(8001, dtype=torch.float64, device="cuda"), 4001, _f64(0.1), _f64(0.1)),
+    "fold": (lambda D: D.dprc_pld_fold(torch.rand(80001, dtype=torch.float64, device="cuda"), 40001, _f64(0.1), _f64(0.1)),
              ["pld"] * 3),
     "fold, one workgroup": (lambda D: D.dprc_pld_fold(_f64(0.2, 0.3, 0.1), 1, _f64(0.1), _f64(0.1)), ["pld"]),
     "step": (lambda D: D.dprc_pld_step(1.0, 0.1, 0.01, 300), ["pld"] * 2),
