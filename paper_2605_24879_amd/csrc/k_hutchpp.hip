@@ -143,7 +143,7 @@ template <int SP>
 __global__ __launch_bounds__(64) void qr_factor_kernel(QrBatch bt) {
   __shared__ double red[SP * kRedLd];
   __shared__ double tot[SP];
-  if (flat_block() >= bt.blocks) return;
+  if (blockIdx.y > 0 && flat_block() >= bt.blocks) return;     // (the first row is full)
   const QrJob& a = bt.job[qr_job_index(bt)];
   const int level = a.level;
   const int rel = flat_block() - a.blk0;
@@ -236,17 +236,20 @@ __global__ __launch_bounds__(64) void qr_factor_kernel(QrBatch bt) {
 // waves draw the residual probes meanwhile, and all four then form C_b on the fp64 matrix
 // cores (16x16x4 MFMA: A[c][j] from the block's Q in LDS, B[j][q] = +-1 from the probe bits;
 // D register e of lane l is row 4 e + l / 16, column l % 16).  One wave adding 128 signed rows
-// per entry took 37 of the 49 us of a level-0 launch.
+// per entry took 37 of the 49 us of a level-0 launch.  Four waves a workgroup while the CUs
+// hold them all at once (four, two or one each by registers); beyond that the idle waves'
+// registers keep others out, and a workgroup is one wave: 29260 blocks of 16 columns took
+// 1177 us with a wave adding signed rows, 1954 with four waves each, 960 with one.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
-template <int SP>
-__global__ __launch_bounds__(256) void qr_expand_kernel(QrBatch bt) {
+template <int SP, int NT>
+__global__ __launch_bounds__(NT) void qr_expand_kernel(QrBatch bt) {
   __shared__ double red[SP * kRedLd];
   __shared__ double tot[SP];
   constexpr int SR = SP < 16 ? 16 : SP;           // rows of Q in LDS, whole blocks of 16
   constexpr int QLd = kQrRows + 1;
   __shared__ double qs[SR * QLd];
   __shared__ uint32_t zw[256 * 4];
-  if (flat_block() >= bt.blocks) return;
+  if (blockIdx.y > 0 && flat_block() >= bt.blocks) return;     // (the first row is full)
   const QrJob& a = bt.job[qr_job_index(bt)];
   const int level = a.level;
   const int rel = flat_block() - a.blk0;
@@ -329,9 +332,10 @@ __global__ __launch_bounds__(256) void qr_expand_kernel(QrBatch bt) {
         }
       }
     }
-  } else if (level == 0) {
+  }
+  if (level == 0 && (NT == 64 || wv > 0)) {
     // probe words of rows b*128 .. b*128+127 (one Philox block per column)
-    for (int cc = (int)threadIdx.x - 64; cc < a.r; cc += 192) {
+    for (int cc = (int)threadIdx.x - (NT > 64 ? 64 : 0); cc < a.r; cc += NT > 64 ? NT - 64 : 64) {
       const u32x4 v = rademacher_block(a.key0, a.key1, a.layer, kStreamProbe, (uint32_t)b, (uint32_t)cc);
       zw[cc * 4 + 0] = v.x; zw[cc * 4 + 1] = v.y; zw[cc * 4 + 2] = v.z; zw[cc * 4 + 3] = v.w;
     }
@@ -342,7 +346,7 @@ __global__ __launch_bounds__(256) void qr_expand_kernel(QrBatch bt) {
   double* cp = a.Cpart + ((int64_t)i * L.nblk + b) * s * a.r;
   const int g = lane >> 4, l16 = lane & 15;
   const int nq = (a.r + 15) / 16, nblocks = (s + 15) / 16 * nq;
-  for (int e = wv; e < nblocks; e += 4) {
+  for (int e = wv; e < nblocks; e += NT / 64) {
     const int c0 = 16 * (e / nq), q0 = 16 * (e % nq);
     const double* qa = qs + (c0 + l16) * QLd + g;
     const uint32_t* zq = zw + 4 * min(q0 + l16, a.r - 1);
@@ -380,29 +384,33 @@ int32_t qr_levels(int64_t m, int s, int32_t rows[kQrMaxLevels], int32_t nblk[kQr
   return n;
 }
 
-template <template <int> class K>
-static hipError_t launch_qr_sp(const QrBatch& bt, hipStream_t st) {
-  if (bt.s < 1 || bt.s > 32 || bt.r > 256 || bt.njobs < 1 || bt.njobs > kQrMaxJobs || bt.blocks < 1)
-    return hipErrorInvalidValue;
-  const dim3 grid = flat_grid(bt.blocks), blk((unsigned)K<8>::threads);
-  if (bt.s <= 8) DPRC_LAUNCH(K<8>::fn, grid, blk, 0, st, bt);
-  else if (bt.s <= 16) DPRC_LAUNCH(K<16>::fn, grid, blk, 0, st, bt);
-  else DPRC_LAUNCH(K<32>::fn, grid, blk, 0, st, bt);
+static bool qr_batch_ok(const QrBatch& bt) {
+  return bt.s >= 1 && bt.s <= 32 && bt.r <= 256 && bt.njobs >= 1 && bt.njobs <= kQrMaxJobs && bt.blocks >= 1;
+}
+
+template <int NT>
+static hipError_t launch_qr_expand_t(const QrBatch& bt, hipStream_t st) {
+  const dim3 grid = flat_grid(bt.blocks), blk(NT);
+  if (bt.s <= 8) DPRC_LAUNCH((qr_expand_kernel<8, NT>), grid, blk, 0, st, bt);
+  else if (bt.s <= 16) DPRC_LAUNCH((qr_expand_kernel<16, NT>), grid, blk, 0, st, bt);
+  else DPRC_LAUNCH((qr_expand_kernel<32, NT>), grid, blk, 0, st, bt);
   return hipGetLastError();
 }
-template <int SP>
-struct QrFactorK {
-  static constexpr auto fn = qr_factor_kernel<SP>;
-  static constexpr int threads = 64;
-};
-template <int SP>
-struct QrExpandK {
-  static constexpr auto fn = qr_expand_kernel<SP>;
-  static constexpr int threads = 256;
-};
 
-hipError_t launch_qr_factor(const QrBatch& bt, hipStream_t st) { return launch_qr_sp<QrFactorK>(bt, st); }
-hipError_t launch_qr_expand(const QrBatch& bt, hipStream_t st) { return launch_qr_sp<QrExpandK>(bt, st); }
+hipError_t launch_qr_factor(const QrBatch& bt, hipStream_t st) {
+  if (!qr_batch_ok(bt)) return hipErrorInvalidValue;
+  const dim3 grid = flat_grid(bt.blocks), blk(64);
+  if (bt.s <= 8) DPRC_LAUNCH(qr_factor_kernel<8>, grid, blk, 0, st, bt);
+  else if (bt.s <= 16) DPRC_LAUNCH(qr_factor_kernel<16>, grid, blk, 0, st, bt);
+  else DPRC_LAUNCH(qr_factor_kernel<32>, grid, blk, 0, st, bt);
+  return hipGetLastError();
+}
+
+hipError_t launch_qr_expand(const QrBatch& bt, hipStream_t st) {
+  if (!qr_batch_ok(bt)) return hipErrorInvalidValue;
+  return bt.blocks <= (bt.s <= 8 ? 1024 : (bt.s <= 16 ? 512 : 256)) ? launch_qr_expand_t<256>(bt, st)
+                                                                   : launch_qr_expand_t<64>(bt, st);
+}
 
 // ---- finalize -----------------------------------------------------------------------------------------
 // A workgroup takes 32 rows j of U | W_P; its threads are (row, column group): group

@@ -229,6 +229,19 @@ def test_norms_of_many_short_fp32_samples(D, B, T, d, p, k, probe):
     assert np.all(_rel(n2[rows].cpu().numpy(), ref) < 2e-5)
 
 
+# ---- routes of batched bf16 launches -----------------------------------------------------------
+
+@pytest.mark.parametrize("s,r", [(4, 5), (5, 200), (16, 33), (32, 64)])
+def test_hutchpp_expansions_of_one_and_four_waves(D, s, r):
+    # 2 blocks of rows per sample: 1200 workgroups of one wave, 120 of four
+    A, E = _draw(600, 9, 24, 200, layer=830)
+    n2 = D.dprc_norm_hutchpp([(A, E, 3)], s, r, 8)
+    few = D.dprc_norm_hutchpp([(A[:60], E[:60], 3)], s, r, 8)
+    assert torch.equal(n2[:60], few)
+    ref = est.hutchpp_layer(_np(A[-2:]), _np(E[-2:]), s, r, 8, 3)
+    assert np.all(_rel(n2[-2:].cpu().numpy(), ref) < NORM_RTOL)
+
+
 # ---- rows at any 2-byte alignment -----------------------------------------------------------
 
 def _in_nans(X, pad, lead):
