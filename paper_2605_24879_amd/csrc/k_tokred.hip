@@ -602,23 +602,52 @@ hipError_t launch_tokred_sample(const TokredArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Fewest 64-token stages for two tiles per workgroup up to 64 columns: a pair halves the reads of
+// Y, but its workgroups take twice the time to start and finish (four layers of 2944 columns
+// in pairs of 32 probes each: 495 us either way at 64 samples of 2048 tokens, 291 in pairs and
+// 279 without at 1024, 323 and 264 at 318 samples of 64).
+constexpr int64_t kPairStages = 32;
+// Workgroups from which on a job of one tile per workgroup leaves its batch: the batch's look
+// their job up first, which many short ones notice (401 samples of 30 tokens, 2888 columns:
+// 104 us in a batch of one, 83 alone; jobs of 1024 to 4096 workgroups gain less than a launch
+// costs).
+constexpr int64_t kOwnLaunchWgs = 4096;
+
 hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st) {
   if (bt.njobs < 1 || bt.njobs > kTokMaxJobs) return hipErrorInvalidValue;
   const int nb = bt.job[0].ncols_pad / 16;
   int load = kLoadVec;
   bool pairs = nb % 2 == 0;
-  int64_t pair_blocks = 0;
+  int64_t pair_blocks = 0, work = 0, stages = 1 << 30;
   for (int j = 0; j < bt.njobs; ++j) {
     const TokredArgs& a = bt.job[j];
     if (a.ncols_pad != bt.job[0].ncols_pad) return hipErrorInvalidValue;   // one instantiation
     load = std::min(load, load_mode(a.vec, a.B, a.T, a.n, a.ldx, kStage));
     pairs = pairs && a.S == 1 && a.mode == 0;
     pair_blocks += (int64_t)(a.ntiles + 1) / 2 * a.S * a.B;
+    work += (int64_t)a.ntiles * a.S * a.B;
+    stages = std::min<int64_t>(stages, a.stages_per_split);
   }
-  // Two tiles per workgroup: up to 64 columns in unsplit squared-norm launches; above 64
+  // Two tiles per workgroup: up to 64 columns in unsplit squared-norm launches of at least
+  // kPairStages stages whose tiles mostly have a second one; above 64
   // columns, where one workgroup's LDS leaves room for no second one in a CU (92 KB of it
   // at 96 columns), as soon as the pairs alone give every CU a workgroup.
   if (nb > 4) pairs = pair_blocks >= 256;
+  else if (stages < kPairStages || 4 * work < 7 * pair_blocks) pairs = false;
+  if (nb <= 4 && !pairs) {                          // large jobs take launches of their own
+    int n = 0;
+    for (int j = 0; j < bt.njobs; ++j) {
+      const TokredArgs& a = bt.job[j];
+      if ((int64_t)a.ntiles * a.S * a.B < kOwnLaunchWgs) {
+        bt.job[n++] = a;
+        continue;
+      }
+      const hipError_t e = launch_tokred(a, st);
+      if (e != hipSuccess) return e;
+    }
+    if (n == 0) return hipSuccess;
+    bt.njobs = n;
+  }
   const int tt = pairs && load != kLoadElem ? 2 : 1;  // (element loads: one tile only)
   bt.blocks = 0;
   for (int j = 0; j < bt.njobs; ++j) {

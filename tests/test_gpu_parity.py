@@ -231,6 +231,26 @@ def test_norms_of_many_short_fp32_samples(D, B, T, d, p, k, probe):
 
 # ---- routes of batched bf16 launches -----------------------------------------------------------
 
+@pytest.mark.parametrize("B,T,d,k,probe", [
+    (1500, 3, 384, 24, "rademacher"),     # 4500 workgroups of a tile: launches of their own
+    (1500, 3, 384, 24, "gaussian"),
+    (1300, 70, 264, 8, "rademacher"),     # two stages, 16 columns
+    (128, 2048, 896, 32, "rademacher"),   # 7 tiles in 4 pairs, 32 stages
+    (128, 1985, 640, 32, "gaussian"),     # 5 tiles would leave 3 pairs half empty
+    (128, 1984, 896, 40, "rademacher"),   # 31 stages
+])
+def test_batched_reductions_of_many_samples(D, B, T, d, k, probe):
+    code = D.PROBE_GAUSSIAN if probe == "gaussian" else D.PROBE_RADEMACHER
+    pairs = [_draw(B, T, d, 40 + 8 * j, layer=820 + j) + (j,) for j in range(2)]
+    per = torch.zeros(2, B, device="cuda")
+    n2 = D.dprc_norm_hutch(pairs, k, 5, probe=code, n2_layers=per)
+    rows = [0, B // 2, B - 1]
+    for A, E, j in pairs:
+        ref = est.hutch_layer(_np(A[rows]), _np(E[rows]), k, 5, j, probe=probe)
+        assert np.all(_rel(per[j][rows].cpu().numpy(), ref) < NORM_RTOL)
+    assert np.all(_rel(n2.cpu().numpy(), per.sum(0).cpu().numpy()) < 1e-6)
+
+
 @pytest.mark.parametrize("s,r", [(4, 5), (5, 200), (16, 33), (32, 64)])
 def test_hutchpp_expansions_of_one_and_four_waves(D, s, r):
     # 2 blocks of rows per sample: 1200 workgroups of one wave, 120 of four
