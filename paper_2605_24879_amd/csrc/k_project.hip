@@ -46,8 +46,11 @@ struct PInt {
   static constexpr int value = V;
 };
 
-// NBD: NB when the columns are dense, 0 when they are probes.
-template <int RB, int NB, int NBD, int LD>
+// NBD: NB when the columns are dense, 0 when they are probes.  ONE (dense): every row is one
+// stage, and nothing is read ahead.  The general form reads the fragments of R of two more
+// stages, which workgroups this short wait for: 2 x 1721 samples of 466 tokens, 96 and 8
+// columns, 32 probes took 941 us with it and take 372.
+template <int RB, int NB, int NBD, int LD, bool ONE>
 __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int by) {
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   constexpr bool DENSE = NBD > 0;
@@ -186,7 +189,8 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
           const bool isd = 16 * nb + l16 < a.nd;
           bh = select4(isd, dh[4 * nb + kb], bh);
           bl = select4(isd, dl[4 * nb + kb], bl);
-        } else {
+        } else if (a.nz > 0) {                     // (always true: without the branch every column's words are read
+                                                   // ahead, 294 registers at 200 columns: one wave, 20% slower)
           const uint32_t word = zw[zrow[nb] + w];
           bh = expand_signs(__builtin_amdgcn_perm(word, word, psel), zmask[nb], zone[nb]);
         }
@@ -206,6 +210,13 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
     const int s0 = uc / kProjStage;
     const int nst = (col_end - uc + kProjStage - 1) / kProjStage;
     uint4 ring[P][NL], rdh[P][ND], rdl[P][ND];
+    if constexpr (ONE) {
+      gload(ring[0], s0, col_end);
+      rload(rdh[0], rdl[0], s0, col_end);
+      to_lds(ring[0], s0);
+      mult(s0, uc, rdh[0], rdl[0]);
+      break;
+    }
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       gload(ring[q], s0 + q, q < nst ? col_end : 0);
@@ -527,32 +538,32 @@ __device__ __forceinline__ void project_rows_body(const ProjectArgs& a, int bx, 
 template <int RB, int NB, int NBD, int LD>
 constexpr bool kProjRows = NBD == 0 && LD == kLoadVec && RB <= 2 && RB * NB <= 4;
 
-template <int RB, int NB, int NBD, int LD>
+template <int RB, int NB, int NBD, int LD, bool ONE>
 __device__ __forceinline__ void project_dispatch(const ProjectArgs& a, int bx, int by) {
   if constexpr (kProjRows<RB, NB, NBD, LD>) project_rows_body<RB, NB>(a, bx, by);
-  else project_body<RB, NB, NBD, LD>(a, bx, by);
+  else project_body<RB, NB, NBD, LD, ONE>(a, bx, by);
 }
 
-template <int RB, int NB, int NBD, int LD>
+template <int RB, int NB, int NBD, int LD, bool ONE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_kernel(ProjectArgs a) {
-  project_dispatch<RB, NB, NBD, LD>(a, blockIdx.x, blockIdx.y);
+  project_dispatch<RB, NB, NBD, LD, ONE>(a, blockIdx.x, blockIdx.y);
 }
 
 // Projections of several layers in one launch (same instantiation): block (x, sample) of
 // job j at blk0[j] + sample * (T_pad / (16 RB rblocks)) + x.
-template <int RB, int NB, int NBD, int LD>
+template <int RB, int NB, int NBD, int LD, bool ONE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_batch_kernel(ProjectBatch bt) {
   const int blk = flat_block();
-  if (blk >= bt.blocks) return;
+  if (blockIdx.y > 0 && blk >= bt.blocks) return;  // (the first row is full)
   int jb = 0;
 #pragma unroll
   for (int q = 1; q < kProjMaxJobs; ++q) jb += (q < bt.njobs && blk >= bt.blk0[q]) ? 1 : 0;
   const ProjectArgs& a = bt.job[jb];
   const int gx = a.T_pad / (16 * RB * a.rblocks);
   const int rel = blk - bt.blk0[jb];
-  project_dispatch<RB, NB, NBD, LD>(a, rel % gx, rel / gx);
+  project_dispatch<RB, NB, NBD, LD, ONE>(a, rel % gx, rel / gx);
 }
 
 template <int RB, int NB>
@@ -633,16 +644,19 @@ static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
     bt.blocks += (bt.job[j].T_pad / (16 * RB * bt.job[j].rblocks)) * bt.job[j].B;
   }
   const bool dense = bt.job[0].nd > 0;
-#define DPRC_PROJECT_BATCH_CASE(NBDV)                                                                             \
+#define DPRC_PROJECT_BATCH_CASE(NBDV, ONEV)                                                                             \
   if (load == kLoadVec)                                                                                            \
-    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec, ONEV>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
   else                                                                                                             \
-    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny, ONEV>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
   return hipGetLastError();
   if (!dense) {
-    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_BATCH_CASE(0) }
-  } else {
-    if constexpr (kProjDense<RB, NB>) { DPRC_PROJECT_BATCH_CASE(NB) }
+    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_BATCH_CASE(0, false) }
+  } else if constexpr (kProjDense<RB, NB>) {
+    bool one = true;
+    for (int j = 0; j < bt.njobs; ++j) one = one && bt.job[j].m <= kProjStage;
+    if (one) { DPRC_PROJECT_BATCH_CASE(NB, true) }
+    DPRC_PROJECT_BATCH_CASE(NB, false)
   }
 #undef DPRC_PROJECT_BATCH_CASE
   return hipErrorInvalidValue;
@@ -669,16 +683,19 @@ hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st
         a.words_per_chunk % 16 != 0 || a.nd > a.ncols_pad || a.T_pad % rows_per_wg != 0)
       return hipErrorInvalidValue;
   }
-  // a job that needs element loads sends every job to a launch of its own
+  // jobs that need element loads take launches of their own
+  int n = 0;
   for (int j = 0; j < bt.njobs; ++j) {
     const ProjectArgs& a = bt.job[j];
-    if (load_mode(a.vec, a.B, a.T, a.m, a.ldx, rows_per_wg) != kLoadElem) continue;
-    for (int q = 0; q < bt.njobs; ++q) {
-      const hipError_t e = launch_project(bt.job[q], rows_per_wg, st);
-      if (e != hipSuccess) return e;
+    if (load_mode(a.vec, a.B, a.T, a.m, a.ldx, rows_per_wg) != kLoadElem) {
+      bt.job[n++] = a;
+      continue;
     }
-    return hipSuccess;
+    const hipError_t e = launch_project(a, rows_per_wg, st);
+    if (e != hipSuccess) return e;
   }
+  if (n == 0) return hipSuccess;
+  bt.njobs = n;
   switch (rb) {
     case 1: return launch_batch_rb<1>(bt, st);
     case 2: return launch_batch_rb<2>(bt, st);
@@ -693,19 +710,20 @@ static hipError_t launch_rb_nb(ProjectArgs a, hipStream_t st) {
   const int load = plan_rblocks<RB, NB>(&a, 1);
   const size_t lds = project_lds<RB, NB>(a);
   dim3 grid((unsigned)(a.T_pad / (16 * RB * a.rblocks)), (unsigned)a.B);
-#define DPRC_PROJECT_CASE(NBDV)                                                                   \
+#define DPRC_PROJECT_CASE(NBDV, ONEV)                                                                   \
   if (load == kLoadVec)                                                                              \
-    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadVec>), grid, dim3(kBlock), lds, st, a);          \
+    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadVec, ONEV>), grid, dim3(kBlock), lds, st, a);          \
   else if (load == kLoadAny)                                                                        \
-    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadAny>), grid, dim3(kBlock), lds, st, a);          \
+    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadAny, ONEV>), grid, dim3(kBlock), lds, st, a);          \
   else                                                                                              \
-    if constexpr (RB == 1) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadElem>), grid, dim3(kBlock), lds, st, a); \
+    if constexpr (RB == 1) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadElem, ONEV>), grid, dim3(kBlock), lds, st, a); \
     else return hipErrorInvalidValue;                                                               \
   return hipGetLastError();
   if (a.nd == 0) {
-    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_CASE(0) }
-  } else {
-    if constexpr (kProjDense<RB, NB>) { DPRC_PROJECT_CASE(NB) }
+    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_CASE(0, false) }
+  } else if constexpr (kProjDense<RB, NB>) {
+    if (a.m <= kProjStage) { DPRC_PROJECT_CASE(NB, true) }
+    DPRC_PROJECT_CASE(NB, false)
   }
 #undef DPRC_PROJECT_CASE
   return hipErrorInvalidValue;

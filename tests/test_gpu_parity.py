@@ -231,6 +231,22 @@ def test_norms_of_many_short_fp32_samples(D, B, T, d, p, k, probe):
 
 # ---- routes of batched bf16 launches -----------------------------------------------------------
 
+@pytest.mark.parametrize("probe,k", [("rademacher", 48), ("gaussian", 9), ("gaussian", 32)])
+def test_batched_layers_of_every_kind_match_calls_of_one(D, probe, k):
+    # one call over layers whose projections take element loads (fewer than 8 elements), any
+    # alignment, rows of one 512-column stage and more than one
+    code = D.PROBE_GAUSSIAN if probe == "gaussian" else D.PROBE_RADEMACHER
+    B, T = 2, 2
+    widths = [(3, 1), (90, 1), (40, 64), (56, 512), (9, 513), (24, 1030), (5, 2)]
+    pairs = [_draw(B, T, d, p, layer=800 + j) + (j,) for j, (d, p) in enumerate(widths)]
+    per = torch.zeros(len(pairs), B, device="cuda")
+    D.dprc_norm_hutch(pairs, k, 5, probe=code, n2_layers=per)
+    for j, q in enumerate(pairs):
+        assert torch.equal(per[j], D.dprc_norm_hutch([q], k, 5, probe=code)), widths[j]
+        ref = est.hutch_layer(_np(q[0]), _np(q[1]), k, 5, j, probe=probe)
+        assert np.all(_rel(per[j].cpu().numpy(), ref) < NORM_RTOL)
+
+
 @pytest.mark.parametrize("B,T,d,k,probe", [
     (1500, 3, 384, 24, "rademacher"),     # 4500 workgroups of a tile: launches of their own
     (1500, 3, 384, 24, "gaussian"),
