@@ -46,11 +46,15 @@ struct PInt {
   static constexpr int value = V;
 };
 
-// NBD: NB when the columns are dense, 0 when they are probes.  ONE (dense): every row is one
+// NBD: NB when the columns are dense, 0 when they are probes.  LEAN, of sign columns: every
+// column's probe words are read at their use and not ahead, 242 registers at 256 columns instead
+// of 294, so that two workgroups fit a CU where its LDS holds two (200 columns, 110 samples of
+// 2028 tokens, 280 wide: 326 us in lean form, 455 in the other; 256 columns, where it holds
+// one: 591 and 458; 32 workgroups, 8192 wide: 170 and 126).  LEAN, of dense columns: every row is one
 // stage, and nothing is read ahead.  The general form reads the fragments of R of two more
 // stages, which workgroups this short wait for: 2 x 1721 samples of 466 tokens, 96 and 8
-// columns, 32 probes took 941 us with it and take 372.
-template <int RB, int NB, int NBD, int LD, bool ONE>
+// columns, 32 probes took 941 us with it and take 394.
+template <int RB, int NB, int NBD, int LD, bool LEAN>
 __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int by) {
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   constexpr bool DENSE = NBD > 0;
@@ -68,9 +72,6 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
   uint16_t* xt = reinterpret_cast<uint16_t*>(region) + wv * (16 * RB * kProjSlice);
   float* red = reinterpret_cast<float*>(region);
   constexpr int RS = 16 * NB + 4;                                 // padded row of a reduction slot
-
-  if (a.zero_ptr != nullptr && bx == 0 && by == 0)
-    for (int idx = tid; idx < a.zero_count; idx += kBlock) a.zero_ptr[idx] = 0u;
 
   // loads: lane -> row 4j + lane/16 of the tile (j = load index), 16-byte piece
   // p = (lane%16) ^ row of its slice, stored at LDS slot lane%16
@@ -189,8 +190,7 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
           const bool isd = 16 * nb + l16 < a.nd;
           bh = select4(isd, dh[4 * nb + kb], bh);
           bl = select4(isd, dl[4 * nb + kb], bl);
-        } else if (a.nz > 0) {                     // (always true: without the branch every column's words are read
-                                                   // ahead, 294 registers at 200 columns: one wave, 20% slower)
+        } else if (!LEAN || a.nz > 0) {            // (always; the branch keeps the reads of zw in place)
           const uint32_t word = zw[zrow[nb] + w];
           bh = expand_signs(__builtin_amdgcn_perm(word, word, psel), zmask[nb], zone[nb]);
         }
@@ -210,7 +210,7 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
     const int s0 = uc / kProjStage;
     const int nst = (col_end - uc + kProjStage - 1) / kProjStage;
     uint4 ring[P][NL], rdh[P][ND], rdl[P][ND];
-    if constexpr (ONE) {
+    if constexpr (DENSE && LEAN) {
       gload(ring[0], s0, col_end);
       rload(rdh[0], rdl[0], s0, col_end);
       to_lds(ring[0], s0);
@@ -330,9 +330,6 @@ __device__ __forceinline__ void project_rows_body(const ProjectArgs& a, int bx, 
   uint16_t* xt = reinterpret_cast<uint16_t*>(region) + wv * (ROWS * kProjSlice);
   float* red = reinterpret_cast<float*>(region);
   constexpr int RS = 16 * NB + 4;                                 // padded row of a reduction slot
-
-  if (a.zero_ptr != nullptr && bx == 0 && by == 0)
-    for (int idx = tid; idx < a.zero_count; idx += kBlock) a.zero_ptr[idx] = 0u;
 
   // loads: lane -> row 4j + lane/16 of the block (j = load index), 16-byte piece
   // p = (lane%16) ^ row of its slice, stored at LDS slot lane%16
@@ -538,21 +535,21 @@ __device__ __forceinline__ void project_rows_body(const ProjectArgs& a, int bx, 
 template <int RB, int NB, int NBD, int LD>
 constexpr bool kProjRows = NBD == 0 && LD == kLoadVec && RB <= 2 && RB * NB <= 4;
 
-template <int RB, int NB, int NBD, int LD, bool ONE>
+template <int RB, int NB, int NBD, int LD, bool LEAN>
 __device__ __forceinline__ void project_dispatch(const ProjectArgs& a, int bx, int by) {
   if constexpr (kProjRows<RB, NB, NBD, LD>) project_rows_body<RB, NB>(a, bx, by);
-  else project_body<RB, NB, NBD, LD, ONE>(a, bx, by);
+  else project_body<RB, NB, NBD, LD, LEAN>(a, bx, by);
 }
 
-template <int RB, int NB, int NBD, int LD, bool ONE>
+template <int RB, int NB, int NBD, int LD, bool LEAN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_kernel(ProjectArgs a) {
-  project_dispatch<RB, NB, NBD, LD, ONE>(a, blockIdx.x, blockIdx.y);
+  project_dispatch<RB, NB, NBD, LD, LEAN>(a, blockIdx.x, blockIdx.y);
 }
 
 // Projections of several layers in one launch (same instantiation): block (x, sample) of
 // job j at blk0[j] + sample * (T_pad / (16 RB rblocks)) + x.
-template <int RB, int NB, int NBD, int LD, bool ONE>
+template <int RB, int NB, int NBD, int LD, bool LEAN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kProjRows<RB, NB, NBD, LD> ? 3 : 1)))
 void project_batch_kernel(ProjectBatch bt) {
   const int blk = flat_block();
@@ -563,7 +560,7 @@ void project_batch_kernel(ProjectBatch bt) {
   const ProjectArgs& a = bt.job[jb];
   const int gx = a.T_pad / (16 * RB * a.rblocks);
   const int rel = blk - bt.blk0[jb];
-  project_dispatch<RB, NB, NBD, LD, ONE>(a, rel % gx, rel / gx);
+  project_dispatch<RB, NB, NBD, LD, LEAN>(a, rel % gx, rel / gx);
 }
 
 template <int RB, int NB>
@@ -644,11 +641,11 @@ static hipError_t launch_batch_rb_nb(ProjectBatch bt, hipStream_t st) {
     bt.blocks += (bt.job[j].T_pad / (16 * RB * bt.job[j].rblocks)) * bt.job[j].B;
   }
   const bool dense = bt.job[0].nd > 0;
-#define DPRC_PROJECT_BATCH_CASE(NBDV, ONEV)                                                                             \
+#define DPRC_PROJECT_BATCH_CASE(NBDV, LEANV)                                                                             \
   if (load == kLoadVec)                                                                                            \
-    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec, ONEV>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadVec, LEANV>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
   else                                                                                                             \
-    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny, ONEV>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
+    DPRC_LAUNCH((project_batch_kernel<RB, NB, NBDV, kLoadAny, LEANV>), flat_grid(bt.blocks), dim3(kBlock), lds, st, bt);       \
   return hipGetLastError();
   if (!dense) {
     if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_BATCH_CASE(0, false) }
@@ -710,17 +707,21 @@ static hipError_t launch_rb_nb(ProjectArgs a, hipStream_t st) {
   const int load = plan_rblocks<RB, NB>(&a, 1);
   const size_t lds = project_lds<RB, NB>(a);
   dim3 grid((unsigned)(a.T_pad / (16 * RB * a.rblocks)), (unsigned)a.B);
-#define DPRC_PROJECT_CASE(NBDV, ONEV)                                                                   \
+#define DPRC_PROJECT_CASE(NBDV, LEANV)                                                                   \
   if (load == kLoadVec)                                                                              \
-    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadVec, ONEV>), grid, dim3(kBlock), lds, st, a);          \
+    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadVec, LEANV>), grid, dim3(kBlock), lds, st, a);          \
   else if (load == kLoadAny)                                                                        \
-    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadAny, ONEV>), grid, dim3(kBlock), lds, st, a);          \
+    DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadAny, LEANV>), grid, dim3(kBlock), lds, st, a);          \
   else                                                                                              \
-    if constexpr (RB == 1) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadElem, ONEV>), grid, dim3(kBlock), lds, st, a); \
+    if constexpr (RB == 1) DPRC_LAUNCH((project_kernel<RB, NB, NBDV, kLoadElem, LEANV>), grid, dim3(kBlock), lds, st, a); \
     else return hipErrorInvalidValue;                                                               \
   return hipGetLastError();
   if (a.nd == 0) {
-    if constexpr (kProjSigns<RB, NB>) { DPRC_PROJECT_CASE(0, false) }
+    if constexpr (kProjSigns<RB, NB>) {
+      if constexpr (NB == 16)
+        if (2 * lds <= 160 * 1024 && (int64_t)grid.x * grid.y > 256) { DPRC_PROJECT_CASE(0, true) }
+      DPRC_PROJECT_CASE(0, false)
+    }
   } else if constexpr (kProjDense<RB, NB>) {
     if (a.m <= kProjStage) { DPRC_PROJECT_CASE(NB, true) }
     DPRC_PROJECT_CASE(NB, false)
@@ -757,7 +758,7 @@ hipError_t launch_project(const ProjectArgs& args, int rows_per_wg, hipStream_t 
   }
 }
 
-// ---- probe bits (verification export and the fp32 path) -------------------------
+// ---- probe bits (verification export) ------------------------------------------
 __global__ void probe_bits_kernel(int kind, uint32_t key0, uint32_t key1, uint32_t layer,
                                   uint32_t stream_id, int64_t m, int32_t k, uint32_t* out) {
   const int64_t nw = (m + 31) >> 5;
@@ -789,19 +790,6 @@ hipError_t launch_probe_bits(int kind, uint32_t key0, uint32_t key1, uint32_t la
   if (total == 0) return hipSuccess;
   DPRC_LAUNCH(probe_bits_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, st,
                      kind, key0, key1, layer, stream_id, m, k, out);
-  return hipGetLastError();
-}
-
-__global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n;
-       idx += (int64_t)gridDim.x * blockDim.x)
-    p[idx] = v;
-}
-
-hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)std::min<int64_t>(1024, ceil_div(n, 256));
-  DPRC_LAUNCH(fill_u32_kernel, dim3(blocks), dim3(256), 0, st, p, n, v);
   return hipGetLastError();
 }
 

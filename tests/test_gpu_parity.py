@@ -267,6 +267,18 @@ def test_batched_reductions_of_many_samples(D, B, T, d, k, probe):
     assert np.all(_rel(n2.cpu().numpy(), per.sum(0).cpu().numpy()) < 1e-6)
 
 
+@pytest.mark.parametrize("k", [193, 225, 226])
+def test_sign_columns_in_few_and_many_workgroups(D, k):
+    # 256 padded columns: from 257 workgroups on the registers are held to two of them per CU where
+    # the LDS has room for two (up to 225 columns)
+    A, E = _draw(40, 130, 24, 1100, layer=840)
+    n2 = D.dprc_norm_hutch([(A, E, 3)], k, 8)
+    few = torch.cat([D.dprc_norm_hutch([(A[i:i + 4], E[i:i + 4], 3)], k, 8) for i in range(0, 40, 4)])
+    assert np.all(_rel(n2.cpu().numpy(), few.cpu().numpy()) < 1e-6)
+    ref = est.hutch_layer(_np(A[-2:]), _np(E[-2:]), k, 8, 3)
+    assert np.all(_rel(n2[-2:].cpu().numpy(), ref) < NORM_RTOL)
+
+
 @pytest.mark.parametrize("s,r", [(4, 5), (5, 200), (16, 33), (32, 64)])
 def test_hutchpp_expansions_of_one_and_four_waves(D, s, r):
     # 2 blocks of rows per sample: 1200 workgroups of one wave, 120 of four
