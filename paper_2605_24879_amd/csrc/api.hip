@@ -248,7 +248,6 @@ void pass_args(const PassSpec& ps, int64_t B, int64_t T, uint32_t k0, uint32_t k
   pa.words_per_chunk = words_per_chunk(ps.m, ps.nz);
   pa.Yt = Yt; pa.yt_ld = B * tp.T_pad;
   pa.ylo_off = (int64_t)ncols_pad * pa.yt_ld; pa.ncols_write = ncols_pad;
-  pa.zero_ptr = nullptr; pa.zero_count = 0;
   pa.vec = rows16(ps.X, ps.ldx);
 
   ta.X = ps.Xo; ta.ldx = ps.ldo; ta.x_ss = T * ps.ldo;
@@ -485,7 +484,6 @@ dprc_status hutch_group(const View* v, int G, int32_t k, int probe, uint32_t k0,
     pa.Yt = Yt + (int64_t)l * k * yt_ld; pa.yt_ld = yt_ld;
     pa.ylo_off = (int64_t)ncols_pad * yt_ld;
     pa.ncols_write = G == 1 ? pa.ncols_pad : k;   // inside a shared Y only the layer's own columns
-    pa.zero_ptr = nullptr; pa.zero_count = 0;
     pa.vec = rows16(w.X, w.ldx);
     if (pjobs) {                                   // collected: the caller launches them in batches
       pjobs[(*npj)++] = pa;

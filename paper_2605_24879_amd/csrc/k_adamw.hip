@@ -18,7 +18,10 @@ constexpr int kAT = 64;
 // with non-temporal loads and stores: the seven layers of a decoder block, 1.8 GB, went from
 // 392 to 375 us; with only the loads or only the stores marked they stayed at 392.  Smaller
 // layers may still be cached from the accumulation or the step before, and were 8 to 20%
-// slower marked (2048 x 2048: 20.2 us against 24.3, repeated).
+// slower marked (2048 x 2048: 20.2 us against 24.3, repeated).  Just above the line a layer that
+// is updated over and over with nothing between still finds part of itself cached (2048 x
+// 5120, 280 MB: 48 us plain, 62 marked), but a step's passes over the model lie between two
+// updates, and with 1 GB touched there it is 81 and 66.
 constexpr int64_t kStreamBytes = 256 << 20;
 
 typedef float f4_t __attribute__((ext_vector_type(4)));

@@ -43,7 +43,7 @@ struct GInt {
 // GM = 128: quarter `sub` of that tile, four waves of 64 x 64; three such workgroups share a
 // CU.  A quarter's entries are summed in the same order as the whole tile's.  split: the
 // token split.
-template <int GM, int NS, int LD>
+template <int GM, int LD>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split, int sub = 0) {
   constexpr int NW = GM == 256 ? 8 : 4;
   constexpr int kThreads = 64 * NW;
@@ -75,7 +75,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split, 
   const int lr = tid / TPR, lc = (tid % TPR) * 8;          // loads: rows lr + RP q, 8 columns at lc
   const int64_t ja = (int64_t)d0 + lc, je = (int64_t)p0 + lc;
 
-  uint4 ga[NS][RQ], ge[NS][RQ];                   // slabs in flight
+  constexpr int NS = 2;                           // slabs in flight
+  uint4 ga[NS][RQ], ge[NS][RQ];
   // kLoadVec: per slab one buffer resource per operand over its (up to) 32 token rows,
   // starting at the tile's first column; rows past T and columns past d / p read
   // as zero through out-of-range offsets, and a slab past the sample's last one has
@@ -237,24 +238,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split, 
     for (; st + 2 * NS <= st_hi; st += 2 * NS) {
       step(st, GInt<0>{});
       step(st + 1, GInt<1>{});
-      if constexpr (NS > 1) {
-        step(st + 2, GInt<2>{});
-        step(st + 3, GInt<3>{});
-      }
-      if constexpr (NS > 2) {
-        step(st + 4, GInt<4>{});
-        step(st + 5, GInt<5>{});
-      }
+      step(st + 2, GInt<2>{});
+      step(st + 3, GInt<3>{});
     }
     if (st < st_hi) step(st, GInt<0>{});
-    if constexpr (NS > 1) {
-      if (st + 1 < st_hi) step(st + 1, GInt<1>{});
-      if (st + 2 < st_hi) step(st + 2, GInt<2>{});
-    }
-    if constexpr (NS > 2) {
-      if (st + 3 < st_hi) step(st + 3, GInt<3>{});
-      if (st + 4 < st_hi) step(st + 4, GInt<4>{});
-    }
+    if (st + 1 < st_hi) step(st + 1, GInt<1>{});
+    if (st + 2 < st_hi) step(st + 2, GInt<2>{});
     __syncthreads();                               // the last reads of both buffers are done
   }
 
@@ -287,22 +276,24 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, int wg, int split, 
     }
 }
 
-template <int NS, int LD>
+template <int LD>
 __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs a) {
-  gemm_body<kGM, NS, LD>(a, blockIdx.x, blockIdx.y);
+  gemm_body<kGM, LD>(a, blockIdx.x, blockIdx.y);
 }
 
-// Quarters of the tiles from `first` on, four workgroups each.
-template <int NS, int LD>
+// Quarters of the tiles from `first` on, four workgroups each.  (Workgroups go to the XCDs in
+// turn, so the quarters of a tile, which share its slabs, sit on four of them, and the order
+// of the tiles among the XCDs is not the whole tiles' one.)
+template <int LD>
 __global__ __launch_bounds__(256) void gemm_quarters_kernel(GemmArgs a, int first) {
-  gemm_body<kGM / 2, NS, LD>(a, first + (int)blockIdx.x / 4, 0, (int)blockIdx.x % 4);
+  gemm_body<kGM / 2, LD>(a, first + (int)blockIdx.x / 4, 0, (int)blockIdx.x % 4);
 }
 
 // Several layers in one launch, each unsplit (S = 1): job j owns blocks blk0[j] ..
 // blk0[j] + ntiles_j - 1, and blk0[j] is a multiple of 8, so that a job's blocks are
 // dealt to the XCDs as those of a launch of its own; blocks up to the next multiple of
-// 8 are idle.  QUARTERS: four workgroups per block.
-template <int NS, int LD, bool QUARTERS>
+// 8 are idle.  QUARTERS: four workgroups per block, on four XCDs as above.
+template <int LD, bool QUARTERS>
 __global__ __launch_bounds__(QUARTERS ? 256 : 512, 1) void gemm_batch_kernel(GemmBatch bt) {
   const int blk = QUARTERS ? (int)blockIdx.x / 4 : (int)blockIdx.x;
   int jb = 0;
@@ -311,8 +302,8 @@ __global__ __launch_bounds__(QUARTERS ? 256 : 512, 1) void gemm_batch_kernel(Gem
   const GemmArgs& a = bt.job[jb];
   const int wg = blk - bt.blk0[jb];
   if (wg >= (int)(((int64_t)a.d + kGM - 1) / kGM * (((int64_t)a.p + kGM - 1) / kGM))) return;
-  if constexpr (QUARTERS) gemm_body<kGM / 2, NS, LD>(a, wg, 0, (int)blockIdx.x % 4);
-  else gemm_body<kGM, NS, LD>(a, wg, 0);
+  if constexpr (QUARTERS) gemm_body<kGM / 2, LD>(a, wg, 0, (int)blockIdx.x % 4);
+  else gemm_body<kGM, LD>(a, wg, 0);
 }
 
 GemmPlan gemm_plan_v2(int64_t B, int64_t T, int64_t d, int64_t p) {
@@ -340,7 +331,7 @@ static int gemm_load(const GemmArgs& a) {        // offsets within one slab stay
 hipError_t launch_gemm(const GemmArgs& a, int64_t ntiles, hipStream_t st) {
   const dim3 grid((unsigned)ntiles, (unsigned)a.S);
   const int load = gemm_load(a);
-#define DPRC_K(LD) gemm_kernel<2, LD>
+#define DPRC_K(LD) gemm_kernel<LD>
   DPRC_GEMM_LOADS(DPRC_K, grid, dim3(512), a)
 #undef DPRC_K
   return hipGetLastError();
@@ -350,7 +341,7 @@ hipError_t launch_gemm_quarters(const GemmArgs& a, int64_t first, int64_t ntiles
   if (a.S != 1 || ntiles < 1 || 4 * ntiles >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(4 * ntiles));
   const int load = gemm_load(a);
-#define DPRC_K(LD) gemm_quarters_kernel<2, LD>
+#define DPRC_K(LD) gemm_quarters_kernel<LD>
   DPRC_GEMM_LOADS(DPRC_K, grid, dim3(256), a, (int)first)
 #undef DPRC_K
   return hipGetLastError();
@@ -371,12 +362,12 @@ hipError_t launch_gemm_batch(GemmBatch bt, hipStream_t st) {
   if (4 * blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   if (tiles <= kGemmQuarterTiles) {
     const dim3 grid((unsigned)(4 * blocks));
-#define DPRC_K(LD) gemm_batch_kernel<2, LD, true>
+#define DPRC_K(LD) gemm_batch_kernel<LD, true>
     DPRC_GEMM_LOADS(DPRC_K, grid, dim3(256), bt)
 #undef DPRC_K
   } else {
     const dim3 grid((unsigned)blocks);
-#define DPRC_K(LD) gemm_batch_kernel<2, LD, false>
+#define DPRC_K(LD) gemm_batch_kernel<LD, false>
     DPRC_GEMM_LOADS(DPRC_K, grid, dim3(512), bt)
 #undef DPRC_K
   }

@@ -82,8 +82,6 @@ struct ProjectArgs {
   int64_t yt_ld;            // B * T_pad
   int64_t ylo_off;
   int32_t ncols_write;      // columns written (ncols_pad, or only the real ones inside a shared Y)
-  uint32_t* zero_ptr;       // counters cleared by workgroup (0,0) (may be null)
-  int32_t zero_count;
   int32_t vec;              // token rows of X are 16-byte aligned: 16-byte loads
   int32_t rblocks;          // row blocks per workgroup (set by the launcher)
 };
@@ -381,7 +379,6 @@ struct GaussBatch {
   GaussJob job[kGaussMaxJobs];
 };
 hipError_t launch_gauss_batch(GaussBatch bt, hipStream_t st);
-hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_project(const ProjectArgs& a, int rows_per_wg, hipStream_t st);
 hipError_t launch_project_batch(ProjectBatch bt, int rows_per_wg, hipStream_t st);   // <= 64 columns
 hipError_t launch_tokred_batch(TokredBatch bt, hipStream_t st);                      // <= kTokBatchCols columns
