@@ -108,10 +108,14 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
 
 
 def _stream(dev):
-    """torch's current stream on the GPU `dev`, as a pointer."""
-    if dev.type != "cuda":
-        raise ValueError(f"expected a GPU device, not {dev}")
-    return ctypes.c_void_p(_raw_stream(dev.index if dev.index is not None else torch.cuda.current_device()))
+    """torch's current stream on a tensor's device, as a pointer.  A tensor on a GPU has a device with
+    an index, one in host memory a device without (asking every device for its type costs 0.2 us)."""
+    index = dev.index
+    if index is None:
+        if dev.type != "cuda":
+            raise ValueError(f"expected a GPU device, not {dev}")
+        index = torch.cuda.current_device()
+    return ctypes.c_void_p(_raw_stream(index))
 
 
 def _dtype_code(t):
@@ -364,7 +368,7 @@ def dprc_pld_step(sigma, p, h, n_half, ybar=None, w=None, device=None):
     _check(lib().dprc_pld_step(float(sigma), float(p), float(h), n_half,
                                ybar.data_ptr() if ybar is not None else None,
                                w.data_ptr() if w is not None else None, ybar.numel() if ybar is not None else 0,
-                               q.data_ptr(), q_inf.data_ptr(), ws.data_ptr(), need, _stream(dev)))
+                               q.data_ptr(), q_inf.data_ptr(), ws.data_ptr(), need, _stream(q.device)))
     return q, q_inf
 
 

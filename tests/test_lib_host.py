@@ -298,6 +298,7 @@ def test_tensors_that_are_not_on_a_gpu_are_refused(monkeypatch):
                  lambda: dprc.dprc_envelope_middle(host[0].double(), 4, 3, 5), lambda: dprc.dprc_chi2_cdf(host[0].double(), 4),
                  lambda: dprc.dprc_probe_bits(0, 0, 0, 0, 32, 4, out=torch.zeros(4, 1, dtype=torch.int32)),
                  lambda: dprc.dprc_probe_gaussian(0, 0, 8, 4, out=host), lambda: dprc.dprc_pld_step(1.0, 0.1, 0.1, 3, device="cpu"),
+                 lambda: dprc.dprc_pld_step(1.0, 0.1, 0.1, 3, device="cpu:0"),
                  lambda: dprc.dprc_norm_hutch([(host[None], host[None], 0)], 4, 0)):
         with pytest.raises(ValueError):
             call()
