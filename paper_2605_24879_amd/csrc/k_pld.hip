@@ -17,7 +17,7 @@
 //   all of them (four lanes per cut; the bins' 1/mu and mu/2 are computed once per wave), and
 //   the lanes' and waves' sums are added in order.  Bound by fp64 arithmetic, two normal
 //   tails per bin and cut: 4000 bins and 40000 cuts took 2241 us with a thread per cut and two
-//   erfc per bin, 420 us here (750 with erfc and 64 cuts per workgroup, 590 with the shared
+//   erfc per bin, 327 us here (750 with erfc and 64 cuts per workgroup, 590 with the shared
 //   exponential; the 20000 cuts above the support then left a third of the CUs idle at the end).
 // * pld_masses_kernel: cell masses of the grid t_j = (j - n + 1) h, j < 2n - 1,
 //   as decrements of S between the cuts around each cell (clamped at zero); the

@@ -143,7 +143,7 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int bx, int b
     }
   };
   // Issued after the multiply, into the fragments it has just used: loaded with X before it, they
-  // needed a second set of registers and copies (Hutch++ on a decoder block 1860 -> 1839 us).
+  // needed a second set of registers and copies (Hutch++ on a decoder block 1860 -> 1836 us).
   auto rload = [&](uint4 (&dh)[ND], uint4 (&dl)[ND], int st, int col_end) __attribute__((always_inline)) {
     const int c0 = st * kProjStage + kProjSlice * wv;
     if constexpr (DENSE) {
