@@ -299,9 +299,11 @@ hipError_t launch_tokred_f32(const TokredF32Args& a, hipStream_t st) {
 // double-buffered LDS, two slabs ahead in registers.  Each sample is summed by itself and
 // then added, scaled by its factor; samples with factor 0 are skipped.  Bound by the fp32
 // matrix rate (157 TFLOP/s) from 256 tiles up: 1024 x 4096 over 2048 tokens took 4144 us with
-// one thread per entry and takes 168 us here (102 TFLOP/s).
-// Against 177 us of an earlier form of this kernel, slabs of 16 tokens measured 194, 128 x 64 tiles of four waves with two workgroups per CU
-// 189, the 32x32x2 MFMA 196, fragment reads pinned ahead of the MFMAs 176.
+// one thread per entry and takes 168 us here (102 TFLOP/s).  When it took 177, slabs of 16
+// tokens measured 194 us, 128 x 64 tiles of four waves with two workgroups per CU 189, the
+// 32x32x2 MFMA 196, fragment reads pinned ahead of the MFMAs 176.  One to four tokens in all
+// over more than 256 tiles are bound by the stores of the second round (1027 x 4097: 17 us, 10
+// with one thread per entry; 27 with 64-wide tiles).
 constexpr int kFK = 32;                          // tokens per slab
 
 // NARROW: operands less than 4 wide (or strides past 32-bit offsets), read by element.
